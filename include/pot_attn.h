@@ -234,18 +234,18 @@ pot_status pot_workspace_init(void* workspace, size_t ws_bytes, void* stream);
  *               time.
  * Steps: q is rotated (if hadamard) and quantised to int8 with step
  * Delta = amax/127; each score is the exact int32 sum of sign-flipped
- * shifts of q^ (eq. sac: the products q^ 2^(F-e) are formed by packed 16-bit
- * arithmetic shifts of q^ 2^7; the signs and the sum are applied by
- * v_dot2_i32_i16, the dot unit's multiply-add, with weights +-1, 0 for the
- * zero code; PoT-Mk adds one such sum per mantissa bit plane, combined
- * by shifts); x = acc * s * Delta * log2(e) * 2^-(F+k) / 8 in a fixed fp32
+ * shifts of q^ (eq. sac), regrouped by bit position: one sum of q^ with
+ * weights -1, 0 or +1 per position of the code magnitudes (7 + k of them),
+ * each shifted by its position (matrix cores: fp4 operands that hold only
+ * those three values, shifts as power-of-two block scales, every partial sum
+ * exact in fp32); x = acc * s * Delta * log2(e) * 2^-(F+k) / 8 in a fixed fp32
  * order; the running maximum is the integer M = ceil(max x)
  * (eq. logsm) so rescales are exact powers of two; weights 2^(x-M) multiply
  * the fp16 values with fp32 accumulation (matrix cores, weights split into
  * fp16 high and low parts); key splits (chosen to fill the GPU's resident
  * workgroup slots in one round) are merged with exact 2^(M_s - M) factors.
- * Launches: a query-preparation kernel, the split decode kernel and, with
- * more than one split, a combine kernel, all on `stream`.
+ * Launches: the split decode kernel (which prepares the queries) and, with
+ * more than one split, a combine kernel, both on `stream`.
  */
 pot_status pot_decode_attention(const pot_format* fmt, const float* q,
                                 const uint8_t* codes_se,
@@ -290,8 +290,8 @@ pot_status pot_append_decode_attention(const pot_format* fmt, const float* q,
  * int32 scores and integer maxima are the same as with fp16 values. In the
  * kernel each workgroup takes g_ref = min g over its keys and forms the
  * weights p 2^(g_ref - g_t) (exact, never above p) for the matrix cores,
- * with the value bytes read as the fp16 numbers 1152 + v^; the 1152 offset
- * and 2^-g_ref are applied to the fp32 sums. Arguments, workspace, taps and
+ * with the value bytes read as the fp16 numbers v^ (exact); 2^-g_ref is
+ * applied to the fp32 sums. Arguments, workspace, taps and
  * errors as pot_decode_attention, with (v_u8, v_exp) in place of v_cache
  * (NULL or not 16-byte aligned -> INVALID_ARG); engine outside {0, 1} ->
  * INVALID_ARG. */

@@ -12,36 +12,29 @@
 // partial sums.
 //
 // Per 64-key tile and wave:
-//  1. Scores, one key per lane (Sec. II-B eq. sac). PoT-4: the key's 32 code
-//     bytes arrive as two 16-byte loads. Each query operand holds two
-//     elements of one head as signed 16-bit halves, q 2^7 (prepared once per
-//     kv head, read through the scalar cache in chunks of two element pairs,
-//     each requested while the previous one is used). v_pk_ashrrev_i16
-//     (inline assembly, which reads the exponent nibbles in place) shifts
-//     each half by its element's exponent e:
-//     q 2^7 >> e = q 2^(7 - e), exact since the low 7 bits are clear, so
-//     every product q 2^(7 - e) is formed by the shifter with head-room
-//     F_int = 7 >= e (eq. exact). v_dot2_i32_i16 then applies the signs and
-//     sums both halves into the int32 score: it is the dot unit's integer
-//     multiply-add, used here with weights sigma in {-1, +1} (0 for the zero
-//     code), so its multipliers only ever see -1, 0 or +1. PoT-Mk (Sec.
-//     II-D) adds one sum per mantissa bit plane b over the same shifted
-//     operands, with weight sigma where bit b of the element's mantissa is
-//     set and 0 elsewhere; the key's sum is 2^k S_lead + sum_b 2^b S_b, the
-//     per-bit shifts of eq. sac regrouped by plane. The decoded-code engines
-//     (a multiply path) instead decode each code once per key into dot-unit
-//     weights shared by all G heads: PoT-4 into int8 bytes sigma 2^(6 - e)
-//     for v_dot4_i32_i8, PoT-Mk into 16-bit sigma (2^k + j) 2^(7 - e) for
-//     v_dot2_i32_i16; the int32 sums equal the shift-accumulate ones.
+//  1. Scores (Sec. II-B eq. sac). Shift-accumulate: exact integer sums on the
+//     matrix cores, one ternary operand per bit position, scaled by powers of
+//     two (score_planes.hpp). A lane ends up with the scores of one head and
+//     8 consecutive keys, the operand order of step 4. (Packed 16-bit shifts
+//     and v_dot2 sums on the VALU, one key per lane, took 741 / 1119 / 2261
+//     VALU lane-operations per key at k = 0 / 1 / 4 and were bound by their
+//     issue: B = 64, T = 32768, PoT-4 222 us per call, now 202; B = 8, T =
+//     32768, PoT-M4 80 us, now 41; B = 16, T = 16384, PoT-4 with INT8 values
+//     39 us, now 28.) The decoded-code engines (a multiply path) decode each
+//     code once per key into dot-unit weights shared by all G heads, one key
+//     per lane: PoT-4 into int8 bytes sigma 2^(6 - e) for v_dot4_i32_i8,
+//     PoT-Mk into 16-bit sigma (2^k + j) 2^(7 - e) for v_dot2_i32_i16; the
+//     int32 sums equal the shift-accumulate ones, and are staged transposed in
+//     wave-private LDS.
 //  2. x = fl32(fl32(float(acc) * s) * c), c = fl32(fl32(Delta * log2 e) *
-//     2^-(F+k+3)) in this order; x is staged transposed in wave-private LDS.
+//     2^-(F+k+3)) in this order.
 //  3. Integer running maximum M = max(M, ceil(max x)) per head (eq. logsm);
 //     when it rises the accumulators are rescaled by the exact power of two
 //     2^(M_old - M_new).
 //  4. A.V on the matrix cores: P (16 rows = 8 heads x {fp16 high part, fp16
 //     low part} of p = 2^(x - M + 12)) times V (fp16) with
-//     v_mfma_f32_16x16x32_f16, fp32 accumulation; a fifth column block of
-//     ones yields the row sums l. The value cache is stored token-interleaved
+//     v_mfma_f32_16x16x32_f16, fp32 accumulation; the sums l of p are per
+//     lane in fp32. The value cache is stored token-interleaved
 //     ([t/8][d][t%8]) so a lane's 16-byte load is exactly its B fragment.
 // With one split the workgroup writes O directly; otherwise it writes its
 // (M_s, l_s, o_s) and a small combine kernel merges the splits with exact
@@ -60,6 +53,7 @@
 
 #include "pot_device.hpp"
 #include "pot_launch.hpp"
+#include "score_planes.hpp"
 
 namespace potattn {
 
@@ -68,219 +62,6 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-// Shift-accumulate of one element pair for G heads (G = 2, 4 or 8): each
-// head's uniform word q[h] (operands q 2^7 of elements 8c + n and 8c + n + 4)
-// is shifted right arithmetically per half by the low four bits of the
-// matching half of sh, and the result is added into the head's int32 sum
-// a[h] by v_dot2_i32_i16 with the pair's weights w (1, -1 or 0 per half); the
-// first pair of a key starts the sums from 0. v_pk_ashrrev_i16 reads only
-// those four bits, so the caller need not clear the bits above them (a C++
-// vector shift needs every amount below 16 and so costs a mask). Heads go two
-// at a time, both shifts before both sums, so each v_dot2 reads a result
-// written two instructions earlier; one block for all G heads leaves the
-// compiler no boundary between them at which to add wait states.
-#define POT_SAC_SH(t, h) "v_pk_ashrrev_i16 %" #t ", %[sh], %[q" #h "]\n\t"
-#define POT_SAC_D0(h, t) "v_dot2_i32_i16 %[a" #h "], %" #t ", %[w], 0\n\t"
-#define POT_SAC_DC(h, t) "v_dot2c_i32_i16 %[a" #h "], %" #t ", %[w]\n\t"
-#define POT_SAC_2(D, x, y) POT_SAC_SH(0, x) POT_SAC_SH(1, y) D(x, 0) D(y, 1)
-template <int G, bool kFirst>
-__device__ __forceinline__ void sac_heads(int32_t* a, const uint32_t* q, uint32_t sh, uint32_t w) {
-  static_assert(G == 2 || G == 4 || G == 8, "two, four or eight heads");
-  uint32_t t0, t1;
-  if constexpr (G == 2) {
-    if constexpr (kFirst)
-      asm(POT_SAC_2(POT_SAC_D0, 0, 1)
-          : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[0]), [a1] "=&v"(a[1])
-          : [sh] "v"(sh), [w] "v"(w), [q0] "s"(q[0]), [q1] "s"(q[1]));
-    else
-      asm(POT_SAC_2(POT_SAC_DC, 0, 1)
-          : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[0]), [a1] "+v"(a[1])
-          : [sh] "v"(sh), [w] "v"(w), [q0] "s"(q[0]), [q1] "s"(q[1]));
-  } else if constexpr (G == 4) {
-    if constexpr (kFirst)
-      asm(POT_SAC_2(POT_SAC_D0, 0, 1) POT_SAC_2(POT_SAC_D0, 2, 3)
-          : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[0]), [a1] "=&v"(a[1]), [a2] "=&v"(a[2]),
-            [a3] "=&v"(a[3])
-          : [sh] "v"(sh), [w] "v"(w), [q0] "s"(q[0]), [q1] "s"(q[1]), [q2] "s"(q[2]),
-            [q3] "s"(q[3]));
-    else
-      asm(POT_SAC_2(POT_SAC_DC, 0, 1) POT_SAC_2(POT_SAC_DC, 2, 3)
-          : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[0]), [a1] "+v"(a[1]), [a2] "+v"(a[2]),
-            [a3] "+v"(a[3])
-          : [sh] "v"(sh), [w] "v"(w), [q0] "s"(q[0]), [q1] "s"(q[1]), [q2] "s"(q[2]),
-            [q3] "s"(q[3]));
-  } else {
-    if constexpr (kFirst)
-      asm(POT_SAC_2(POT_SAC_D0, 0, 1) POT_SAC_2(POT_SAC_D0, 2, 3)
-              POT_SAC_2(POT_SAC_D0, 4, 5) POT_SAC_2(POT_SAC_D0, 6, 7)
-          : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[0]), [a1] "=&v"(a[1]), [a2] "=&v"(a[2]),
-            [a3] "=&v"(a[3]), [a4] "=&v"(a[4]), [a5] "=&v"(a[5]), [a6] "=&v"(a[6]),
-            [a7] "=&v"(a[7])
-          : [sh] "v"(sh), [w] "v"(w), [q0] "s"(q[0]), [q1] "s"(q[1]), [q2] "s"(q[2]),
-            [q3] "s"(q[3]), [q4] "s"(q[4]), [q5] "s"(q[5]), [q6] "s"(q[6]), [q7] "s"(q[7]));
-    else
-      asm(POT_SAC_2(POT_SAC_DC, 0, 1) POT_SAC_2(POT_SAC_DC, 2, 3)
-              POT_SAC_2(POT_SAC_DC, 4, 5) POT_SAC_2(POT_SAC_DC, 6, 7)
-          : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[0]), [a1] "+v"(a[1]), [a2] "+v"(a[2]),
-            [a3] "+v"(a[3]), [a4] "+v"(a[4]), [a5] "+v"(a[5]), [a6] "+v"(a[6]),
-            [a7] "+v"(a[7])
-          : [sh] "v"(sh), [w] "v"(w), [q0] "s"(q[0]), [q1] "s"(q[1]), [q2] "s"(q[2]),
-            [q3] "s"(q[3]), [q4] "s"(q[4]), [q5] "s"(q[5]), [q6] "s"(q[6]), [q7] "s"(q[7]));
-  }
-}
-// The same for one mantissa bit plane (k = 1): each shifted operand also goes
-// into the head's plane sum c[h] with the plane weights m (sigma where the
-// element's mantissa bit is set, else 0).
-#define POT_SAC1_D0(h, t)                                 \
-  "v_dot2_i32_i16 %[a" #h "], %" #t ", %[w], 0\n\t" \
-  "v_dot2_i32_i16 %[c" #h "], %" #t ", %[m], 0\n\t"
-#define POT_SAC1_DC(h, t)                              \
-  "v_dot2c_i32_i16 %[a" #h "], %" #t ", %[w]\n\t" \
-  "v_dot2c_i32_i16 %[c" #h "], %" #t ", %[m]\n\t"
-template <int G, bool kFirst>
-__device__ __forceinline__ void sac_heads_m1(int32_t* a, int32_t* c, const uint32_t* q, uint32_t sh,
-                                             uint32_t w, uint32_t m) {
-  static_assert(G == 2 || G == 4 || G == 8, "two, four or eight heads");
-  uint32_t t0, t1;
-  if constexpr (G == 2) {
-    if constexpr (kFirst)
-      asm(POT_SAC_2(POT_SAC1_D0, 0, 1)
-          : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[0]), [a1] "=&v"(a[1]), [c0] "=&v"(c[0]), [c1] "=&v"(c[1])
-          : [sh] "v"(sh), [w] "v"(w), [m] "v"(m), [q0] "s"(q[0]), [q1] "s"(q[1]));
-    else
-      asm(POT_SAC_2(POT_SAC1_DC, 0, 1)
-          : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[0]), [a1] "+v"(a[1]), [c0] "+v"(c[0]), [c1] "+v"(c[1])
-          : [sh] "v"(sh), [w] "v"(w), [m] "v"(m), [q0] "s"(q[0]), [q1] "s"(q[1]));
-  } else if constexpr (G == 4) {
-    if constexpr (kFirst)
-      asm(POT_SAC_2(POT_SAC1_D0, 0, 1) POT_SAC_2(POT_SAC1_D0, 2, 3)
-          : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[0]), [a1] "=&v"(a[1]), [a2] "=&v"(a[2]), [a3] "=&v"(a[3]), [c0] "=&v"(c[0]), [c1] "=&v"(c[1]), [c2] "=&v"(c[2]), [c3] "=&v"(c[3])
-          : [sh] "v"(sh), [w] "v"(w), [m] "v"(m), [q0] "s"(q[0]), [q1] "s"(q[1]), [q2] "s"(q[2]), [q3] "s"(q[3]));
-    else
-      asm(POT_SAC_2(POT_SAC1_DC, 0, 1) POT_SAC_2(POT_SAC1_DC, 2, 3)
-          : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[0]), [a1] "+v"(a[1]), [a2] "+v"(a[2]), [a3] "+v"(a[3]), [c0] "+v"(c[0]), [c1] "+v"(c[1]), [c2] "+v"(c[2]), [c3] "+v"(c[3])
-          : [sh] "v"(sh), [w] "v"(w), [m] "v"(m), [q0] "s"(q[0]), [q1] "s"(q[1]), [q2] "s"(q[2]), [q3] "s"(q[3]));
-  } else if constexpr (G == 8) {
-    if constexpr (kFirst)
-      asm(POT_SAC_2(POT_SAC1_D0, 0, 1) POT_SAC_2(POT_SAC1_D0, 2, 3) POT_SAC_2(POT_SAC1_D0, 4, 5) POT_SAC_2(POT_SAC1_D0, 6, 7)
-          : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[0]), [a1] "=&v"(a[1]), [a2] "=&v"(a[2]), [a3] "=&v"(a[3]), [a4] "=&v"(a[4]), [a5] "=&v"(a[5]), [a6] "=&v"(a[6]), [a7] "=&v"(a[7]), [c0] "=&v"(c[0]), [c1] "=&v"(c[1]), [c2] "=&v"(c[2]), [c3] "=&v"(c[3]), [c4] "=&v"(c[4]), [c5] "=&v"(c[5]), [c6] "=&v"(c[6]), [c7] "=&v"(c[7])
-          : [sh] "v"(sh), [w] "v"(w), [m] "v"(m), [q0] "s"(q[0]), [q1] "s"(q[1]), [q2] "s"(q[2]), [q3] "s"(q[3]), [q4] "s"(q[4]), [q5] "s"(q[5]), [q6] "s"(q[6]), [q7] "s"(q[7]));
-    else
-      asm(POT_SAC_2(POT_SAC1_DC, 0, 1) POT_SAC_2(POT_SAC1_DC, 2, 3) POT_SAC_2(POT_SAC1_DC, 4, 5) POT_SAC_2(POT_SAC1_DC, 6, 7)
-          : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[0]), [a1] "+v"(a[1]), [a2] "+v"(a[2]), [a3] "+v"(a[3]), [a4] "+v"(a[4]), [a5] "+v"(a[5]), [a6] "+v"(a[6]), [a7] "+v"(a[7]), [c0] "+v"(c[0]), [c1] "+v"(c[1]), [c2] "+v"(c[2]), [c3] "+v"(c[3]), [c4] "+v"(c[4]), [c5] "+v"(c[5]), [c6] "+v"(c[6]), [c7] "+v"(c[7])
-          : [sh] "v"(sh), [w] "v"(w), [m] "v"(m), [q0] "s"(q[0]), [q1] "s"(q[1]), [q2] "s"(q[2]), [q3] "s"(q[3]), [q4] "s"(q[4]), [q5] "s"(q[5]), [q6] "s"(q[6]), [q7] "s"(q[7]));
-  }
-}
-#undef POT_SAC1_DC
-#undef POT_SAC1_D0
-// The same for k = 2, 3 or 4 mantissa bit planes, H = 2 or 4 heads per block
-// (the operand count of one statement is limited): plane b's sum of head h is
-// c[b][h0 + h], with the plane weights m[b].
-#define POT_DOT0(acc, t, wt) "v_dot2_i32_i16 %[" acc "], %" #t ", %[" wt "], 0\n\t"
-#define POT_DOTC(acc, t, wt) "v_dot2c_i32_i16 %[" acc "], %" #t ", %[" wt "]\n\t"
-#define POT_HEAD_K2(D, h, t) D("a" #h, t, "w") D("c0" #h, t, "m0") D("c1" #h, t, "m1")
-#define POT_HEAD_K3(D, h, t) POT_HEAD_K2(D, h, t) D("c2" #h, t, "m2")
-#define POT_HEAD_K4(D, h, t) POT_HEAD_K3(D, h, t) D("c3" #h, t, "m3")
-#define POT_PAIR(HK, D, x, y) POT_SAC_SH(0, x) POT_SAC_SH(1, y) HK(D, x, 0) HK(D, y, 1)
-template <int H, int K, int G, bool kFirst>
-__device__ __forceinline__ void sac_heads_mk(int32_t* a, int32_t (*c)[G], int h0, const uint32_t* q,
-                                             uint32_t sh, uint32_t w, const uint32_t* m) {
-  static_assert((H == 2 && K >= 2 && K <= 4) || (H == 4 && (K == 2 || K == 3)),
-                "two heads with two to four planes, or four heads with two or three");
-  uint32_t t0, t1;
-  if constexpr (H == 2 && K == 2 && kFirst) {
-    asm(POT_PAIR(POT_HEAD_K2, POT_DOT0, 0, 1)
-        : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[h0 + 0]), [a1] "=&v"(a[h0 + 1]),
-          [c00] "=&v"(c[0][h0 + 0]), [c01] "=&v"(c[0][h0 + 1]), [c10] "=&v"(c[1][h0 + 0]),
-          [c11] "=&v"(c[1][h0 + 1])
-        : [sh] "v"(sh), [w] "v"(w), [m0] "v"(m[0]), [m1] "v"(m[1]), [q0] "s"(q[0]),
-          [q1] "s"(q[1]));
-  } else if constexpr (H == 2 && K == 2 && !kFirst) {
-    asm(POT_PAIR(POT_HEAD_K2, POT_DOTC, 0, 1)
-        : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[h0 + 0]), [a1] "+v"(a[h0 + 1]),
-          [c00] "+v"(c[0][h0 + 0]), [c01] "+v"(c[0][h0 + 1]), [c10] "+v"(c[1][h0 + 0]),
-          [c11] "+v"(c[1][h0 + 1])
-        : [sh] "v"(sh), [w] "v"(w), [m0] "v"(m[0]), [m1] "v"(m[1]), [q0] "s"(q[0]),
-          [q1] "s"(q[1]));
-  } else if constexpr (H == 2 && K == 3 && kFirst) {
-    asm(POT_PAIR(POT_HEAD_K3, POT_DOT0, 0, 1)
-        : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[h0 + 0]), [a1] "=&v"(a[h0 + 1]),
-          [c00] "=&v"(c[0][h0 + 0]), [c01] "=&v"(c[0][h0 + 1]), [c10] "=&v"(c[1][h0 + 0]),
-          [c11] "=&v"(c[1][h0 + 1]), [c20] "=&v"(c[2][h0 + 0]), [c21] "=&v"(c[2][h0 + 1])
-        : [sh] "v"(sh), [w] "v"(w), [m0] "v"(m[0]), [m1] "v"(m[1]), [m2] "v"(m[2]),
-          [q0] "s"(q[0]), [q1] "s"(q[1]));
-  } else if constexpr (H == 2 && K == 3 && !kFirst) {
-    asm(POT_PAIR(POT_HEAD_K3, POT_DOTC, 0, 1)
-        : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[h0 + 0]), [a1] "+v"(a[h0 + 1]),
-          [c00] "+v"(c[0][h0 + 0]), [c01] "+v"(c[0][h0 + 1]), [c10] "+v"(c[1][h0 + 0]),
-          [c11] "+v"(c[1][h0 + 1]), [c20] "+v"(c[2][h0 + 0]), [c21] "+v"(c[2][h0 + 1])
-        : [sh] "v"(sh), [w] "v"(w), [m0] "v"(m[0]), [m1] "v"(m[1]), [m2] "v"(m[2]),
-          [q0] "s"(q[0]), [q1] "s"(q[1]));
-  } else if constexpr (H == 2 && K == 4 && kFirst) {
-    asm(POT_PAIR(POT_HEAD_K4, POT_DOT0, 0, 1)
-        : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[h0 + 0]), [a1] "=&v"(a[h0 + 1]),
-          [c00] "=&v"(c[0][h0 + 0]), [c01] "=&v"(c[0][h0 + 1]), [c10] "=&v"(c[1][h0 + 0]),
-          [c11] "=&v"(c[1][h0 + 1]), [c20] "=&v"(c[2][h0 + 0]), [c21] "=&v"(c[2][h0 + 1]),
-          [c30] "=&v"(c[3][h0 + 0]), [c31] "=&v"(c[3][h0 + 1])
-        : [sh] "v"(sh), [w] "v"(w), [m0] "v"(m[0]), [m1] "v"(m[1]), [m2] "v"(m[2]),
-          [m3] "v"(m[3]), [q0] "s"(q[0]), [q1] "s"(q[1]));
-  } else if constexpr (H == 2 && K == 4 && !kFirst) {
-    asm(POT_PAIR(POT_HEAD_K4, POT_DOTC, 0, 1)
-        : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[h0 + 0]), [a1] "+v"(a[h0 + 1]),
-          [c00] "+v"(c[0][h0 + 0]), [c01] "+v"(c[0][h0 + 1]), [c10] "+v"(c[1][h0 + 0]),
-          [c11] "+v"(c[1][h0 + 1]), [c20] "+v"(c[2][h0 + 0]), [c21] "+v"(c[2][h0 + 1]),
-          [c30] "+v"(c[3][h0 + 0]), [c31] "+v"(c[3][h0 + 1])
-        : [sh] "v"(sh), [w] "v"(w), [m0] "v"(m[0]), [m1] "v"(m[1]), [m2] "v"(m[2]),
-          [m3] "v"(m[3]), [q0] "s"(q[0]), [q1] "s"(q[1]));
-  } else if constexpr (H == 4 && K == 2 && kFirst) {
-    asm(POT_PAIR(POT_HEAD_K2, POT_DOT0, 0, 1) POT_PAIR(POT_HEAD_K2, POT_DOT0, 2, 3)
-        : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[h0 + 0]), [a1] "=&v"(a[h0 + 1]),
-          [a2] "=&v"(a[h0 + 2]), [a3] "=&v"(a[h0 + 3]), [c00] "=&v"(c[0][h0 + 0]),
-          [c01] "=&v"(c[0][h0 + 1]), [c02] "=&v"(c[0][h0 + 2]), [c03] "=&v"(c[0][h0 + 3]),
-          [c10] "=&v"(c[1][h0 + 0]), [c11] "=&v"(c[1][h0 + 1]), [c12] "=&v"(c[1][h0 + 2]),
-          [c13] "=&v"(c[1][h0 + 3])
-        : [sh] "v"(sh), [w] "v"(w), [m0] "v"(m[0]), [m1] "v"(m[1]), [q0] "s"(q[0]),
-          [q1] "s"(q[1]), [q2] "s"(q[2]), [q3] "s"(q[3]));
-  } else if constexpr (H == 4 && K == 2 && !kFirst) {
-    asm(POT_PAIR(POT_HEAD_K2, POT_DOTC, 0, 1) POT_PAIR(POT_HEAD_K2, POT_DOTC, 2, 3)
-        : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[h0 + 0]), [a1] "+v"(a[h0 + 1]), [a2] "+v"(a[h0 + 2]),
-          [a3] "+v"(a[h0 + 3]), [c00] "+v"(c[0][h0 + 0]), [c01] "+v"(c[0][h0 + 1]),
-          [c02] "+v"(c[0][h0 + 2]), [c03] "+v"(c[0][h0 + 3]), [c10] "+v"(c[1][h0 + 0]),
-          [c11] "+v"(c[1][h0 + 1]), [c12] "+v"(c[1][h0 + 2]), [c13] "+v"(c[1][h0 + 3])
-        : [sh] "v"(sh), [w] "v"(w), [m0] "v"(m[0]), [m1] "v"(m[1]), [q0] "s"(q[0]),
-          [q1] "s"(q[1]), [q2] "s"(q[2]), [q3] "s"(q[3]));
-  } else if constexpr (H == 4 && K == 3 && kFirst) {
-    asm(POT_PAIR(POT_HEAD_K3, POT_DOT0, 0, 1) POT_PAIR(POT_HEAD_K3, POT_DOT0, 2, 3)
-        : "=&v"(t0), "=&v"(t1), [a0] "=&v"(a[h0 + 0]), [a1] "=&v"(a[h0 + 1]),
-          [a2] "=&v"(a[h0 + 2]), [a3] "=&v"(a[h0 + 3]), [c00] "=&v"(c[0][h0 + 0]),
-          [c01] "=&v"(c[0][h0 + 1]), [c02] "=&v"(c[0][h0 + 2]), [c03] "=&v"(c[0][h0 + 3]),
-          [c10] "=&v"(c[1][h0 + 0]), [c11] "=&v"(c[1][h0 + 1]), [c12] "=&v"(c[1][h0 + 2]),
-          [c13] "=&v"(c[1][h0 + 3]), [c20] "=&v"(c[2][h0 + 0]), [c21] "=&v"(c[2][h0 + 1]),
-          [c22] "=&v"(c[2][h0 + 2]), [c23] "=&v"(c[2][h0 + 3])
-        : [sh] "v"(sh), [w] "v"(w), [m0] "v"(m[0]), [m1] "v"(m[1]), [m2] "v"(m[2]),
-          [q0] "s"(q[0]), [q1] "s"(q[1]), [q2] "s"(q[2]), [q3] "s"(q[3]));
-  } else if constexpr (H == 4 && K == 3 && !kFirst) {
-    asm(POT_PAIR(POT_HEAD_K3, POT_DOTC, 0, 1) POT_PAIR(POT_HEAD_K3, POT_DOTC, 2, 3)
-        : "=&v"(t0), "=&v"(t1), [a0] "+v"(a[h0 + 0]), [a1] "+v"(a[h0 + 1]), [a2] "+v"(a[h0 + 2]),
-          [a3] "+v"(a[h0 + 3]), [c00] "+v"(c[0][h0 + 0]), [c01] "+v"(c[0][h0 + 1]),
-          [c02] "+v"(c[0][h0 + 2]), [c03] "+v"(c[0][h0 + 3]), [c10] "+v"(c[1][h0 + 0]),
-          [c11] "+v"(c[1][h0 + 1]), [c12] "+v"(c[1][h0 + 2]), [c13] "+v"(c[1][h0 + 3]),
-          [c20] "+v"(c[2][h0 + 0]), [c21] "+v"(c[2][h0 + 1]), [c22] "+v"(c[2][h0 + 2]),
-          [c23] "+v"(c[2][h0 + 3])
-        : [sh] "v"(sh), [w] "v"(w), [m0] "v"(m[0]), [m1] "v"(m[1]), [m2] "v"(m[2]),
-          [q0] "s"(q[0]), [q1] "s"(q[1]), [q2] "s"(q[2]), [q3] "s"(q[3]));
-  }
-}
-#undef POT_PAIR
-#undef POT_HEAD_K4
-#undef POT_HEAD_K3
-#undef POT_HEAD_K2
-#undef POT_DOTC
-#undef POT_DOT0
-#undef POT_SAC_2
-#undef POT_SAC_DC
-#undef POT_SAC_D0
-#undef POT_SAC_SH
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = kBlock / 64;  // waves per workgroup of the default variant
@@ -305,71 +86,6 @@ __device__ __forceinline__ uint32_t xad_u32(uint32_t a, uint32_t b, uint32_t c) 
   asm("v_xad_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
-// One 64-bit shift moves a pair of 32-bit words (v_lshrrev_b64 /
-// v_lshlrev_b64 issue at the rate of a 32-bit shift).
-__device__ __forceinline__ uint64_t pack64(uint32_t lo, uint32_t hi) {
-  return ((uint64_t)hi << 32) | lo;
-}
-template <int S>
-__device__ __forceinline__ uint64_t shr64(uint64_t v) {
-  uint64_t r;
-  asm("v_lshrrev_b64 %0, %1, %2" : "=v"(r) : "n"(S), "v"(v));
-  return r;
-}
-template <int S>
-__device__ __forceinline__ uint64_t shl64(uint64_t v) {
-  uint64_t r;
-  asm("v_lshlrev_b64 %0, %1, %2" : "=v"(r) : "n"(S), "v"(v));
-  return r;
-}
-
-// Shift amounts and weight fields of the four element pairs of two PoT code
-// words wa, wb (8 elements each; element m in nibble m = (sign << 3) | e).
-// am[.][n]: the exponents of elements n and n + 4 in bits 3:0 and 19:16,
-// where v_pk_ashrrev_i16 reads its per-half shift amounts (the bits above
-// them in each half may be set: 20 and up hold bits of the other word).
-// wf[.][n]: the weight field of elements n and n + 4, (sign, "not the zero
-// code") in bits 15:14 and 31:30, so that an arithmetic shift of each half
-// by 14 gives 1, -1, or 0 for the zero code (bits below 14 of each half are
-// left as they come). The two words share every shift; sel must hold
-// 0x88888888 (in a register, so that the select runs at the rate of a
-// VGPR-only op).
-struct CodePairFields {
-  uint32_t am[2][4], wf[2][4];
-};
-__device__ __forceinline__ CodePairFields code_pair_fields(uint32_t wa, uint32_t wb,
-                                                           uint32_t sel) {
-  CodePairFields f;
-  const uint32_t xa = wa & 0x77777777u, xb = wb & 0x77777777u;  // e per nibble
-  // e + 1 per nibble (no carry between nibbles): bit 3 is set exactly for
-  // the zero code, e = 7; moved to bit 2 by the pair's shift right by one
-  const uint64_t ys = shr64<1>(pack64(xa + 0x11111111u, xb + 0x11111111u));
-  // bit 3 of each nibble: the sign; bit 2: "not the zero code"
-  const uint32_t swa = (wa & sel) | (~(uint32_t)ys & ~sel);
-  const uint32_t swb = (wb & sel) | (~(uint32_t)(ys >> 32) & ~sel);
-  const uint64_t xx = pack64(xa, xb);
-  const uint64_t a1 = shr64<4>(xx), a2 = shr64<8>(xx), a3 = shr64<12>(xx);
-  f.am[0][0] = xa;
-  f.am[1][0] = xb;
-  f.am[0][1] = (uint32_t)a1;
-  f.am[1][1] = (uint32_t)(a1 >> 32);
-  f.am[0][2] = (uint32_t)a2;
-  f.am[1][2] = (uint32_t)(a2 >> 32);
-  f.am[0][3] = (uint32_t)a3;
-  f.am[1][3] = (uint32_t)(a3 >> 32);
-  const uint64_t ss = pack64(swa, swb);
-  const uint64_t s0 = shl64<12>(ss), s1 = shl64<8>(ss), s2 = shl64<4>(ss);
-  f.wf[0][0] = (uint32_t)s0;
-  f.wf[1][0] = (uint32_t)(s0 >> 32);
-  f.wf[0][1] = (uint32_t)s1;
-  f.wf[1][1] = (uint32_t)(s1 >> 32);
-  f.wf[0][2] = (uint32_t)s2;
-  f.wf[1][2] = (uint32_t)(s2 >> 32);
-  f.wf[0][3] = swa;
-  f.wf[1][3] = swb;
-  return f;
-}
-
 // max(a, b) for scores (never NaN) as v_max_f32 without operand canonicalisation
 __device__ __forceinline__ float max_f32(float a, float b) {
   return __builtin_amdgcn_fmed3f(a, b, __builtin_inff());
@@ -434,11 +150,11 @@ __device__ __forceinline__ BufRsrc tile_rsrc(const uint8_t* base, int t0, int li
 // ---- per-tile register payloads -----------------------------------------------
 template <int MODE, int K>
 struct KeyRegs;
+// shift-accumulate: half a key per lane and set (score_planes.hpp)
 template <int K>
 struct KeyRegs<kScorePot, K> {
-  uint4 c0, c1;
-  uint2 pl[K > 0 ? K : 1];
-  float s;
+  uint4 c[2];                       // 16 code bytes of set 0 and set 1
+  uint32_t pl[2][K > 0 ? K : 1];    // mantissa bits as loaded
 };
 template <int K>
 struct KeyRegs<kScoreDs4a, K> {
@@ -486,7 +202,85 @@ __device__ __forceinline__ void load_keys(const DecodeArgs& a, int64_t row, KeyR
   }
 }
 
-// PoT codes of keys t0 + lane (PoT and byte-decode engines): keys at or past
+__device__ __forceinline__ uint4 load_b128(BufRsrc rs, int off, int aux_nt) {
+  const u32x4v v = aux_nt ? __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kAuxNt)
+                          : __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// Codes of a 64-key tile for the plane scores (score_planes.hpp): in set s
+// lane l loads half l / 16 % 2 of key 32 (l / 32) + 8 (l % 16 / 4) + 4 s + l % 4.
+// The mantissa planes of the key's row are loaded as pairs of planes, the two
+// halves of each: the even block's lane takes planes 0 (0 and 1 at k = 4), the
+// odd block's the next ones, and plane_bits exchanges the halves; a last odd
+// plane is one dword. Keys at or past the range's end read zeros. The scales
+// are read up to the end of the last 8-key group (rows that exist; keys past
+// the range are masked when the tile is consumed).
+template <int K>
+__device__ __forceinline__ void load_keys_planes(const Streams& st, int t0, int lane,
+                                                 KeyRegs<kScorePot, K>& r) {
+  const int i = lane & 15, blk = lane >> 4, half = blk & 1;
+  const int key = 32 * (blk >> 1) + 8 * (i >> 2) + (i & 3);
+  const BufRsrc rc = tile_rsrc(st.codes, t0, st.t_end, kDim / 2);
+#pragma unroll
+  for (int s = 0; s < 2; ++s) r.c[s] = load_b128(rc, (key + 4 * s) * 32 + 16 * half, 1);
+  if constexpr (K > 0) {
+    const BufRsrc rp = tile_rsrc(st.planes, t0, st.t_end, 8 * K);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int row = (key + 4 * s) * 8 * K;
+      if constexpr (K == 4) {
+        const uint4 v = load_b128(rp, row + 16 * half, 1);
+        r.pl[s][0] = v.x;
+        r.pl[s][1] = v.y;
+        r.pl[s][2] = v.z;
+        r.pl[s][3] = v.w;
+      } else {
+        if constexpr (K >= 2) {
+          const u32x2v v = __builtin_amdgcn_raw_buffer_load_b64(rp, row + 8 * half, 0, kAuxNt);
+          r.pl[s][0] = v.x;
+          r.pl[s][1] = v.y;
+        }
+        if constexpr (K & 1)
+          r.pl[s][K - 1] =
+              __builtin_amdgcn_raw_buffer_load_b32(rp, row + 8 * (K - 1) + 4 * half, 0, kAuxNt);
+      }
+    }
+  }
+}
+
+// Scales of the 8 keys whose scores the lane gets (keys 32 part + 8 grp ..+7).
+__device__ __forceinline__ void load_scales_planes(const Streams& st, int t0, int lane,
+                                                   uint4 (&s)[2]) {
+  const BufRsrc rs = tile_rsrc(st.scales, t0, st.v_end, 4);
+  const int off = (32 * ((lane >> 3) & 1) + 8 * (lane >> 4)) * 4;
+  s[0] = load_b128(rs, off, 1);
+  s[1] = load_b128(rs, off + 16, 1);
+}
+
+// The lane's half of every mantissa plane of set s, from the pairs as loaded:
+// v_permlane16_swap exchanges the odd blocks of its first operand with the
+// even blocks of its second.
+template <int K>
+__device__ __forceinline__ void plane_bits(const KeyRegs<kScorePot, K>& r, int s, uint32_t* pl) {
+  if constexpr (K == 4) {
+    const auto a = __builtin_amdgcn_permlane16_swap(r.pl[s][0], r.pl[s][1], false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(r.pl[s][2], r.pl[s][3], false, false);
+    pl[0] = a[0];
+    pl[2] = a[1];
+    pl[1] = b[0];
+    pl[3] = b[1];
+  } else {
+    if constexpr (K >= 2) {
+      const auto a = __builtin_amdgcn_permlane16_swap(r.pl[s][0], r.pl[s][1], false, false);
+      pl[0] = a[0];
+      pl[1] = a[1];
+    }
+    if constexpr (K & 1) pl[K - 1] = r.pl[s][K - 1];
+  }
+}
+
+// PoT codes of keys t0 + lane (decoded-code engines): keys at or past
 // the range's end read zeros (they are masked when the tile is consumed).
 template <int MODE, int K>
 __device__ __forceinline__ void load_keys_buf(const Streams& st, int t0, int lane,
@@ -496,7 +290,7 @@ __device__ __forceinline__ void load_keys_buf(const Streams& st, int t0, int lan
   const u32x4v c1 = __builtin_amdgcn_raw_buffer_load_b128(rc, lane * 32 + 16, 0, kAuxNt);
   r.c0 = make_uint4(c0.x, c0.y, c0.z, c0.w);
   r.c1 = make_uint4(c1.x, c1.y, c1.z, c1.w);
-  if constexpr (MODE == kScorePot || MODE == kScoreDs4a) {
+  {
     if constexpr (K > 0) {
       const BufRsrc rp = tile_rsrc(st.planes, t0, st.t_end, 8 * K);
 #pragma unroll
@@ -516,14 +310,15 @@ __device__ __forceinline__ void load_keys_buf(const Streams& st, int t0, int lan
 // the range's last group read zeros (their weights are 0). With INT8 values
 // the lane also loads the exponents of the 8 keys t0 + 32*part + 8*grp ..+7
 // whose weights it forms in stage 2.
-template <bool V8>
+// Blocks kFirst .. kEnd - 1 of the two K-blocks; the exponents come with block 0.
+template <bool V8, int kFirst = 0, int kEnd = 2>
 __device__ __forceinline__ void load_values_buf(const Streams& st, int t0, int lane,
                                                 ValRegs<V8>& v) {
   constexpr int kGroupBytes = V8 ? 8 * kDim : 16 * kDim;  // one 8-token group
   const BufRsrc rv = tile_rsrc(st.values, t0, st.v_end, kGroupBytes / 8);
   const int voff = (lane >> 4) * kGroupBytes + (lane & 15) * (V8 ? 8 : 16);
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
+  for (int kb = kFirst; kb < kEnd; ++kb) {
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) {
       const int off = voff + kb * 4 * kGroupBytes + nb * 16 * (V8 ? 8 : 16);
@@ -536,7 +331,7 @@ __device__ __forceinline__ void load_values_buf(const Streams& st, int t0, int l
       }
     }
   }
-  if constexpr (V8) {
+  if constexpr (V8 && kFirst == 0) {
     const int part = (lane & 15) >> 3, grp = lane >> 4;
     const BufRsrc re = tile_rsrc(st.exps, t0, st.v_end, 1);
     const u32x2v g = __builtin_amdgcn_raw_buffer_load_b64(re, 32 * part + 8 * grp, 0, 0);
@@ -546,17 +341,20 @@ __device__ __forceinline__ void load_values_buf(const Streams& st, int t0, int l
 
 // fp16 B fragment of 8 INT8 values held as v^ + 128: bytes u become the fp16
 // numbers 1024 + u = 1152 + v^ (bit pattern 0x6400 | u, exact), two per
-// v_perm_b32; the 1152 offset is removed after accumulation with the weight
-// sums.
+// v_perm_b32, and a packed fp16 addition takes the 1152 off again (exact).
+// (Taking it off the fp32 sums instead costs 32 operations less per tile and
+// most of their precision: 1.9e-5 against 64 bits where this has 4e-7.)
 __device__ __forceinline__ half8 int8_value_fragment(uint2 w) {
   constexpr uint32_t kHi = 0x64646464u;
-  return __builtin_bit_cast(
+  half8 v = __builtin_bit_cast(
       half8, make_uint4(__builtin_amdgcn_perm(kHi, w.x, 0x04010400u),
                         __builtin_amdgcn_perm(kHi, w.x, 0x04030402u),
                         __builtin_amdgcn_perm(kHi, w.y, 0x04010400u),
                         __builtin_amdgcn_perm(kHi, w.y, 0x04030402u)));
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] -= (_Float16)1152.0f;
+  return v;
 }
-constexpr float kV8Offset = 1152.0f;
 
 // Zero the value fragments of tokens at or past t_end (tail tile only), so
 // that whatever the cache holds there cannot reach the sums (p is 0 there).
@@ -579,18 +377,37 @@ __device__ __forceinline__ void mask_values(int t0, int t_end, int lane, ValRegs
 }
 
 // ---- prepared query operands (workspace, one block per kv head) -------------
-// PoT-4 and PoT-Mk: [(c * 4 + n) * G + h] = q 2^7 of elements 8c + n and
+// PoT-Mk decoded to weights: [(c * 4 + n) * G + h] = q of elements 8c + n and
 // 8c + n + 4 as signed 16-bit halves;
-// PoT-Mk decoded to weights: the same words with q itself;
 // INT8: [i * G + h] four int8 per word;
 // byte decode: [(2c + o) * G + h] four int8 (elements 8c + o + 2t, t = 0..3);
 // fp16: [i * G + h] two fp16 per word. The G per-head score factors follow.
 template <int MODE, int G, int K>
 struct QLayout {
   static constexpr int kCols = G;                              // one operand column per head
-  static constexpr int kWords = (MODE == kScorePot || (MODE == kScoreDs4a && K > 0)) ? 32 * kCols
+  static constexpr int kWords = (MODE == kScoreDs4a && K > 0) ? 32 * kCols
                                 : (MODE == kScoreInt8 || MODE == kScoreDs4a) ? (kDim / 4) * G
                                                      : (kDim / 2) * G;
+};
+
+// ---- shared memory of the decode kernel -------------------------------------
+template <int NW>
+struct alignas(16) MergeSmem {
+  alignas(16) float wo[NW][16][kDim];  // per-wave P.V (rows: heads x {hi, lo})
+  float wp[NW][64];  // per-lane sums of the weights
+  int wm[NW][8];
+  int gm[NW];        // INT8 values: per-wave minimum exponent
+  int next;          // CU-wide variant: the next unclaimed tile of the range
+};
+template <bool PLANES, int NW>
+struct DecodeSmem : MergeSmem<NW> {
+  alignas(16) float x[NW][8][kXRow];  // transposed score tile per wave
+};
+template <int NW>
+struct DecodeSmem<true, NW> : MergeSmem<NW> {
+  alignas(16) _Float16 qh[8][kDim];  // q^ = 16 hi + lo per head, in operand order
+  alignas(16) _Float16 ql[8][kDim];
+  float qc[8];                       // score factor per head
 };
 
 // The new token of one (batch, kv head) sequence appended at row T - 1
@@ -632,14 +449,16 @@ __device__ __forceinline__ QueryIn<G, NW> load_queries(const DecodeArgs& a, int 
 }
 
 // Rotates (optionally) and quantises the G query vectors of one (batch, kv
-// head) and writes the operand words and per-head score factors that the
-// score loop reads through the scalar cache, into qb (this workgroup's own
-// slot of the workspace). Called by all NW waves of the workgroup; wave w
+// head) and writes the operands and per-head score factors: the shift-
+// accumulate path's into LDS, the other engines' into qb (this workgroup's own
+// slot of the workspace), which their score loops read through the scalar
+// cache. Called by all NW waves of the workgroup; wave w
 // handles heads w, w + NW, whose elements qin holds. taps: also write the q^
 // and Delta debug taps.
 template <int MODE, int G, int K, int NW>
 __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, int b,
-                                                int32_t* __restrict__ qb, bool taps,
+                                                int32_t* __restrict__ qb,
+                                                DecodeSmem<MODE == kScorePot, NW>& sm, bool taps,
                                                 const QueryIn<G, NW>& qin) {
   using QL = QLayout<MODE, G, K>;
   const int lane = lane_id(), wave = threadIdx.x >> 6;
@@ -660,17 +479,19 @@ __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, in
       if (a.hadamard) qv = (float)(wave_fwht64((double)qv) * 0.125);
       float step;
       const int qi = wave_quantize_int8(qv, &step);
-      if constexpr (MODE == kScorePot || (MODE == kScoreDs4a && K > 0)) {
+      if constexpr (MODE == kScorePot) {
+        store_query_element<K>(qi, lane, sm.qh[h], sm.ql[h]);
+        if (lane == 0)
+          sm.qc[h] = __fmul_rn(__fmul_rn(step, log2e_f32()),
+                               __builtin_amdgcn_ldexpf(1.0f, -(a.frac_bits + K + 3)));
+      } else if constexpr (MODE == kScoreDs4a && K > 0) {
         // word ((c * 4 + n) * G + h) holds, for elements 8c + n (low half)
-        // and 8c + n + 4 (high half), q 2^7 of head h: signed 16-bit
-        // operands in [-16256, 16256] with 7 clear low bits, so an
-        // arithmetic right shift by e <= 7 is exact. The decoded-weight
-        // path takes q itself (its weights carry the 2^(7 - e)).
-        constexpr int kMul = MODE == kScorePot ? 128 : 1;
+        // and 8c + n + 4 (high half), q of head h as signed 16-bit halves
+        // (the weights carry the 2^(7 - e))
         const uint32_t up = (uint32_t)__shfl_down(qi, 4, 64);
         if ((lane & 4) == 0)
           qb[((lane >> 3) * 4 + (lane & 3)) * G + h] =
-              (int32_t)(((uint32_t)(qi * kMul) & 0xFFFFu) | ((up * (uint32_t)kMul) << 16));
+              (int32_t)(((uint32_t)qi & 0xFFFFu) | (up << 16));
         if (lane == 0)
           cb[h] = __fmul_rn(__fmul_rn(step, log2e_f32()),
                             __builtin_amdgcn_ldexpf(1.0f, -(a.frac_bits + K + 3)));
@@ -699,31 +520,23 @@ __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, in
   }
 }
 
-// ---- shared memory of the decode kernel -------------------------------------
-template <int NW>
-struct alignas(16) DecodeSmem {
-  alignas(16) float x[NW][8][kXRow];  // transposed score tile per wave
-  float wo[NW][16][kDim];             // per-wave P.V (rows: heads x {hi, lo})
-  float wl[NW][16];
-  float wp[NW][64];  // INT8 values: per-lane sums of the unscaled weights
-  int wm[NW][8];
-  int gm[NW];        // INT8 values: per-wave minimum exponent
-  int next;          // CU-wide variant: the next unclaimed tile of the range
-};
-
 // VF: value format, 0 fp16 values, 1 INT8 values, 2 INT8 values with the
 // power-of-two weights of eq. logsm.
 // Resident waves per SIMD the register allocation must allow (1: no
-// constraint). The decoded-weight PoT-Mk path and the one- and two-plane
-// shift-accumulate paths would otherwise take a few registers more than four
-// waves leave (three per SIMD); held to four they keep every value in
-// registers, without spills (measured faster at every shape). The three-
-// and four-plane paths run at two or three waves, where a tighter budget
-// measured slower at B = 8.
+// constraint). The decoded-weight PoT-Mk path would otherwise take a few
+// registers more than four waves leave (three per SIMD); held to four it
+// keeps every value in registers, without spills (measured faster at every
+// shape).
 template <int MODE, int K>
-constexpr int kMinWaves = ((MODE == kScoreDs4a && K > 0) || (MODE == kScorePot && (K == 1 || K == 2)))
-                              ? 4
-                              : 1;
+constexpr int kMinWaves = MODE == kScoreDs4a && K > 0 ? 4 : 1;
+
+// CU-wide shift-accumulate kernels: value blocks (of two, 16 registers each)
+// loaded before the scores; the others are loaded after them, since held
+// meanwhile they would not fit the 128 (k = 3, 4: 168) registers of four
+// (three) waves per SIMD without spills. A wave has about 4 us per tile there
+// and can wait for a load; the four-wave kernels load all of them first.
+template <int K>
+constexpr int kEarlyValueBlocks = K == 0 || K == 3 ? 2 : K == 2 ? 0 : 1;
 
 // NW: waves per workgroup, kWaves or kPoolWaves<MODE, K, VF> (the CU-wide
 // variant, whose waves take their tiles from the counter sm.next).
@@ -737,7 +550,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   using QL = QLayout<MODE, G, K>;
   constexpr bool kPool = NW > kWaves;
   constexpr int kBlk = 64 * NW;
-  __shared__ DecodeSmem<NW> sm;
+  constexpr bool kPlanes = MODE == kScorePot;
+  __shared__ DecodeSmem<kPlanes, NW> sm;
   constexpr bool V8 = VF != 0;
   constexpr bool kPow2 = VF == 2;
   constexpr int kCols = QL::kCols;
@@ -776,22 +590,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     }
   }
   int gref = 0;
-  float lsum = 0.0f;  // INT8 values: this lane's sum of the unscaled weights
+  float lsum = 0.0f;  // this lane's sum of the weights
 
-  float4v acc[5];
+  float4v acc[4];
 #pragma unroll
-  for (int nb = 0; nb < 5; ++nb) acc[nb] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int nb = 0; nb < 4; ++nb) acc[nb] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
   int m_run = INT_MIN;
-  half8 ones;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) ones[i] = (_Float16)1.0f;
   // -1 kept opaque so that p - hi stays one fma_mix reading hi as fp16
   float neg_one = -1.0f;
   asm("" : "+v"(neg_one));
-  // the sign-bit select of the code fields, kept in a VGPR (a VALU op that
-  // reads an SGPR issues at the slower rate)
-  uint32_t sign_sel = 0x88888888u;
-  asm("" : "+v"(sign_sel));
+  // the working bit of the score planes, kept in a VGPR (a VALU op that reads
+  // an SGPR issues at the slower rate)
+  uint32_t m22 = 0x22222222u;
+  if constexpr (kPlanes) asm("" : "+v"(m22));
 
   KeyRegs<MODE, K> kr[2];
   const int g_last = (t_end - 1) & ~7;  // first token of the range's last 8-token group
@@ -813,7 +624,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   // or the range's last key (INT8, fp16)
   auto load_keys_tile = [&](int jt, KeyRegs<MODE, K>& kk) {
     const int t0 = t_begin + kWTile * jt;
-    if constexpr (MODE == kScorePot || MODE == kScoreDs4a)
+    if constexpr (kPlanes)
+      load_keys_planes<K>(st, t0, lane, kk);
+    else if constexpr (MODE == kScoreDs4a)
       load_keys_buf<MODE, K>(st, t0, lane, kk);
     else
       load_keys<MODE, K>(a, row0 + min(t0 + lane, t_end - 1), kk);
@@ -835,8 +648,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   // workgroup's keys (Sec. II-E eq. av): weights are formed as p 2^(g_ref -
   // g_j) <= p, so they stay in fp16 range for any g, and the sums are scaled
   // by 2^-g_ref at the end (fp32). One barrier then publishes both.
-  prepare_queries<MODE, G, K, NW>(a, kvh, b, a.qbuf + slot * a.qstride, DEBUG && split == 0,
-                                  qin);
+  prepare_queries<MODE, G, K, NW>(a, kvh, b, a.qbuf + slot * a.qstride, sm,
+                                  DEBUG && split == 0, qin);
   if constexpr (V8) {
     int gmin = INT_MAX;
     for (int t = t_begin + 8 * tid; t < t_end; t += 8 * kBlk) {
@@ -851,16 +664,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     for (int o = 32; o >= 1; o >>= 1) gmin = min(gmin, __shfl_xor(gmin, o, 64));
     if (lane == 0) sm.gm[wave] = gmin;
   }
-  wait_stores_in_l2();
+  if constexpr (!kPlanes) wait_stores_in_l2();
   __syncthreads();
   if constexpr (V8) {
     gref = sm.gm[0];
 #pragma unroll
     for (int w = 1; w < NW; ++w) gref = min(gref, sm.gm[w]);
   }
+  PlaneQuery pq{};
+  float c_lane = 0.0f;  // the score factor of this lane's head
+  if constexpr (kPlanes) {
+    pq = load_plane_query<G>(sm.qh, sm.ql, a.frac_bits);
+    c_lane = hvalid ? sm.qc[hrow] : 0.0f;
+  }
   // Fill the scalar cache with the slot's lines now, all at once (one load
   // per 64-byte line), instead of one miss per code word in the first tile.
-  {
+  if constexpr (!kPlanes) {
     uint32_t warm = 0;
 #pragma unroll
     for (int l = 0; l < (QL::kWords + G + 15) / 16; ++l) warm ^= (uint32_t)qb[16 * l];
@@ -872,6 +691,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   // prefetch the values of this wave's next tile as well.
   constexpr bool kPrefetchV = !(MODE == kScorePot || (MODE == kScoreDs4a && K > 0));
   ValRegs<V8> vr[kPrefetchV ? 2 : 1];
+  constexpr int kEarlyV = kPlanes && kPool ? kEarlyValueBlocks<K> : 2;
   if constexpr (kPrefetchV) {
     if (j < n_tiles) load_values_buf<V8>(st, t_begin + kWTile * j, lane, vr[0]);
   }
@@ -884,13 +704,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   auto stage1 = [&](const KeyRegs<MODE, K>& ks, KeyRegs<MODE, K>& knext, ValRegs<V8>& vs,
                     ValRegs<V8>& vnext, int jt) {
     const int t0 = t_begin + kWTile * jt;
+    uint4 ksc[2];  // shift-accumulate: this tile's scales
     // the next tile's keys (past the range: the last tile again, unused)
     const int jl = min(kPool ? jn : jt + NW, j_last);
     if constexpr (kPrefetchV) {
       load_keys_tile(jl, knext);
       load_values_buf<V8>(st, t_begin + kWTile * jl, lane, vnext);
     } else {
-      load_values_buf<V8>(st, t0, lane, vs);
+      if constexpr (kPlanes) load_scales_planes(st, t0, lane, ksc);
+      load_values_buf<V8, 0, kEarlyV>(st, t0, lane, vs);
       load_keys_tile(jl, knext);
     }
     if constexpr (kPool) {
@@ -904,173 +726,32 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     const bool kvalid = t < t_end;
     float xs[G];
     // ---- 1. scores (lane = key) ----
-    // Query operands of the shift paths (two element pairs of every head per
-    // chunk, 2 G words; 16 chunks per key): chunk c + 1 is requested
-    // once chunk c is in registers, so every scalar load has a chunk's work to
-    // land in (a wait on scalar loads covers all of them, as they may return
-    // in any order). A zero offset that depends on the tile keeps the
-    // compiler from hoisting the loads out of the loop, where 32 G words
-    // would not fit in scalar registers.
-    uint32_t qc[2][2 * kCols];
-    auto load_chunk = [&](int c) {
-      int toff = 0;
-      asm("" : "+s"(toff) : "s"(jt));
+    if constexpr (kPlanes) {
+      f32x4 d[2];
 #pragma unroll
-      for (int k = 0; k < 2 * kCols; ++k) qc[c & 1][k] = (uint32_t)qb[toff + 2 * kCols * c + k];
-    };
-    // wait for chunk c, then request chunk c + 1
-    auto next_chunk = [&](int c) {
-      asm volatile("" ::"s"(qc[c & 1][0]), "s"(qc[c & 1][2 * kCols - 1]));
-      __builtin_amdgcn_sched_barrier(0);
-      if (c + 1 < 16) load_chunk(c + 1);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    if constexpr (MODE == kScorePot) {
-      const uint32_t w[8] = {ks.c0.x, ks.c0.y, ks.c0.z, ks.c0.w,
-                             ks.c1.x, ks.c1.y, ks.c1.z, ks.c1.w};
-      int32_t accv[G];
-      // Two elements of one head per 16-bit-pair operand (element 8c + n in
-      // the low half, 8c + n + 4 in the high half). v_pk_ashrrev_i16 shifts
-      // each half by its element's exponent: q 2^7 >> e = q 2^(7 - e), exact.
-      // v_dot2_i32_i16 (the dot unit's multiply-add) with weights sigma =
-      // +-1 per half, and 0 for the zero code (e = 7, whose shifted operand
-      // is q), then applies the signs and adds both halves into the int32
-      // sum. PoT-Mk: the value is sigma (2^k + j)
-      // 2^-e, so the key's sum is 2^k times the leading sum plus 2^b times
-      // the sum over the elements whose mantissa j has bit b set, each over
-      // the same shifted operands with weights sigma or 0.
-      constexpr int KP = K > 0 ? K : 1;
-      int32_t accm[KP][G];
-      // With G > 1 the shifts and sums are assembly blocks per element pair
-      // (sac_heads, sac_heads_m1, sac_heads_mk) over operand chunks (above).
-      constexpr bool kRaw = G > 1;
-      if constexpr (kRaw) load_chunk(0);
-      // Shift amounts and weight fields: for PoT-4 and PoT-M1, two code words
-      // at a time with the pair's 64-bit shifts (code_pair_fields); with two
-      // or more mantissa planes, whose registers hold no second word's
-      // fields, one word at a time: x holds
-      // e per nibble, sw the sign in bit 3 and "not the zero code" in bit 2
-      // (bit 3 of e + 1 is set exactly for e = 7; no carry between
-      // nibbles), moved into place per element pair.
-      constexpr bool kPairFields = K <= 1;
-      CodePairFields pf;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        uint32_t x = 0, sw = 0;
-        if constexpr (kPairFields) {
-          if ((i & 1) == 0) pf = code_pair_fields(w[i], w[i + 1], sign_sel);
-        } else {
-          x = w[i] & 0x77777777u;
-          sw = (w[i] & 0x88888888u) | (~((x + 0x11111111u) >> 1) & 0x44444444u);
-        }
-        // the mantissa bits of this code word's 8 elements, one byte per
-        // plane, copied into both halves (bit n for element 8c + n in the
-        // low half, bit n + 4 in the high half)
-        uint32_t pb[KP];
-#pragma unroll
-        for (int bb = 0; bb < K; ++bb) {
-          const uint32_t pw = (i < 4) ? ks.pl[bb].x : ks.pl[bb].y;
-          pb[bb] = __builtin_amdgcn_perm(pw, pw, (uint32_t)(i & 3) * 0x00010001u | 0x0C000C00u);
-        }
-        // one head: this code word's four operand words, read as one scalar
-        // group per tile (the zero offset as for the chunks)
-        uint32_t qq[4 * kCols];
-        if constexpr (!kRaw) {
-          int toff = 0;
-          asm("" : "+s"(toff) : "s"(jt));
-#pragma unroll
-          for (int k = 0; k < 4 * kCols; ++k) qq[k] = (uint32_t)qb[toff + 4 * kCols * i + k];
-        }
-#pragma unroll
-        for (int n = 0; n < 4; ++n) {
-          const int c = 2 * i + (n >> 1);  // operand chunk (kRaw)
-          if constexpr (kRaw) {
-            if ((n & 1) == 0) next_chunk(c);
-          }
-          // exponents of elements 8c + n and 8c + n + 4, one per half (the
-          // shifts in sac_heads* read only the low four bits of each half, so
-          // the bits above them stay; the one-head C++ path masks them)
-          const uint32_t shr = kPairFields ? pf.am[i & 1][n] : x >> (4 * n);
-          // the weights of elements 8c + n and 8c + n + 4
-          const s16x2 sg =
-              __builtin_bit_cast(s16x2, kPairFields ? pf.wf[i & 1][n] : sw << (12 - 4 * n)) >>
-              (short)14;
-          s16x2 mw[KP];
-#pragma unroll
-          for (int bb = 0; bb < K; ++bb) {
-            // mantissa bit of each half moved to bit 15 and spread: the
-            // plane's weight is sigma where the bit is set, else 0
-            const u16x2 amt = {(unsigned short)(15 - n), (unsigned short)(11 - n)};
-            const s16x2 bit =
-                __builtin_bit_cast(s16x2, __builtin_bit_cast(u16x2, pb[bb]) << amt) >> (short)15;
-            mw[bb] = bit & sg;
-          }
-          const bool first = i == 0 && n == 0;  // the first pair starts every sum from 0
-          if constexpr (kRaw) {
-            const uint32_t wsg = __builtin_bit_cast(uint32_t, sg);
-            const uint32_t* qp = &qc[c & 1][kCols * (n & 1)];
-            if constexpr (K == 0) {
-              if (first)
-                sac_heads<G, true>(accv, qp, shr, wsg);
-              else
-                sac_heads<G, false>(accv, qp, shr, wsg);
-            } else if constexpr (K == 1) {
-              const uint32_t wm = __builtin_bit_cast(uint32_t, mw[0]);
-              if (first)
-                sac_heads_m1<G, true>(accv, accm[0], qp, shr, wsg, wm);
-              else
-                sac_heads_m1<G, false>(accv, accm[0], qp, shr, wsg, wm);
-            } else {
-              constexpr int H = (K == 4 || G == 2) ? 2 : 4;
-              uint32_t wm[K];
-#pragma unroll
-              for (int bb = 0; bb < K; ++bb) wm[bb] = __builtin_bit_cast(uint32_t, mw[bb]);
-#pragma unroll
-              for (int h0 = 0; h0 < G; h0 += H) {
-                if (first)
-                  sac_heads_mk<H, K, G, true>(accv, accm, h0, qp + h0, shr, wsg, wm);
-                else
-                  sac_heads_mk<H, K, G, false>(accv, accm, h0, qp + h0, shr, wsg, wm);
-              }
-            }
-          } else {
-            // one head: the same sums in C++ (with clamp set, |sum| <= 2 *
-            // 16256 is never reached, the compiler emits the three-operand
-            // form for the first pair instead of zeroing the sum first)
-            const s16x2 pv = __builtin_bit_cast(s16x2, qq[n]) >>
-                             __builtin_bit_cast(s16x2, shr & 0x000F000Fu);
-            accv[0] = first ? __builtin_amdgcn_sdot2(pv, sg, 0, true)
-                            : __builtin_amdgcn_sdot2(pv, sg, accv[0], false);
-#pragma unroll
-            for (int bb = 0; bb < K; ++bb)
-              accm[bb][0] = first ? __builtin_amdgcn_sdot2(pv, mw[bb], 0, true)
-                                  : __builtin_amdgcn_sdot2(pv, mw[bb], accm[bb][0], false);
-          }
-        }
+      for (int i = 0; i < 2; ++i) {
+        const uint32_t w[4] = {ks.c[i].x, ks.c[i].y, ks.c[i].z, ks.c[i].w};
+        uint32_t pl[K > 0 ? K : 1];
+        if constexpr (K > 0) plane_bits<K>(ks, i, pl);
+        d[i] = score_set<K>(w, pl, m22, pq);
       }
-      if constexpr (K > 0) {
+      // keeps the matrix instructions above here (and so their operands' live
+      // ranges short): the compiler would sink them to their first use
+      asm volatile("" : "+v"(d[0]), "+v"(d[1]));
+      if constexpr (kEarlyV < 2) load_values_buf<V8, kEarlyV, 2>(st, t0, lane, vs);
 #pragma unroll
-        for (int h = 0; h < G; ++h) {
-          uint32_t t = (uint32_t)accv[h] << K;
+      for (int i = 0; i < 2; ++i) {
+        const uint32_t sc[4] = {ksc[i].x, ksc[i].y, ksc[i].z, ksc[i].w};
 #pragma unroll
-          for (int bb = 0; bb < K; ++bb) t += (uint32_t)accm[bb][h] << bb;
-          accv[h] = (int32_t)t;
-        }
-      }
-      if (a.frac_bits != kFInt) {  // uniform: rescale to head-room F exactly
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-          accv[h] = a.frac_bits > kFInt
-                        ? (int32_t)((uint32_t)accv[h] << (a.frac_bits - kFInt))
-                        : (accv[h] >> (kFInt - a.frac_bits));
-      }
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const int32_t v = accv[h];
-        xs[h] = __fmul_rn(__fmul_rn((float)v, ks.s), cb[h]);
-        if constexpr (DEBUG) {
-          if (a.dbg_scores && kvalid)
-            a.dbg_scores[((int64_t)b * a.Hq + a.q_of_kv[kvh * G + h]) * a.T + t] = v;
+        for (int r = 0; r < 4; ++r) {
+          const float x = __fmul_rn(__fmul_rn(d[i][r], __uint_as_float(sc[r])), c_lane);
+          xv[4 * i + r] = hvalid ? x : -INFINITY;
+          if constexpr (DEBUG) {
+            const int key = t0 + 32 * part + 8 * grp + 4 * i + r;
+            if (a.dbg_scores && hvalid && key < t_end)
+              a.dbg_scores[((int64_t)b * a.Hq + a.q_of_kv[kvh * G + hrow]) * a.T + key] =
+                  (int32_t)d[i][r];
+          }
         }
       }
     } else if constexpr (MODE == kScoreDs4a && K > 0) {
@@ -1250,6 +931,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     // past the range carry the score of the range's last key (clamped
     // loads) or of zero codes (buffer reads past the range): they are masked
     // below in the tail tile.
+    if constexpr (!kPlanes) {
 #pragma unroll
     for (int h = 0; h < G; ++h) sm.x[wave][h][lane] = xs[h];
     wave_sync_lds();
@@ -1263,6 +945,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
       for (int i = 0; i < 8; ++i) xv[i] = hvalid ? r8[i] : -INFINITY;
     }
     wave_sync_lds();  // the tile buffer is rewritten by the next tile
+    }
     const bool tail = t0 + kWTile > t_end;  // wave-uniform
     if (tail) {
       const int k0 = t0 + 32 * part + 8 * grp;
@@ -1303,7 +986,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     const float f = (m_run == INT_MIN) ? 0.0f : __builtin_amdgcn_ldexpf(1.0f, m_run - m_new);
     const int arow = lane & 15, acol = lane >> 4;
 #pragma unroll
-    for (int nb = 0; nb < 5; ++nb) {
+    for (int nb = 0; nb < 4; ++nb) {
       float4v d = float4v{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj)
@@ -1311,7 +994,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
                                                  0, 0, 0);
       acc[nb] = d;
     }
-    if constexpr (V8) lsum *= f;
+    lsum *= f;
     m_run = m_new;
   };
 
@@ -1347,19 +1030,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
         p0 = __builtin_amdgcn_exp2f(xv[2 * i] + bias);
         p1 = __builtin_amdgcn_exp2f(xv[2 * i + 1] + bias);
       }
+      lsum += p0;
+      lsum += p1;
       if constexpr (V8) {
         // the softmax sum takes p; A.V takes p 2^(g_ref - g) (exact scaling)
-        lsum += p0;
-        lsum += p1;
         const uint32_t gw = (i < 2) ? vs.g.x : vs.g.y;
         p0 = __builtin_amdgcn_ldexpf(p0, gref - (int)(int8_t)(gw >> (16 * (i & 1))));
         p1 = __builtin_amdgcn_ldexpf(p1, gref - (int)(int8_t)(gw >> (16 * (i & 1) + 8)));
       }
       const half2v hi = __builtin_bit_cast(half2v, __builtin_amdgcn_cvt_pkrtz(p0, p1));
       hw[i] = __builtin_bit_cast(uint32_t, hi);
-      lw[i] = __builtin_bit_cast(
-          uint32_t, __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf(neg_one, (float)hi.x, p0),
-                                               __builtin_fmaf(neg_one, (float)hi.y, p1)));
+      const half2v lo = {(_Float16)__builtin_fmaf(neg_one, (float)hi.x, p0),
+                         (_Float16)__builtin_fmaf(neg_one, (float)hi.y, p1)};
+      lw[i] = __builtin_bit_cast(uint32_t, lo);
     }
     uint32_t a0w[4], a1w[4];
 #pragma unroll
@@ -1378,11 +1061,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb)
       acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af0, bfrag(0, nb), acc[nb], 0, 0, 0);
-    acc[4] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af0, ones, acc[4], 0, 0, 0);
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb)
       acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af1, bfrag(1, nb), acc[nb], 0, 0, 0);
-    acc[4] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af1, ones, acc[4], 0, 0, 0);
   };
 
   // The hot loop runs the tiles that do not raise any head's maximum; a tile
@@ -1420,10 +1101,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   for (int r = 0; r < 4; ++r) {
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) sm.wo[wave][4 * grp + r][16 * nb + row] = acc[nb][r];
-    if (row == 0) sm.wl[wave][4 * grp + r] = acc[4][r];
   }
   if (lane < 8) sm.wm[wave][lane] = m_run;
-  if constexpr (V8) sm.wp[wave][lane] = lsum;
+  sm.wp[wave][lane] = lsum;
   __syncthreads();
 
   const int Sn = a.n_splits;
@@ -1438,20 +1118,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     for (int w = 0; w < NW; ++w) {
       if (sm.wm[w][h] == INT_MIN) continue;
       const float f = __builtin_amdgcn_ldexpf(1.0f, sm.wm[w][h] - M);
-      if constexpr (V8) {
-        // numerator sum w (1152 + v^) minus 1152 sum w; denominator sum p over
-        // the 8 lanes that formed head h's weights
-        const float num = (sm.wo[w][h][d] + sm.wo[w][h + 8][d]) -
-                          kV8Offset * (sm.wl[w][h] + sm.wl[w][h + 8]);
-        float lw = 0.0f;
+      // the 8 lanes that formed head h's weights
+      float lw = 0.0f;
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq) lw += sm.wp[w][16 * gq + h] + sm.wp[w][16 * gq + h + 8];
-        o = fmaf(f, num, o);
-        l = fmaf(f, lw, l);
-      } else {
-        o = fmaf(f, sm.wo[w][h][d] + sm.wo[w][h + 8][d], o);
-        l = fmaf(f, sm.wl[w][h] + sm.wl[w][h + 8], l);
-      }
+      for (int gq = 0; gq < 4; ++gq) lw += sm.wp[w][16 * gq + h] + sm.wp[w][16 * gq + h + 8];
+      o = fmaf(f, sm.wo[w][h][d] + sm.wo[w][h + 8][d], o);
+      l = fmaf(f, lw, l);
     }
     if constexpr (V8) o = __builtin_amdgcn_ldexpf(o, -gref);
     if (Sn == 1) {
