@@ -201,8 +201,8 @@ pot_status pot_store_values_int8(const uint16_t* v_fp16, int64_t n_seq, int64_t 
                                  int8_t* v_exp, void* stream);
 
 /* Workspace bytes pot_decode_attention needs for this problem shape: the
- * prepared query operands of each (batch, kv head) and the key-split partials
- * (M_s, l_s, o_s) for the largest split count the planner can choose.
+ * key-split partials (M_s, l_s, o_s) for the largest split count the planner
+ * can choose, and room for query operands of each (batch, kv head, split).
  * Host-only. Returns 0 for invalid shapes. The same figure serves
  * pot_int8_decode_attention and pot_fp16_decode_attention. */
 size_t pot_decode_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv,
@@ -377,8 +377,8 @@ pot_status pot_int8_encode_keys(const uint16_t* k_fp16, int64_t n_rows,
                                 int64_t out_row_stride, int32_t hadamard,
                                 float* key_scale, int8_t* codes, void* stream);
 
-/* Decode attention with INT8 keys: scores by 4-way int8 dot products
- * (v_dot4), the same query quantiser, integer-M softmax and fp16 A.V. */
+/* Decode attention with INT8 keys: scores by int8 matrix instructions (exact
+ * int32), the same query quantiser, integer-M softmax and fp16 A.V. */
 pot_status pot_int8_decode_attention(
     const float* q, const int8_t* codes, const float* key_scale,
     const uint16_t* v_cache, int64_t t_cap, const int32_t* kv_head_of_q,
@@ -388,10 +388,10 @@ pot_status pot_int8_decode_attention(
 
 /* Decode attention over a PoT-4 cache (mant_bits = 0) with the score computed
  * by a software form of the packed shift-dot operation DS4A (Sec. III,
- * eq. ds4a): each code nibble is decoded by a byte table (v_perm_b32) to the
- * int8 value sigma 2^(6-e) (0 for the zero code, which must be stored with
- * neg = 0 as pot_encode_keys writes it), and v_dot4_i32_i8 accumulates
- * q^ * sigma 2^(6-e); one left shift by F - 6 gives exactly the int32 score
+ * eq. ds4a): each code nibble is decoded to an fp16 number sigma 2^(-8-e) (0
+ * for the zero code, which must be stored with neg = 0 as pot_encode_keys
+ * writes it), matrix instructions multiply it with q^ 2^8 and accumulate in
+ * fp32, exactly, and one power of two gives the int32 score
  * of pot_decode_attention. This is a multiply path, provided to measure what
  * a packed shift-dot would buy (eq. proj); pot_decode_attention is the
  * shift-accumulate path. Arguments, layout, workspace, taps and errors as
@@ -405,12 +405,10 @@ pot_status pot_ds4a_decode_attention(const pot_format* fmt, const float* q,
                                      pot_debug* dbg, void* stream);
 
 /* Decode attention over a PoT or PoT-Mk cache with the codes decoded to
- * integer weights and scored on the dot unit (a multiply path beside the
- * shift-accumulate one, Sec. III, eq. ds4a and eq. mant): PoT-4 as
- * pot_ds4a_decode_attention (bytes sigma 2^(6-e), v_dot4_i32_i8); PoT-Mk as
- * 16-bit weights sigma (2^k + j) 2^(7-e) (0 for the zero code), at most
- * 31 * 128, with v_dot2_i32_i16 over q^ for two elements per head, one dot
- * per head and element pair whatever k. The int32 scores, integer maxima and
+ * weights that are multiplied (a multiply path beside the
+ * shift-accumulate one, Sec. III, eq. ds4a and eq. mant): fp16 numbers
+ * sigma (1 + j / 2^k) 2^(-8-e) on the matrix cores, one product per element
+ * and head whatever k, exact in fp32. The int32 scores, integer maxima and
  * outputs equal pot_decode_attention's (same scores tap convention, 2^-(F+k)
  * for k > 0). Arguments, layout, workspace, taps and errors as
  * pot_decode_attention. */

@@ -158,15 +158,12 @@ constexpr int kPoolTilesPerWave = 2;
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct WsLayout {
-  size_t qbuf, part_m, part_l, part_o, total;
+  size_t part_m, part_l, part_o, total;
 };
 
-// Workspace: one slot of prepared query operands per decode workgroup
-// (B * Hkv * S slots; each workgroup writes its own and reads it back through
-// the scalar cache), then the split partials.
+// Workspace: query_words per decode workgroup (unused), then the split partials.
 WsLayout ws_layout(long B, long Hq, long Hkv, long S) {
   WsLayout w;
-  w.qbuf = 0;
   w.part_m = align_up((size_t)(B * Hkv * S) * query_words((int)(Hq / Hkv)) * 4, 256);
   w.part_l = w.part_m + align_up((size_t)(B * Hq * S) * 4, 256);
   w.part_o = w.part_l + align_up((size_t)(B * Hq * S) * 4, 256);
@@ -266,8 +263,6 @@ pot_status decode_common(int mode, int mant_bits, DecodeArgs& a, const int32_t* 
     return fail(POT_ERR_WORKSPACE, "workspace %zu bytes < %zu needed for %d splits", ws_bytes,
                 w.total, p.n_splits);
   uint8_t* ws = static_cast<uint8_t*>(workspace);
-  a.qbuf = reinterpret_cast<int32_t*>(ws + w.qbuf);
-  a.qstride = query_words(G);
   a.part_m = reinterpret_cast<int32_t*>(ws + w.part_m);
   a.part_l = reinterpret_cast<float*>(ws + w.part_l);
   a.part_o = reinterpret_cast<float*>(ws + w.part_o);

@@ -1,4 +1,4 @@
-// Decode kernels: codes decoded to integer weights on the dot unit (every value format).
+// Decode kernels: codes decoded to fp16 weights (every value format).
 #include "decode_kernel.hpp"
 
 namespace potattn {

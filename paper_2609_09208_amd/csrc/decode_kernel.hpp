@@ -6,7 +6,7 @@
 // kv head (GQA), so every code and value byte is read from HBM once and used
 // G times. Inside the workgroup each wave streams its own 64-key tiles
 // (tile j of the range goes to wave j % 4; in the CU-wide variant the waves
-// claim tiles from a counter in LDS) with the next tile's codes (and, for
+// claim tiles from a counter in LDS) with the next tile's keys (and, for
 // the short score cores, value fragments) prefetched into registers while
 // the current one is processed; waves only meet at the end to merge their
 // partial sums.
@@ -20,12 +20,10 @@
 //     VALU lane-operations per key at k = 0 / 1 / 4 and were bound by their
 //     issue: B = 64, T = 32768, PoT-4 222 us per call, now 202; B = 8, T =
 //     32768, PoT-M4 80 us, now 41; B = 16, T = 16384, PoT-4 with INT8 values
-//     39 us, now 28.) The decoded-code engines (a multiply path) decode each
-//     code once per key into dot-unit weights shared by all G heads, one key
-//     per lane: PoT-4 into int8 bytes sigma 2^(6 - e) for v_dot4_i32_i8,
-//     PoT-Mk into 16-bit sigma (2^k + j) 2^(7 - e) for v_dot2_i32_i16; the
-//     int32 sums equal the shift-accumulate ones, and are staged transposed in
-//     wave-private LDS.
+//     39 us, now 28.) The decoded-code engines (a multiply path) and the
+//     comparators take the same operand layout with fp16 or INT8 matrix
+//     instructions (score_decoded.hpp); the decoded codes' int32 sums equal
+//     the shift-accumulate ones.
 //  2. x = fl32(fl32(float(acc) * s) * c), c = fl32(fl32(Delta * log2 e) *
 //     2^-(F+k+3)) in this order.
 //  3. Integer running maximum M = max(M, ceil(max x)) per head (eq. logsm);
@@ -53,15 +51,12 @@
 
 #include "pot_device.hpp"
 #include "pot_launch.hpp"
+#include "score_decoded.hpp"
 #include "score_planes.hpp"
 
 namespace potattn {
 
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = kBlock / 64;  // waves per workgroup of the default variant
@@ -76,39 +71,23 @@ constexpr int kWaves = kBlock / 64;  // waves per workgroup of the default varia
 template <int MODE, int K, int VF>
 constexpr int kPoolWaves = pool_waves(MODE, K, VF);
 constexpr int kWTile = 64;    // keys per wave tile
-constexpr int kXRow = 68;     // floats per head row of the transposed score tile
 constexpr float kPScale = 12.0f;  // p is formed as 2^(x - M + 12) (fp16-normal range)
 constexpr int kDppRowRor8 = 0x128;  // DPP row_ror:8: lane l reads lane l ^ 8 within its row of 16
 
-// ---- VALU forms the compiler does not pick by itself ------------------------
-__device__ __forceinline__ uint32_t xad_u32(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t r;
-  asm("v_xad_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
 // max(a, b) for scores (never NaN) as v_max_f32 without operand canonicalisation
 __device__ __forceinline__ float max_f32(float a, float b) {
   return __builtin_amdgcn_fmed3f(a, b, __builtin_inff());
 }
 
-
-// Waits until this wave's vector stores are acknowledged by the L2. A
-// workgroup barrier alone does not: it orders the wave's accesses for the
-// other waves' vector loads, but the scalar cache, which reads the prepared
-// query operands, fills from the L2.
+// Waits until this wave's vector stores are acknowledged by the L2, where
+// every later load of the workgroup finds them.
 __device__ __forceinline__ void wait_stores_in_l2() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-__device__ __forceinline__ void wave_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // ---- streaming loads -----------------------------------------------------------
 // The cache is read once per call, so its loads carry the non-temporal hint.
 // It pays for the value fragments of every engine and for the 32-byte PoT
-// code rows; the fp16 comparator's 128-byte key rows are read by eight
-// 16-byte loads per lane that revisit the same lines, and stay plain there.
+// code rows; the comparators' 64- and 128-byte key rows are read by several
+// 16-byte loads per lane that revisit the same lines, and stay plain.
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
 
@@ -148,28 +127,19 @@ __device__ __forceinline__ BufRsrc tile_rsrc(const uint8_t* base, int t0, int li
 }
 
 // ---- per-tile register payloads -----------------------------------------------
+// One half of one key per lane and set (score_planes.hpp).
 template <int MODE, int K>
-struct KeyRegs;
-// shift-accumulate: half a key per lane and set (score_planes.hpp)
-template <int K>
-struct KeyRegs<kScorePot, K> {
-  uint4 c[2];                       // 16 code bytes of set 0 and set 1
-  uint32_t pl[2][K > 0 ? K : 1];    // mantissa bits as loaded
-};
-template <int K>
-struct KeyRegs<kScoreDs4a, K> {
-  uint4 c0, c1;
-  uint2 pl[K > 0 ? K : 1];
-  float s;
+struct KeyRegs {                   // PoT codes
+  uint4 c[2];                      // 16 code bytes of set 0 and set 1
+  uint32_t pl[2][K > 0 ? K : 1];   // mantissa bits as loaded
 };
 template <int K>
 struct KeyRegs<kScoreInt8, K> {
-  int4 k[4];
-  float s;
+  uint4 k[2][2];
 };
 template <int K>
 struct KeyRegs<kScoreFp16, K> {
-  uint4 k[8];
+  uint4 k[2][4];
 };
 
 template <bool V8>
@@ -182,55 +152,47 @@ struct ValRegs<true> {
   uint2 g;        // exponents g of the 8 keys whose weights this lane forms
 };
 
-// Loads are unconditional (addresses clamped into the valid range, or reads
-// past a buffer resource's end, which return zeros) so that the compiler can
-// count outstanding loads statically and keep the prefetch of the next tile in
-// flight while the current one is processed; keys past the range are masked
-// when the tile is consumed.
-// Key rows of the comparators (INT8 codes, fp16 keys).
-template <int MODE, int K>
-__device__ __forceinline__ void load_keys(const DecodeArgs& a, int64_t row, KeyRegs<MODE, K>& r) {
-  if constexpr (MODE == kScoreInt8) {
-    const int4* kp = reinterpret_cast<const int4*>(a.codes_i8 + row * kDim);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r.k[i] = kp[i];
-    r.s = a.key_scale[row];
-  } else {
-    const uint4* kp = reinterpret_cast<const uint4*>(a.k_f16 + row * kDim);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) r.k[i] = kp[i];
-  }
-}
-
-__device__ __forceinline__ uint4 load_b128(BufRsrc rs, int off, int aux_nt) {
+// Loads are unconditional (reads past a buffer resource's end return zeros) so
+// that the compiler can count outstanding loads statically and keep the
+// prefetch of the next tile in flight while the current one is processed; keys
+// past the range are masked when the tile is consumed.
+__device__ __forceinline__ uint4 load_b128(BufRsrc rs, int off, bool aux_nt) {
   const u32x4v v = aux_nt ? __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kAuxNt)
                           : __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// Codes of a 64-key tile for the plane scores (score_planes.hpp): in set s
-// lane l loads half l / 16 % 2 of key 32 (l / 32) + 8 (l % 16 / 4) + 4 s + l % 4.
-// The mantissa planes of the key's row are loaded as pairs of planes, the two
+// Keys of a 64-key tile (score_planes.hpp): in set s lane l loads half
+// l / 16 % 2 of key 32 (l / 32) + 8 (l % 16 / 4) + 4 s + l % 4. The mantissa
+// planes of the key's row are loaded as pairs of planes, the two
 // halves of each: the even block's lane takes planes 0 (0 and 1 at k = 4), the
 // odd block's the next ones, and plane_bits exchanges the halves; a last odd
-// plane is one dword. Keys at or past the range's end read zeros. The scales
-// are read up to the end of the last 8-key group (rows that exist; keys past
-// the range are masked when the tile is consumed).
-template <int K>
-__device__ __forceinline__ void load_keys_planes(const Streams& st, int t0, int lane,
-                                                 KeyRegs<kScorePot, K>& r) {
+// plane is one dword. Keys at or past the range's end read zeros.
+template <int MODE, int K>
+__device__ __forceinline__ void load_keys(const Streams& st, int t0, int lane,
+                                          KeyRegs<MODE, K>& r) {
   const int i = lane & 15, blk = lane >> 4, half = blk & 1;
   const int key = 32 * (blk >> 1) + 8 * (i >> 2) + (i & 3);
+  if constexpr (MODE == kScoreInt8 || MODE == kScoreFp16) {
+    constexpr int kRow = MODE == kScoreInt8 ? kDim : 2 * kDim, kLoads = kRow / 32;
+    const BufRsrc rk = tile_rsrc(st.codes, t0, st.t_end, kRow);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int c = 0; c < kLoads; ++c)
+        r.k[s][c] = load_b128(rk, (key + 4 * s) * kRow + 16 * (kLoads * half + c), false);
+    return;
+  } else {
   const BufRsrc rc = tile_rsrc(st.codes, t0, st.t_end, kDim / 2);
 #pragma unroll
-  for (int s = 0; s < 2; ++s) r.c[s] = load_b128(rc, (key + 4 * s) * 32 + 16 * half, 1);
+  for (int s = 0; s < 2; ++s) r.c[s] = load_b128(rc, (key + 4 * s) * 32 + 16 * half, true);
   if constexpr (K > 0) {
     const BufRsrc rp = tile_rsrc(st.planes, t0, st.t_end, 8 * K);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const int row = (key + 4 * s) * 8 * K;
       if constexpr (K == 4) {
-        const uint4 v = load_b128(rp, row + 16 * half, 1);
+        const uint4 v = load_b128(rp, row + 16 * half, true);
         r.pl[s][0] = v.x;
         r.pl[s][1] = v.y;
         r.pl[s][2] = v.z;
@@ -247,22 +209,24 @@ __device__ __forceinline__ void load_keys_planes(const Streams& st, int t0, int 
       }
     }
   }
+  }
 }
 
-// Scales of the 8 keys whose scores the lane gets (keys 32 part + 8 grp ..+7).
-__device__ __forceinline__ void load_scales_planes(const Streams& st, int t0, int lane,
-                                                   uint4 (&s)[2]) {
+// Scales of the 8 keys whose scores the lane gets (keys 32 part + 8 grp ..+7),
+// up to the end of the last 8-key group (rows that exist).
+__device__ __forceinline__ void load_scales(const Streams& st, int t0, int lane,
+                                            uint4 (&s)[2]) {
   const BufRsrc rs = tile_rsrc(st.scales, t0, st.v_end, 4);
   const int off = (32 * ((lane >> 3) & 1) + 8 * (lane >> 4)) * 4;
-  s[0] = load_b128(rs, off, 1);
-  s[1] = load_b128(rs, off + 16, 1);
+  s[0] = load_b128(rs, off, true);
+  s[1] = load_b128(rs, off + 16, true);
 }
 
 // The lane's half of every mantissa plane of set s, from the pairs as loaded:
 // v_permlane16_swap exchanges the odd blocks of its first operand with the
 // even blocks of its second.
-template <int K>
-__device__ __forceinline__ void plane_bits(const KeyRegs<kScorePot, K>& r, int s, uint32_t* pl) {
+template <int MODE, int K>
+__device__ __forceinline__ void plane_bits(const KeyRegs<MODE, K>& r, int s, uint32_t* pl) {
   if constexpr (K == 4) {
     const auto a = __builtin_amdgcn_permlane16_swap(r.pl[s][0], r.pl[s][1], false, false);
     const auto b = __builtin_amdgcn_permlane16_swap(r.pl[s][2], r.pl[s][3], false, false);
@@ -278,30 +242,6 @@ __device__ __forceinline__ void plane_bits(const KeyRegs<kScorePot, K>& r, int s
     }
     if constexpr (K & 1) pl[K - 1] = r.pl[s][K - 1];
   }
-}
-
-// PoT codes of keys t0 + lane (decoded-code engines): keys at or past
-// the range's end read zeros (they are masked when the tile is consumed).
-template <int MODE, int K>
-__device__ __forceinline__ void load_keys_buf(const Streams& st, int t0, int lane,
-                                              KeyRegs<MODE, K>& r) {
-  const BufRsrc rc = tile_rsrc(st.codes, t0, st.t_end, kDim / 2);
-  const u32x4v c0 = __builtin_amdgcn_raw_buffer_load_b128(rc, lane * 32, 0, kAuxNt);
-  const u32x4v c1 = __builtin_amdgcn_raw_buffer_load_b128(rc, lane * 32 + 16, 0, kAuxNt);
-  r.c0 = make_uint4(c0.x, c0.y, c0.z, c0.w);
-  r.c1 = make_uint4(c1.x, c1.y, c1.z, c1.w);
-  {
-    if constexpr (K > 0) {
-      const BufRsrc rp = tile_rsrc(st.planes, t0, st.t_end, 8 * K);
-#pragma unroll
-      for (int bb = 0; bb < K; ++bb) {
-        const u32x2v p = __builtin_amdgcn_raw_buffer_load_b64(rp, lane * 8 * K + 8 * bb, 0, kAuxNt);
-        r.pl[bb] = make_uint2(p.x, p.y);
-      }
-    }
-  }
-  const BufRsrc rs = tile_rsrc(st.scales, t0, st.t_end, 4);
-  r.s = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, kAuxNt));
 }
 
 // B fragments of one 64-key tile: lane l takes keys t0 + 32*kb + 8*(l/16) ..+7
@@ -376,20 +316,6 @@ __device__ __forceinline__ void mask_values(int t0, int t_end, int lane, ValRegs
   }
 }
 
-// ---- prepared query operands (workspace, one block per kv head) -------------
-// PoT-Mk decoded to weights: [(c * 4 + n) * G + h] = q of elements 8c + n and
-// 8c + n + 4 as signed 16-bit halves;
-// INT8: [i * G + h] four int8 per word;
-// byte decode: [(2c + o) * G + h] four int8 (elements 8c + o + 2t, t = 0..3);
-// fp16: [i * G + h] two fp16 per word. The G per-head score factors follow.
-template <int MODE, int G, int K>
-struct QLayout {
-  static constexpr int kCols = G;                              // one operand column per head
-  static constexpr int kWords = (MODE == kScoreDs4a && K > 0) ? 32 * kCols
-                                : (MODE == kScoreInt8 || MODE == kScoreDs4a) ? (kDim / 4) * G
-                                                     : (kDim / 2) * G;
-};
-
 // ---- shared memory of the decode kernel -------------------------------------
 template <int NW>
 struct alignas(16) MergeSmem {
@@ -399,15 +325,21 @@ struct alignas(16) MergeSmem {
   int gm[NW];        // INT8 values: per-wave minimum exponent
   int next;          // CU-wide variant: the next unclaimed tile of the range
 };
-template <bool PLANES, int NW>
+template <int MODE, int NW>
 struct DecodeSmem : MergeSmem<NW> {
-  alignas(16) float x[NW][8][kXRow];  // transposed score tile per wave
+  alignas(16) _Float16 qh[8][kDim];  // decoded weights: q^ 2^8; fp16 keys: q
+  float qc[8];                       // score factor per head
 };
 template <int NW>
-struct DecodeSmem<true, NW> : MergeSmem<NW> {
+struct DecodeSmem<kScorePot, NW> : MergeSmem<NW> {
   alignas(16) _Float16 qh[8][kDim];  // q^ = 16 hi + lo per head, in operand order
   alignas(16) _Float16 ql[8][kDim];
-  float qc[8];                       // score factor per head
+  float qc[8];
+};
+template <int NW>
+struct DecodeSmem<kScoreInt8, NW> : MergeSmem<NW> {
+  alignas(16) int8_t qb[8][kDim];  // q^
+  float qc[8];
 };
 
 // The new token of one (batch, kv head) sequence appended at row T - 1
@@ -449,20 +381,14 @@ __device__ __forceinline__ QueryIn<G, NW> load_queries(const DecodeArgs& a, int 
 }
 
 // Rotates (optionally) and quantises the G query vectors of one (batch, kv
-// head) and writes the operands and per-head score factors: the shift-
-// accumulate path's into LDS, the other engines' into qb (this workgroup's own
-// slot of the workspace), which their score loops read through the scalar
-// cache. Called by all NW waves of the workgroup; wave w
-// handles heads w, w + NW, whose elements qin holds. taps: also write the q^
-// and Delta debug taps.
+// head) and writes the operands and per-head score factors into LDS. Called by
+// all NW waves of the workgroup; wave w handles heads w, w + NW, whose
+// elements qin holds. taps: also write the q^ and Delta debug taps.
 template <int MODE, int G, int K, int NW>
 __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, int b,
-                                                int32_t* __restrict__ qb,
-                                                DecodeSmem<MODE == kScorePot, NW>& sm, bool taps,
+                                                DecodeSmem<MODE, NW>& sm, bool taps,
                                                 const QueryIn<G, NW>& qin) {
-  using QL = QLayout<MODE, G, K>;
   const int lane = lane_id(), wave = threadIdx.x >> 6;
-  float* cb = reinterpret_cast<float*>(qb + QL::kWords);
   constexpr int kHeadsPerWave = QueryIn<G, NW>::kHeadsPerWave;
 #pragma unroll
   for (int i = 0; i < kHeadsPerWave; ++i) {
@@ -471,46 +397,22 @@ __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, in
     const int64_t bq = (int64_t)b * a.Hq + a.q_of_kv[kvh * G + h];
     float qv = qin.v[i];
     if constexpr (MODE == kScoreFp16) {
-      const uint32_t bits = __half_as_ushort(__float2half_rn(qv));
-      const uint32_t other = __shfl_xor(bits, 1, 64);
-      if ((lane & 1) == 0) qb[(lane >> 1) * G + h] = (int32_t)(bits | (other << 16));
-      if (lane == 0) cb[h] = __fmul_rn(log2e_f32(), 0.125f);
+      sm.qh[h][lane] = (_Float16)qv;
+      if (lane == 0) sm.qc[h] = __fmul_rn(log2e_f32(), 0.125f);
     } else {
       if (a.hadamard) qv = (float)(wave_fwht64((double)qv) * 0.125);
       float step;
       const int qi = wave_quantize_int8(qv, &step);
-      if constexpr (MODE == kScorePot) {
+      if constexpr (MODE == kScorePot)
         store_query_element<K>(qi, lane, sm.qh[h], sm.ql[h]);
-        if (lane == 0)
-          sm.qc[h] = __fmul_rn(__fmul_rn(step, log2e_f32()),
-                               __builtin_amdgcn_ldexpf(1.0f, -(a.frac_bits + K + 3)));
-      } else if constexpr (MODE == kScoreDs4a && K > 0) {
-        // word ((c * 4 + n) * G + h) holds, for elements 8c + n (low half)
-        // and 8c + n + 4 (high half), q of head h as signed 16-bit halves
-        // (the weights carry the 2^(7 - e))
-        const uint32_t up = (uint32_t)__shfl_down(qi, 4, 64);
-        if ((lane & 4) == 0)
-          qb[((lane >> 3) * 4 + (lane & 3)) * G + h] =
-              (int32_t)(((uint32_t)qi & 0xFFFFu) | (up << 16));
-        if (lane == 0)
-          cb[h] = __fmul_rn(__fmul_rn(step, log2e_f32()),
-                            __builtin_amdgcn_ldexpf(1.0f, -(a.frac_bits + K + 3)));
-      } else if constexpr (MODE == kScoreDs4a) {
-        // the word of code word c and parity o holds elements 8c + o + 2t in
-        // byte t: lanes differing in bits 1 and 2 fill one word
-        uint32_t word = (uint32_t)(qi & 0xFF) << (8 * ((lane >> 1) & 3));
-        word |= __shfl_xor(word, 2, 64);
-        word |= __shfl_xor(word, 4, 64);
-        if ((lane & 6) == 0) qb[(2 * (lane >> 3) + (lane & 1)) * G + h] = (int32_t)word;
-        if (lane == 0)
-          cb[h] = __fmul_rn(__fmul_rn(step, log2e_f32()),
-                            __builtin_amdgcn_ldexpf(1.0f, -(a.frac_bits + 3)));
-      } else {
-        uint32_t word = (uint32_t)(qi & 0xFF) << (8 * (lane & 3));
-        word |= __shfl_xor(word, 1, 64);
-        word |= __shfl_xor(word, 2, 64);
-        if ((lane & 3) == 0) qb[(lane >> 2) * G + h] = (int32_t)word;
-        if (lane == 0) cb[h] = __fmul_rn(__fmul_rn(step, log2e_f32()), 0.125f);
+      else if constexpr (MODE == kScoreDs4a)
+        sm.qh[h][(lane & 32) + pair_order<K>(lane & 31)] = (_Float16)(qi * 256);
+      else
+        sm.qb[h][lane] = (int8_t)qi;
+      if (lane == 0) {
+        const int bits = MODE == kScoreInt8 ? 3 : a.frac_bits + K + 3;
+        sm.qc[h] =
+            __fmul_rn(__fmul_rn(step, log2e_f32()), __builtin_amdgcn_ldexpf(1.0f, -bits));
       }
       if (taps) {
         if (a.dbg_qhat) a.dbg_qhat[bq * kDim + lane] = (int8_t)qi;
@@ -522,39 +424,26 @@ __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, in
 
 // VF: value format, 0 fp16 values, 1 INT8 values, 2 INT8 values with the
 // power-of-two weights of eq. logsm.
-// Resident waves per SIMD the register allocation must allow (1: no
-// constraint). The decoded-weight PoT-Mk path would otherwise take a few
-// registers more than four waves leave (three per SIMD); held to four it
-// keeps every value in registers, without spills (measured faster at every
-// shape).
+// CU-wide kernels: value blocks (of two, 16 registers each) loaded before the
+// scores; the others are loaded after them, since held meanwhile they would
+// not fit the 128 registers of four waves per SIMD (shift-accumulate at k = 3,
+// 4: 168 of three) without spills. A wave has about 4 us per tile there and
+// can wait for a load; the four-wave kernels load all of them first.
 template <int MODE, int K>
-constexpr int kMinWaves = MODE == kScoreDs4a && K > 0 ? 4 : 1;
-
-// CU-wide shift-accumulate kernels: value blocks (of two, 16 registers each)
-// loaded before the scores; the others are loaded after them, since held
-// meanwhile they would not fit the 128 (k = 3, 4: 168) registers of four
-// (three) waves per SIMD without spills. A wave has about 4 us per tile there
-// and can wait for a load; the four-wave kernels load all of them first.
-template <int K>
-constexpr int kEarlyValueBlocks = K == 0 || K == 3 ? 2 : K == 2 ? 0 : 1;
+constexpr int kEarlyValueBlocks = MODE == kScorePot    ? (K == 0 || K == 3 ? 2 : K == 2 ? 0 : 1)
+                                  : MODE == kScoreDs4a ? (K >= 2 ? 1 : 2)
+                                                       : 2;
 
 // NW: waves per workgroup, kWaves or kPoolWaves<MODE, K, VF> (the CU-wide
 // variant, whose waves take their tiles from the counter sm.next).
 template <int MODE, int G, int K, bool DEBUG, int VF, int NW>
-// qbuf is passed on its own as a restrict parameter: the prepared query
-// operands are never written here, which lets the compiler read them through
-// the scalar cache even in the debug variants that store score taps.
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
-    NW > kWaves ? NW / 4 : kMinWaves<MODE, K>))) void decode_kernel(const DecodeArgs a,
-                                                               const int32_t* __restrict__ qbuf) {
-  using QL = QLayout<MODE, G, K>;
+    NW > kWaves ? NW / 4 : 1))) void decode_kernel(const DecodeArgs a) {
   constexpr bool kPool = NW > kWaves;
   constexpr int kBlk = 64 * NW;
-  constexpr bool kPlanes = MODE == kScorePot;
-  __shared__ DecodeSmem<kPlanes, NW> sm;
+  __shared__ DecodeSmem<MODE, NW> sm;
   constexpr bool V8 = VF != 0;
   constexpr bool kPow2 = VF == 2;
-  constexpr int kCols = QL::kCols;
 
   const int tid = threadIdx.x, lane = tid & 63;
   // the wave index is uniform in a wave; saying so keeps the tile loop's
@@ -564,13 +453,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   const int64_t seq = (int64_t)b * a.Hkv + kvh;
   const int64_t row0 = seq * a.t_cap;
   const int8_t* eseq = V8 ? a.v_exp + row0 : nullptr;
-  // This workgroup's own slot of query operands and score factors: written
-  // by the prologue below, then only read, through the scalar cache (which
-  // starts each dispatch empty; no other workgroup touches the slot).
-  const int64_t slot = seq * a.n_splits + split;
-  const int32_t* __restrict__ qb = qbuf + slot * a.qstride;
-  const float* __restrict__ cb = reinterpret_cast<const float*>(qb + QL::kWords);
-
   // ---- per-wave streaming over 64-key tiles ------------------------------------
   const int t_begin = split * a.split_len;
   const int t_end = min(a.T, t_begin + a.split_len);
@@ -602,7 +484,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   // the working bit of the score planes, kept in a VGPR (a VALU op that reads
   // an SGPR issues at the slower rate)
   uint32_t m22 = 0x22222222u;
-  if constexpr (kPlanes) asm("" : "+v"(m22));
+  if constexpr (MODE == kScorePot) asm("" : "+v"(m22));
 
   KeyRegs<MODE, K> kr[2];
   const int g_last = (t_end - 1) & ~7;  // first token of the range's last 8-token group
@@ -613,6 +495,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     st.codes = a.codes_se + row0 * (kDim / 2);
     st.scales = reinterpret_cast<const uint8_t*>(a.key_scale + row0);
     if constexpr (K > 0) st.planes = a.codes_m + row0 * 8 * K;
+  } else if constexpr (MODE == kScoreInt8) {
+    st.codes = reinterpret_cast<const uint8_t*>(a.codes_i8 + row0 * kDim);
+    st.scales = reinterpret_cast<const uint8_t*>(a.key_scale + row0);
+  } else {
+    st.codes = reinterpret_cast<const uint8_t*>(a.k_f16 + row0 * kDim);
   }
   if constexpr (V8) {
     st.values = a.v8 + row0 * kDim;
@@ -620,16 +507,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   } else {
     st.values = reinterpret_cast<const uint8_t*>(a.v + row0 * kDim);
   }
-  // key codes of tile jt; keys past the range read zeros (PoT, byte decode)
-  // or the range's last key (INT8, fp16)
   auto load_keys_tile = [&](int jt, KeyRegs<MODE, K>& kk) {
-    const int t0 = t_begin + kWTile * jt;
-    if constexpr (kPlanes)
-      load_keys_planes<K>(st, t0, lane, kk);
-    else if constexpr (MODE == kScoreDs4a)
-      load_keys_buf<MODE, K>(st, t0, lane, kk);
-    else
-      load_keys<MODE, K>(a, row0 + min(t0 + lane, t_end - 1), kk);
+    load_keys<MODE, K>(st, t_begin + kWTile * jt, lane, kk);
   };
   // Tiles: wave w starts with tiles w and w + NW; after that the default
   // variant takes every NW-th tile and the CU-wide one claims the next
@@ -643,13 +522,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     if (tid == 0) sm.next = 2 * NW;
   }
 
-  // Query preparation into this workgroup's slot while the first codes load;
+  // Query preparation into LDS while the first codes load;
   // with INT8 values also the reference exponent g_ref = min g over this
   // workgroup's keys (Sec. II-E eq. av): weights are formed as p 2^(g_ref -
   // g_j) <= p, so they stay in fp16 range for any g, and the sums are scaled
   // by 2^-g_ref at the end (fp32). One barrier then publishes both.
-  prepare_queries<MODE, G, K, NW>(a, kvh, b, a.qbuf + slot * a.qstride, sm,
-                                  DEBUG && split == 0, qin);
+  prepare_queries<MODE, G, K, NW>(a, kvh, b, sm, DEBUG && split == 0, qin);
   if constexpr (V8) {
     int gmin = INT_MAX;
     for (int t = t_begin + 8 * tid; t < t_end; t += 8 * kBlk) {
@@ -664,54 +542,48 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     for (int o = 32; o >= 1; o >>= 1) gmin = min(gmin, __shfl_xor(gmin, o, 64));
     if (lane == 0) sm.gm[wave] = gmin;
   }
-  if constexpr (!kPlanes) wait_stores_in_l2();
   __syncthreads();
   if constexpr (V8) {
     gref = sm.gm[0];
 #pragma unroll
     for (int w = 1; w < NW; ++w) gref = min(gref, sm.gm[w]);
   }
-  PlaneQuery pq{};
-  float c_lane = 0.0f;  // the score factor of this lane's head
-  if constexpr (kPlanes) {
-    pq = load_plane_query<G>(sm.qh, sm.ql, a.frac_bits);
-    c_lane = hvalid ? sm.qc[hrow] : 0.0f;
-  }
-  // Fill the scalar cache with the slot's lines now, all at once (one load
-  // per 64-byte line), instead of one miss per code word in the first tile.
-  if constexpr (!kPlanes) {
-    uint32_t warm = 0;
-#pragma unroll
-    for (int l = 0; l < (QL::kWords + G + 15) / 16; ++l) warm ^= (uint32_t)qb[16 * l];
-    asm volatile("" ::"s"(warm));
-  }
+  const float c_lane = hvalid ? sm.qc[hrow] : 0.0f;  // the score factor of this lane's head
+  std::conditional_t<MODE == kScorePot, PlaneQuery,
+                     std::conditional_t<MODE == kScoreInt8, ByteQuery, HalfQuery>>
+      qop;
+  if constexpr (MODE == kScorePot) qop = load_plane_query<G>(sm.qh, sm.ql, a.frac_bits);
+  else if constexpr (MODE == kScoreInt8) qop = load_byte_query<G>(sm.qb);
+  else qop = load_half_query<G>(sm.qh);
+  // decoded weights: their sums to the int32 score at head-room F
+  const float to_int = MODE == kScoreDs4a ? __builtin_amdgcn_ldexpf(1.0f, a.frac_bits + K) : 1.0f;
 
-  // PoT scoring is long enough to cover the latency of value loads issued at
-  // the start of the tile; the short INT8 / fp16 scoring is not, so those
+  // The plane sums are long enough to cover the latency of value loads issued
+  // at the start of the tile; the other scores are not, so those engines
   // prefetch the values of this wave's next tile as well.
   constexpr bool kPrefetchV = !(MODE == kScorePot || (MODE == kScoreDs4a && K > 0));
   ValRegs<V8> vr[kPrefetchV ? 2 : 1];
-  constexpr int kEarlyV = kPlanes && kPool ? kEarlyValueBlocks<K> : 2;
+  constexpr int kEarlyV = kPool ? kEarlyValueBlocks<MODE, K> : 2;
   if constexpr (kPrefetchV) {
     if (j < n_tiles) load_values_buf<V8>(st, t_begin + kWTile * j, lane, vr[0]);
   }
 
   // Stage 1 of a tile: issue the loads it still needs and those of this
-  // wave's next tile, score (the loads land meanwhile), transpose and find
-  // the tile's integer maximum per head (returned in m_new).
+  // wave's next tile, score (the loads land meanwhile) and find the tile's
+  // integer maximum per head (returned in m_new).
   float xv[8];
   int m_new = m_run;
   auto stage1 = [&](const KeyRegs<MODE, K>& ks, KeyRegs<MODE, K>& knext, ValRegs<V8>& vs,
                     ValRegs<V8>& vnext, int jt) {
     const int t0 = t_begin + kWTile * jt;
-    uint4 ksc[2];  // shift-accumulate: this tile's scales
+    uint4 ksc[2];  // this tile's scales
+    if constexpr (MODE != kScoreFp16) load_scales(st, t0, lane, ksc);
     // the next tile's keys (past the range: the last tile again, unused)
     const int jl = min(kPool ? jn : jt + NW, j_last);
     if constexpr (kPrefetchV) {
       load_keys_tile(jl, knext);
       load_values_buf<V8>(st, t_begin + kWTile * jl, lane, vnext);
     } else {
-      if constexpr (kPlanes) load_scales_planes(st, t0, lane, ksc);
       load_values_buf<V8, 0, kEarlyV>(st, t0, lane, vs);
       load_keys_tile(jl, knext);
     }
@@ -722,29 +594,36 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
       jc = __builtin_amdgcn_readfirstlane(c);
     }
-    const int t = t0 + lane;
-    const bool kvalid = t < t_end;
-    float xs[G];
-    // ---- 1. scores (lane = key) ----
-    if constexpr (kPlanes) {
+    // ---- 1. scores: keys t0 + 32 part + 8 grp ..+7 of head hrow ----
+    {
       f32x4 d[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const uint32_t w[4] = {ks.c[i].x, ks.c[i].y, ks.c[i].z, ks.c[i].w};
-        uint32_t pl[K > 0 ? K : 1];
-        if constexpr (K > 0) plane_bits<K>(ks, i, pl);
-        d[i] = score_set<K>(w, pl, m22, pq);
+        if constexpr (MODE == kScorePot || MODE == kScoreDs4a) {
+          const uint32_t w[4] = {ks.c[i].x, ks.c[i].y, ks.c[i].z, ks.c[i].w};
+          uint32_t pl[K > 0 ? K : 1];
+          if constexpr (K > 0) plane_bits<MODE, K>(ks, i, pl);
+          if constexpr (MODE == kScorePot) d[i] = score_set<K>(w, pl, m22, qop);
+          else d[i] = score_set_decoded<K>(w, pl, qop, to_int);
+        } else if constexpr (MODE == kScoreInt8) {
+          d[i] = score_set_int8(ks.k[i], qop);
+        } else {
+          d[i] = score_set_fp16(ks.k[i], qop);
+        }
       }
       // keeps the matrix instructions above here (and so their operands' live
       // ranges short): the compiler would sink them to their first use
       asm volatile("" : "+v"(d[0]), "+v"(d[1]));
       if constexpr (kEarlyV < 2) load_values_buf<V8, kEarlyV, 2>(st, t0, lane, vs);
+      // ---- 2. scores to the log2 domain ----
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const uint32_t sc[4] = {ksc[i].x, ksc[i].y, ksc[i].z, ksc[i].w};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float x = __fmul_rn(__fmul_rn(d[i][r], __uint_as_float(sc[r])), c_lane);
+          float x = d[i][r];
+          if constexpr (MODE != kScoreFp16) x = __fmul_rn(x, __uint_as_float(sc[r]));
+          x = __fmul_rn(x, c_lane);
           xv[4 * i + r] = hvalid ? x : -INFINITY;
           if constexpr (DEBUG) {
             const int key = t0 + 32 * part + 8 * grp + 4 * i + r;
@@ -754,197 +633,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
           }
         }
       }
-    } else if constexpr (MODE == kScoreDs4a && K > 0) {
-      // PoT-Mk codes decoded to 16-bit integer weights (a multiply path):
-      // element m's weight is sigma (2^k + j) 2^(7 - e), 0 for the zero code,
-      // at most 31 * 128 in magnitude; v_dot2_i32_i16 accumulates q^ times
-      // the weights of two elements per head. The sum is exactly 2^k times
-      // the key's sum of eq. sac at head-room 7 (eq. mant), the integer the
-      // shift-accumulate path forms from its planes, with one dot per head
-      // and element pair for any k.
-      const uint32_t w[8] = {ks.c0.x, ks.c0.y, ks.c0.z, ks.c0.w,
-                             ks.c1.x, ks.c1.y, ks.c1.z, ks.c1.w};
-      int32_t accv[G];
-      // the mantissas regrouped per element pair n: byte i of jw[n][hw]
-      // holds j of element 8(4 hw + i) + n in bits 0..3 and of element
-      // 8(4 hw + i) + n + 4 in bits 4..7 (bit m of plane byte i is bit b of
-      // the mantissa of element 8i + m)
-      uint32_t jw[4][2];
-#pragma unroll
-      for (int n = 0; n < 4; ++n)
-#pragma unroll
-        for (int hw = 0; hw < 2; ++hw) {
-          uint32_t jacc = 0;
-#pragma unroll
-          for (int bb = 0; bb < K; ++bb) {
-            const uint32_t pw = hw ? ks.pl[bb].y : ks.pl[bb].x;
-            const uint32_t t = (bb <= n) ? (pw >> (n - bb)) : (pw << (bb - n));
-            jacc |= t & (0x11111111u << bb);
-          }
-          jw[n][hw] = jacc;
-        }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const uint32_t wi = w[i];
-        const uint32_t x = wi & 0x77777777u;
-        const uint32_t y = x + 0x11111111u;
-        // per nibble, bit 3: the sign; bit 2: "not the zero code" (as in
-        // the shift-accumulate path); ~wi holds 7 - e in each nibble's low
-        // three bits
-        const uint32_t sw = (wi & 0x88888888u) | (~(y >> 1) & 0x44444444u);
-        const uint32_t nx = ~wi;
-        // this code word's operands as one scalar group (one wait per code
-        // word: the chunked loads of the shift paths measured slower here)
-        int toff = 0;
-        asm("" : "+s"(toff) : "s"(jt));
-        uint32_t qq[4 * kCols];
-#pragma unroll
-        for (int k = 0; k < 4 * kCols; ++k) qq[k] = (uint32_t)qb[toff + 4 * kCols * i + k];
-#pragma unroll
-        for (int n = 0; n < 4; ++n) {
-          // weights sigma 2^(7 - e) (0 for the zero code) of elements 8i + n
-          // and 8i + n + 4, then times 2^k + j
-          const s16x2 sg = __builtin_bit_cast(s16x2, sw << (12 - 4 * n)) >> (short)14;
-          const s16x2 sh7 = __builtin_bit_cast(s16x2, (nx >> (4 * n)) & 0x00070007u);
-          const u16x2 sgs = __builtin_bit_cast(u16x2, (s16x2)(sg << sh7));
-          const uint32_t jb = __builtin_amdgcn_perm(jw[n][i >> 2], jw[n][i >> 2],
-                                                    (uint32_t)(i & 3) * 0x00010001u | 0x0C000C00u);
-          const u16x2 j4 = __builtin_bit_cast(u16x2, jb) >> u16x2{0, 4};
-          const u16x2 jn = (j4 & u16x2{15, 15}) | u16x2{1 << K, 1 << K};
-          const s16x2 wt = __builtin_bit_cast(s16x2, (u16x2)(jn * sgs));
-#pragma unroll
-          for (int h = 0; h < G; ++h) {
-            const s16x2 qv = __builtin_bit_cast(s16x2, qq[kCols * n + h]);
-            accv[h] = (i == 0 && n == 0) ? __builtin_amdgcn_sdot2(qv, wt, 0, true)
-                                         : __builtin_amdgcn_sdot2(qv, wt, accv[h], false);
-          }
-        }
-      }
-      if (a.frac_bits != kFInt) {  // uniform: rescale to head-room F exactly
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-          accv[h] = a.frac_bits > kFInt
-                        ? (int32_t)((uint32_t)accv[h] << (a.frac_bits - kFInt))
-                        : (accv[h] >> (kFInt - a.frac_bits));
-      }
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const int32_t v = accv[h];
-        xs[h] = __fmul_rn(__fmul_rn((float)v, ks.s), cb[h]);
-        if constexpr (DEBUG) {
-          if (a.dbg_scores && kvalid)
-            a.dbg_scores[((int64_t)b * a.Hq + a.q_of_kv[kvh * G + h]) * a.T + t] = v;
-        }
-      }
-    } else if constexpr (MODE == kScoreDs4a) {
-      // Byte decode of the PoT-4 codes (the DS4A operation, eq. ds4a, in
-      // software): a v_perm_b32 table maps each exponent field to 2^(6 - e)
-      // (0 for the zero code), the sign is applied per byte as (m ^ N) + n
-      // with N = 0xff and n = 1 in the bytes of negative elements (no carry
-      // between bytes: m <= 64, and the zero code is never negative), and
-      // v_dot4_i32_i8 accumulates q * sigma 2^(6 - e): the exact score at
-      // head-room 6, which one left shift brings to F. A multiply path.
-      const uint32_t w[8] = {ks.c0.x, ks.c0.y, ks.c0.z, ks.c0.w,
-                             ks.c1.x, ks.c1.y, ks.c1.z, ks.c1.w};
-      int32_t accd[G];
-#pragma unroll
-      for (int h = 0; h < G; ++h) accd[h] = 0;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const uint32_t wc = w[c];
-        const uint32_t e0 = wc & 0x07070707u, e1 = (wc >> 4) & 0x07070707u;
-        const uint32_t m0 = __builtin_amdgcn_perm(0x00010204u, 0x08102040u, e0);
-        const uint32_t m1 = __builtin_amdgcn_perm(0x00010204u, 0x08102040u, e1);
-        const uint32_t n0 = (wc >> 3) & 0x01010101u, n1 = (wc >> 7) & 0x01010101u;
-        // 0xff in the bytes of negative elements as (n << 8) - n: the shift is
-        // kept opaque, or the compiler forms n * 255 with the quarter-rate
-        // v_mul_lo_u32
-        uint32_t n0s = n0 << 8, n1s = n1 << 8;
-        asm("" : "+v"(n0s), "+v"(n1s));
-        const uint32_t k0 = xad_u32(m0, n0s - n0, n0);
-        const uint32_t k1 = xad_u32(m1, n1s - n1, n1);
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-          accd[h] = __builtin_amdgcn_sdot4(qb[(2 * c) * G + h], (int32_t)k0, accd[h], false);
-          accd[h] = __builtin_amdgcn_sdot4(qb[(2 * c + 1) * G + h], (int32_t)k1, accd[h], false);
-        }
-      }
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const int32_t v = (int32_t)((uint32_t)accd[h] << (a.frac_bits - 6));
-        xs[h] = __fmul_rn(__fmul_rn((float)v, ks.s), cb[h]);
-        if constexpr (DEBUG) {
-          if (a.dbg_scores && kvalid)
-            a.dbg_scores[((int64_t)b * a.Hq + a.q_of_kv[kvh * G + h]) * a.T + t] = v;
-        }
-      }
-    } else if constexpr (MODE == kScoreInt8) {
-      int32_t kw[16];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        kw[4 * i] = ks.k[i].x;
-        kw[4 * i + 1] = ks.k[i].y;
-        kw[4 * i + 2] = ks.k[i].z;
-        kw[4 * i + 3] = ks.k[i].w;
-      }
-      int32_t accd[G];
-#pragma unroll
-      for (int h = 0; h < G; ++h) accd[h] = 0;
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-          accd[h] = __builtin_amdgcn_sdot4(qb[i * G + h], kw[i], accd[h], false);
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        xs[h] = __fmul_rn(__fmul_rn((float)accd[h], ks.s), cb[h]);
-        if constexpr (DEBUG) {
-          if (a.dbg_scores && kvalid)
-            a.dbg_scores[((int64_t)b * a.Hq + a.q_of_kv[kvh * G + h]) * a.T + t] = accd[h];
-        }
-      }
-    } else {
-      uint32_t kw[32];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        kw[4 * i] = ks.k[i].x;
-        kw[4 * i + 1] = ks.k[i].y;
-        kw[4 * i + 2] = ks.k[i].z;
-        kw[4 * i + 3] = ks.k[i].w;
-      }
-      float dot[G];
-#pragma unroll
-      for (int h = 0; h < G; ++h) dot[h] = 0.0f;
-#pragma unroll
-      for (int i = 0; i < 32; ++i)
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-          dot[h] = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, qb[i * G + h]),
-                                          __builtin_bit_cast(half2v, kw[i]), dot[h], false);
-#pragma unroll
-      for (int h = 0; h < G; ++h) xs[h] = __fmul_rn(dot[h], cb[h]);
-    }
-
-    // ---- 2. transpose through wave-private LDS ----
-    // Lane (row, grp) takes head row & 7 and keys 32 * part + 8 * grp .. + 7
-    // of the tile (part = row >> 3), so every weight is computed once. Keys
-    // past the range carry the score of the range's last key (clamped
-    // loads) or of zero codes (buffer reads past the range): they are masked
-    // below in the tail tile.
-    if constexpr (!kPlanes) {
-#pragma unroll
-    for (int h = 0; h < G; ++h) sm.x[wave][h][lane] = xs[h];
-    wave_sync_lds();
-    {
-      // rows of heads >= G are never written: read row 0 and discard
-      const float4* src =
-          reinterpret_cast<const float4*>(&sm.x[wave][hvalid ? hrow : 0][32 * part + 8 * grp]);
-      const float4 u0 = src[0], u1 = src[1];
-      const float r8[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-#pragma unroll
-      for (int i = 0; i < 8; ++i) xv[i] = hvalid ? r8[i] : -INFINITY;
-    }
-    wave_sync_lds();  // the tile buffer is rewritten by the next tile
     }
     const bool tail = t0 + kWTile > t_end;  // wave-uniform
     if (tail) {
@@ -1244,13 +932,13 @@ static hipError_t launch_t(const DecodeArgs& a, hipStream_t stream, hipEvent_t e
   if constexpr (PW > 0) {
     if (a.wg_waves == PW)
       hipLaunchKernelGGL((decode_kernel<MODE, G, K, DEBUG, VF, PW>), grid, dim3(64 * PW), 0,
-                         stream, a, static_cast<const int32_t*>(a.qbuf));
+                         stream, a);
     else
       hipLaunchKernelGGL((decode_kernel<MODE, G, K, DEBUG, VF, kWaves>), grid, dim3(kBlock), 0,
-                         stream, a, static_cast<const int32_t*>(a.qbuf));
+                         stream, a);
   } else {
     hipLaunchKernelGGL((decode_kernel<MODE, G, K, DEBUG, VF, kWaves>), grid, dim3(kBlock), 0,
-                       stream, a, static_cast<const int32_t*>(a.qbuf));
+                       stream, a);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev_end != nullptr && (e = hipEventRecord(ev_end, stream)) != hipSuccess) return e;

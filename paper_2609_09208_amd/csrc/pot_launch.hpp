@@ -49,7 +49,7 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t stream);
 // returns st (api.cpp).
 pot_status report_error(pot_status st, const char* fmt, ...);
 
-// kScoreDs4a: PoT-4 codes decoded to int8 bytes and scored by v_dot4 (a
+// kScoreDs4a: PoT codes decoded to fp16 weights that are multiplied (a
 // multiply path, kept beside the shift path for measurement)
 enum ScoreMode : int { kScorePot = 0, kScoreInt8 = 1, kScoreFp16 = 2, kScoreDs4a = 3 };
 
@@ -66,9 +66,6 @@ struct DecodeArgs {
   const int8_t* v_exp;       // one exponent g per row: value v^ 2^-g
   float* out;
   // workspace
-  int32_t* qbuf;             // [B*Hkv*n_splits][qstride]: prepared query operands, one
-                             // slot per decode workgroup (written and read by it)
-  int32_t qstride;           // 32-bit words per slot in qbuf
   int32_t* part_m;           // [B*Hq*S]
   float* part_l;             // [B*Hq*S]
   float* part_o;             // [B*Hq*S*64]
@@ -119,10 +116,9 @@ constexpr int pool_waves(int mode, int mant_bits, int vf) {
 // (fp16 values: 128 bytes per key, rounded up to whole 8-key groups).
 constexpr int kMaxKeys = (1 << 24) - 8;
 
-// 32-bit words of prepared query operands per kv head for group size G:
-// room for the largest layout (32 words per head: 16-bit operand pairs for
-// the PoT codes, fp16 pairs for the fp16 comparator) plus the G per-head
-// score factors.
+// 32-bit words per decode workgroup at the head of the workspace. The kernels
+// keep the prepared queries in LDS; the workspace sizes that callers compute
+// and allocate by are part of the interface, so this part of them stays.
 constexpr int query_words(int G) { return (33 * G + 63) / 64 * 64; }
 
 // Resident workgroups per CU of the (non-debug) decode kernel for this
