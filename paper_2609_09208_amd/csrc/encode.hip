@@ -13,9 +13,9 @@
 // the ratio's bits with integer operations (an add that carries into the
 // exponent exactly above the cut point, a shift and a clamp) and its sign
 // bits from the inputs' sign bits eight at a time by byte permutes; PoT-Mk
-// (K > 0) compares the mantissa against the fp32 cut points. (The fused per-
-// token append in the decode kernel and the INT8 comparator encode one row
-// per wavefront, one element per lane.)
+// (K > 0) compares the mantissa against the fp32 cut points. (The INT8
+// comparator's encoder takes the same shape; the fused per-token append in the
+// decode kernel encodes one row per wavefront, one element per lane.)
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
@@ -59,8 +59,16 @@ EncodeTables make_encode_tables(int mant_bits) {
 // launch has at most kMaxGrid workgroups, since a dispatch is limited to
 // 2^32 work-items per dimension (2^26 rows of one wave each).
 constexpr int64_t kMaxGrid = 1 << 20;
-// bulk PoT encoder: 256 CUs x 8 workgroups of 4 waves
-constexpr int64_t kEncodeGrid = 256 * 8;
+// Workgroups of the bulk encoders: eight per CU, each wave looping over row
+// groups, and up to 32 per CU while every wave still has eight groups (2 M rows:
+// k = 0 66 -> 64 us, k = 4 118 -> 108; 131072 rows, one group per wave instead
+// of two: 7.0 -> 7.4).
+constexpr int64_t kEncodeGrid = 256 * 8, kEncodeGridMax = 256 * 32;
+inline uint32_t encode_grid(int64_t n_rows) {
+  const int64_t groups = (n_rows + 7) / 8, wg = kBlock / 64;
+  const int64_t cap = std::max(kEncodeGrid, std::min(kEncodeGridMax, groups / (8 * wg)));
+  return (uint32_t)std::min((groups + wg - 1) / wg, cap);
+}
 
 // Maximum over the 8 lanes of an aligned group (lane & ~7) of non-negative,
 // non-NaN floats, compared as their bit patterns: swap neighbours, swap
@@ -181,6 +189,57 @@ __device__ __forceinline__ uint32_t potmk_word(const float (&v)[8], uint32_t sgn
   return (w ^ 0x77777777u) | (sgn & (w + 0x77777777u) & 0x88888888u);
 }
 
+// 8 elements 8g .. 8g + 7 (g = lane % 8) of a row from their fp16 words, with
+// the optional rotation over the row's 8 lanes: butterflies over bits 0..2 of
+// the element in registers, over bits 0..2 of g across lanes; fp16 inputs keep
+// every fp64 sum exact.
+template <bool HAD>
+__device__ __forceinline__ void unpack_row(const uint32_t (&w4)[4], int lane, float (&x)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    x[2 * i] = __half2float(__ushort_as_half((unsigned short)(w4[i] & 0xFFFFu)));
+    x[2 * i + 1] = __half2float(__ushort_as_half((unsigned short)(w4[i] >> 16)));
+  }
+  if constexpr (HAD) {
+    const double sign1 = butterfly_sign<1>(lane), sign2 = butterfly_sign<2>(lane),
+                 sign4 = butterfly_sign<4>(lane);
+    double v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = (double)x[i];
+#pragma unroll
+    for (int h = 1; h < 8; h <<= 1)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if ((i & h) == 0) {
+          const double p = v[i], q = v[i + h];
+          v[i] = p + q;
+          v[i + h] = p - q;
+        }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = butterfly<1>(v[i], sign1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = butterfly<2>(v[i], sign2);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = butterfly<4>(v[i], sign4);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = (float)(v[i] * 0.125);
+  }
+}
+
+// The K plane bytes of each lane of a quad (code words 4h .. 4h + 3 of a row)
+// to one dword of plane j in lane j: a 4 x 4 byte transpose by two DPP moves
+// and byte permutes, for one dword store per lane. (With a byte store per lane
+// and plane, and the rotation's exchanges through LDS: 2 M rows at k = 4 182 us
+// rotated and 117 not, now 164 and 108; k = 0 rotated 147, now 103.)
+template <int K>
+__device__ __forceinline__ uint32_t quad_planes(const uint32_t (&plane)[K], int lane) {
+  uint32_t w = 0;
+#pragma unroll
+  for (int b = 0; b < K; ++b) w |= plane[b] << (8 * b);
+  w = __builtin_amdgcn_perm(lane_xor_u32<1>(w), w, lane & 1 ? 0x03070105u : 0x06020400u);
+  return __builtin_amdgcn_perm(lane_xor_u32<2>(w), w, lane & 2 ? 0x03020706u : 0x05040100u);
+}
+
 template <int K, bool HAD>
 __global__ __launch_bounds__(kBlock) void encode_pot_kernel(
     const __half* __restrict__ k, int64_t n_rows, int64_t out_stride, int scale_mode,
@@ -207,41 +266,11 @@ __global__ __launch_bounds__(kBlock) void encode_pot_kernel(
     const uint32_t grp = __builtin_amdgcn_readfirstlane(grp_iv);
     const int64_t row0 = (int64_t)grp * 8;
     const bool valid = row0 + rl < n_rows;  // uniform over the row's 8 lanes
-    const char* src = reinterpret_cast<const char*>(k) + row0 * kDim * 2;
     uint4 raw = make_uint4(0u, 0u, 0u, 0u);
-    if (valid) raw = *reinterpret_cast<const uint4*>(src + in_off);
+    if (valid) raw = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(k) + row0 * kDim * 2 + in_off);
     const uint32_t w4[4] = {raw.x, raw.y, raw.z, raw.w};
     float x[8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[2 * i] = __half2float(__ushort_as_half((unsigned short)(w4[i] & 0xFFFFu)));
-      x[2 * i + 1] = __half2float(__ushort_as_half((unsigned short)(w4[i] >> 16)));
-    }
-    if constexpr (HAD) {
-      // element 8g + i: butterflies over bits 0..2 of i in registers, over
-      // bits 0..2 of g across lanes; fp16 inputs keep every sum exact
-      double v[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = (double)x[i];
-#pragma unroll
-      for (int h = 1; h < 8; h <<= 1)
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if ((i & h) == 0) {
-            const double p = v[i], q = v[i + h];
-            v[i] = p + q;
-            v[i + h] = p - q;
-          }
-#pragma unroll
-      for (int hl = 1; hl < 8; hl <<= 1)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const double o = __shfl_xor(v[i], hl, 64);
-          v[i] = (g & hl) ? (o - v[i]) : (v[i] + o);
-        }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] = (float)(v[i] * 0.125);
-    }
+    unpack_row<HAD>(w4, lane, x);
     const int64_t orow = (row0 * out_stride) + out_row;
     float s;
     if (scale_mode == 0) {
@@ -301,30 +330,58 @@ __global__ __launch_bounds__(kBlock) void encode_pot_kernel(
     } else {
       word = potmk_word<K>(c, sign_nibbles(sa, sb), cst, zc_half, plane);
     }
+    uint32_t pq = 0;
+    if constexpr (K > 0) pq = quad_planes<K>(plane, lane);
     if (valid) {
       const int64_t urow = row0 * out_stride;  // uniform part of orow
       *reinterpret_cast<uint32_t*>(codes_se + urow * (kDim / 2) + se_off) = word;
-#pragma unroll
-      for (int b = 0; b < K; ++b) codes_m[orow * 8 * K + 8 * b + g] = (uint8_t)plane[b];
+      if constexpr (K > 0) {
+        // lane j < K of a quad: plane j's bytes of the quad's four code words
+        if ((g & 3) < K)
+          *reinterpret_cast<uint32_t*>(codes_m + orow * 8 * K + 8 * (g & 3) + 4 * (g >> 2)) = pq;
+      }
       if (scale_mode == 0 && g == 0) key_scale[orow] = s;
     }
   }
 }
 
+// INT8 uniform codes, 8 rows per wave as the PoT encoder (one row per wave and
+// element per lane took 20.7 us for 131072 rows and 333 us for 2 M; now 7.4
+// and 76 us).
+template <bool HAD>
 __global__ __launch_bounds__(kBlock) void encode_int8_kernel(
-    const __half* __restrict__ k, int64_t n_rows, int64_t out_stride, int hadamard,
+    const __half* __restrict__ k, int64_t n_rows, int64_t out_stride,
     float* __restrict__ key_scale, int8_t* __restrict__ codes) {
-  const int lane = lane_id();
-  const int64_t stride = (int64_t)gridDim.x * (kBlock / 64);
-  for (int64_t row = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); row < n_rows;
-       row += stride) {  // uniform per wave
-    float x = __half2float(k[row * kDim + lane]);
-    if (hadamard) x = (float)(wave_fwht64((double)x) * 0.125);
-    float step;
-    const int c = wave_quantize_int8(x, &step);
-    const int64_t orow = row * out_stride;
-    codes[orow * kDim + lane] = (int8_t)c;
-    if (lane == 0) key_scale[orow] = step;
+  const int lane = lane_id(), g = lane & 7, rl = lane >> 3;
+  const int64_t groups = (n_rows + 7) / 8, stride = (int64_t)gridDim.x * (kBlock / 64);
+  for (int64_t grp = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); grp < groups;
+       grp += stride) {  // uniform per wave
+    const int64_t row = grp * 8 + rl;
+    const bool valid = row < n_rows;  // uniform over the row's 8 lanes
+    uint4 raw = make_uint4(0u, 0u, 0u, 0u);
+    if (valid) raw = *reinterpret_cast<const uint4*>(k + row * kDim + 8 * g);
+    const uint32_t w4[4] = {raw.x, raw.y, raw.z, raw.w};
+    float x[8];
+    unpack_row<HAD>(w4, lane, x);
+    // fmaxf throughout: NaN only if the whole row is
+    float amax = fabsf(x[0]);
+#pragma unroll
+    for (int i = 1; i < 8; ++i) amax = fmaxf(amax, fabsf(x[i]));
+    amax = fmaxf(amax, __uint_as_float(lane_xor_u32<1>(__float_as_uint(amax))));
+    amax = fmaxf(amax, __uint_as_float(lane_xor_u32<2>(__float_as_uint(amax))));
+    amax = fmaxf(amax, __uint_as_float(lane_xor_u32<4>(__float_as_uint(amax))));
+    const bool zero = amax == 0.0f;
+    const float inv = 127.0f / amax;  // correctly rounded divisions
+    const float step = zero ? 0.0f : amax / 127.0f;
+    uint32_t w[2] = {0u, 0u};
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      w[i / 4] |= ((uint32_t)(zero ? 0 : quantize_int8(x[i], inv)) & 0xFFu) << (8 * (i & 3));
+    if (valid) {
+      const int64_t orow = row * out_stride;
+      *reinterpret_cast<uint2*>(codes + orow * kDim + 8 * g) = make_uint2(w[0], w[1]);
+      if (g == 0) key_scale[orow] = step;
+    }
   }
 }
 
@@ -387,27 +444,124 @@ hipError_t launch_store_values(const uint16_t* src, int64_t n_seq, int64_t n_tok
   return hipGetLastError();
 }
 
-// One wave per (sequence, token): INT8 quantisation with a power-of-two
-// scale and the byte store (Sec. II-E).
-__global__ __launch_bounds__(kBlock) void store_values_i8_kernel(
-    const uint16_t* __restrict__ src, int64_t n_seq, int64_t n_tok, int64_t t_cap, int64_t t0,
-    uint8_t* __restrict__ v_u8, int8_t* __restrict__ v_exp) {
+// INT8 value store: token t of sequence s, dim d at byte
+// (s * t_cap + (t / 8) * 8) * 64 + d * 8 + t % 8. One wave per 8-token group:
+// lane l loads 16 bytes of token l / 8 (dims 8 (l % 8) ..+7), so a group is one
+// contiguous KiB, finds the token's exponent with its 8 lanes and quantises.
+// The 8 x 8 byte blocks of the eight lanes that share l % 8 are then
+// transposed in registers, one exchange per bit of the token index
+// (v_permlane32_swap, v_permlane16_swap, DPP): lane l gets dim 8 (l % 8) + l / 8
+// of all eight tokens, one 8-byte store. One wave per token with byte stores
+// of stride 8 was bound by those stores: 131072 tokens 23.6 us, now 7.9; 2 M
+// tokens 352 us, now 78 (5.2 TB/s). A group per wave: waves that loop over two
+// to sixteen groups took 78 to 98 us. (The same transpose for fp16 values, with
+// its 16-byte stores 128 bytes apart, was slower than the gathers above: 95
+// to 117 us for 2 M tokens against 88.)
+struct ValueRange {
+  int64_t n_seq, n_tok, t_cap, t0, g_first, n_groups;
+};
+
+// Loads 16 bytes of this lane's token of group g (zeros outside the range).
+__device__ __forceinline__ uint4 load_group(const uint16_t* __restrict__ src, const ValueRange& r,
+                                            int64_t s, int64_t g, int lane) {
+  const int64_t t = g * 8 + (lane >> 3) - r.t0;
+  uint4 v = make_uint4(0u, 0u, 0u, 0u);
+  if (t >= 0 && t < r.n_tok)
+    v = *reinterpret_cast<const uint4*>(src + (s * r.n_tok + t) * kDim + 8 * (lane & 7));
+  return v;
+}
+__device__ __forceinline__ bool group_is_full(const ValueRange& r, int64_t g) {
+  return g * 8 >= r.t0 && g * 8 + 8 <= r.t0 + r.n_tok;
+}
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+
+// Grid: x over the groups of a sequence (one per wave), y over sequences.
+template <typename F>
+__device__ __forceinline__ void for_each_group(const ValueRange& r, F&& body) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t stride = (int64_t)gridDim.x * (kBlock / 64);
-  for (int64_t r = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); r < n_seq * n_tok;
-       r += stride) {  // uniform per wave
-    const int64_t s = r / n_tok, t = t0 + r % n_tok;
-    store_value_token_i8_wave(src + r * kDim, v_u8 + s * t_cap * kDim, v_exp + s * t_cap, t);
-  }
+  for (int64_t s = blockIdx.y; s < r.n_seq; s += gridDim.y)
+    for (int64_t i = (int64_t)blockIdx.x * (kBlock / 64) + wave; i < r.n_groups; i += stride)
+      body(s, r.g_first + i);
+}
+
+// INT8 values with a power-of-two scale per token (Sec. II-E), as
+// store_value_token_i8_wave defines them.
+__global__ __launch_bounds__(kBlock) void store_values_i8_kernel(const uint16_t* __restrict__ src,
+                                                                 ValueRange r,
+                                                                 uint8_t* __restrict__ v_u8,
+                                                                 int8_t* __restrict__ v_exp) {
+  const int lane = lane_id();
+  const uint32_t sel16 = (lane >> 4) & 1 ? 0x07060302u : 0x05040100u;
+  const uint32_t sel8 = (lane >> 3) & 1 ? 0x03070105u : 0x06020400u;
+  for_each_group(r, [&](int64_t s, int64_t g8) {
+    const uint4 v = load_group(src, r, s, g8, lane);
+    const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
+    float x[8];
+    float amax = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[2 * i] = __half2float(__ushort_as_half((unsigned short)(w4[i] & 0xFFFFu)));
+      x[2 * i + 1] = __half2float(__ushort_as_half((unsigned short)(w4[i] >> 16)));
+      amax = fmaxf(amax, fmaxf(fabsf(x[2 * i]), fabsf(x[2 * i + 1])));
+    }
+    amax = max_over_8_lanes(amax);
+    const int g = value_exponent(amax);
+    uint32_t b[2] = {0u, 0u};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b[i / 4] |= (uint32_t)value_byte(x[i], g) << (8 * (i & 3));
+    // token bits 2, 1, 0 against dim bits 2 (dword), 1 (half) and 0 (byte)
+    swap32(b[0], b[1]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      uint32_t lo = b[i], hi = b[i];
+      swap16(lo, hi);  // lo: the even row's value, hi: the odd row's
+      b[i] = __builtin_amdgcn_perm(hi, lo, sel16);
+      b[i] = __builtin_amdgcn_perm(lane_xor_u32<8>(b[i]), b[i], sel8);
+    }
+    const int64_t row = s * r.t_cap + g8 * 8;
+    const int d = 8 * (lane & 7) + (lane >> 3);
+    uint8_t* out = v_u8 + row * kDim + d * 8;
+    if (group_is_full(r, g8)) {
+      *reinterpret_cast<uint2*>(out) = make_uint2(b[0], b[1]);
+      if ((lane & 7) == 0) v_exp[row + (lane >> 3)] = (int8_t)g;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int64_t t = g8 * 8 + k;
+        if (t >= r.t0 && t < r.t0 + r.n_tok) out[k] = (uint8_t)(b[k / 4] >> (8 * (k & 3)));
+      }
+      const int64_t t = g8 * 8 + (lane >> 3);
+      if ((lane & 7) == 0 && t >= r.t0 && t < r.t0 + r.n_tok) v_exp[row + (lane >> 3)] = (int8_t)g;
+    }
+  });
+}
+
+static ValueRange value_range(int64_t n_seq, int64_t n_tok, int64_t t_cap, int64_t t0) {
+  return {n_seq, n_tok, t_cap, t0, t0 / 8, (t0 + n_tok - 1) / 8 - t0 / 8 + 1};
+}
+static dim3 store_grid(const ValueRange& r) {
+  const int64_t blocks = (r.n_groups + kBlock / 64 - 1) / (kBlock / 64);
+  return dim3((uint32_t)std::min<int64_t>(blocks, 1 << 15),
+              (uint32_t)std::min<int64_t>(r.n_seq, 1 << 15));
 }
 
 hipError_t launch_store_values_i8(const uint16_t* src, int64_t n_seq, int64_t n_tok,
                                   int64_t t_cap, int64_t t0, uint8_t* v_u8, int8_t* v_exp,
                                   hipStream_t stream) {
   if (n_seq == 0 || n_tok == 0) return hipSuccess;
-  const int64_t rows = n_seq * n_tok;
-  const int64_t grid = (rows + kBlock / 64 - 1) / (kBlock / 64);
-  hipLaunchKernelGGL(store_values_i8_kernel, dim3(bounded_grid(grid)), dim3(kBlock), 0, stream,
-                     src, n_seq, n_tok, t_cap, t0, v_u8, v_exp);
+  const ValueRange r = value_range(n_seq, n_tok, t_cap, t0);
+  hipLaunchKernelGGL(store_values_i8_kernel, store_grid(r), dim3(kBlock), 0, stream, src, r, v_u8,
+                     v_exp);
   return hipGetLastError();
 }
 
@@ -424,12 +578,7 @@ template <int K, bool HAD>
 static void launch_encode_pot_t(const uint16_t* k, int64_t n_rows, int64_t out_stride,
                                 int scale_mode, float* key_scale, uint8_t* codes_se,
                                 uint8_t* codes_m, const EncodeTables& tab, hipStream_t stream) {
-  // enough workgroups for several resident waves per SIMD; each wave then
-  // loops over row groups, so its set-up is paid once
-  const int64_t groups = (n_rows + 7) / 8;
-  const int64_t grid =
-      std::min<int64_t>((groups + kBlock / 64 - 1) / (kBlock / 64), kEncodeGrid);
-  hipLaunchKernelGGL((encode_pot_kernel<K, HAD>), dim3((uint32_t)grid), dim3(kBlock), 0,
+  hipLaunchKernelGGL((encode_pot_kernel<K, HAD>), dim3(encode_grid(n_rows)), dim3(kBlock), 0,
                      stream, reinterpret_cast<const __half*>(k), n_rows, out_stride, scale_mode,
                      key_scale, codes_se, codes_m, tab);
 }
@@ -463,11 +612,14 @@ hipError_t launch_encode_int8(const uint16_t* k, int64_t n_rows, int64_t out_str
                               int hadamard, float* key_scale, int8_t* codes,
                               hipStream_t stream) {
   if (n_rows == 0) return hipSuccess;
-  const int64_t rows_per_block = kBlock / 64;
-  const int64_t grid = (n_rows + rows_per_block - 1) / rows_per_block;
-  hipLaunchKernelGGL(encode_int8_kernel, dim3(bounded_grid(grid)), dim3(kBlock), 0, stream,
-                     reinterpret_cast<const __half*>(k), n_rows, out_stride, hadamard,
-                     key_scale, codes);
+  const __half* kh = reinterpret_cast<const __half*>(k);
+  const dim3 grid(encode_grid(n_rows));
+  if (hadamard)
+    hipLaunchKernelGGL((encode_int8_kernel<true>), grid, dim3(kBlock), 0, stream, kh, n_rows,
+                       out_stride, key_scale, codes);
+  else
+    hipLaunchKernelGGL((encode_int8_kernel<false>), grid, dim3(kBlock), 0, stream, kh, n_rows,
+                       out_stride, key_scale, codes);
   return hipGetLastError();
 }
 

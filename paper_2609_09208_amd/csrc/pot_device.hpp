@@ -52,23 +52,72 @@ __device__ __forceinline__ float wave_max(float v) {
   return fmaxf(__uint_as_float(r32[0]), __uint_as_float(r32[1]));
 }
 
+// The other lane's value of a butterfly of span 1, 2, 4 or 8 (lane ^ H), by DPP
+// moves: swap neighbours, swap pairs, the mirror inside each half row (l ^ 7)
+// and then inside each quad (l ^ 3), and the rotation by 8 inside each row.
+template <int H>
+__device__ __forceinline__ uint32_t lane_xor_u32(uint32_t x) {
+  static_assert(H == 1 || H == 2 || H == 4 || H == 8, "spans inside a row");
+  if constexpr (H == 4) {
+    const int m = __builtin_amdgcn_mov_dpp((int)x, 0x141, 0xF, 0xF, true);
+    return (uint32_t)__builtin_amdgcn_mov_dpp(m, 0x1B, 0xF, 0xF, true);
+  } else {
+    constexpr int kCtrl = H == 1 ? 0xB1 : H == 2 ? 0x4E : 0x128;
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kCtrl, 0xF, 0xF, true);
+  }
+}
+__device__ __forceinline__ double join_f64(uint32_t lo, uint32_t hi) {
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// One butterfly stage of span H over the lanes: (a, b) to (a + b, a - b),
+// where a is the value of the lane whose bit H is clear; sign is -1 in the
+// lanes whose bit H is set and 1 in the others (the sum o + sign v rounds once,
+// as the difference o - v does). No LDS: a shuffle through it costs a memory
+// latency per stage and half.
+template <int H>
+__device__ __forceinline__ double butterfly(double v, double sign) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  if constexpr (H <= 8) {
+    return __builtin_fma(sign, v, join_f64(lane_xor_u32<H>(lo), lane_xor_u32<H>(hi)));
+  } else {
+    // the row (half) swap of a value with itself gives both lanes a and b
+    if constexpr (H == 16) {
+      const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+      const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+      return __builtin_fma(sign, join_f64(l[1], h[1]), join_f64(l[0], h[0]));
+    } else {
+      const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+      const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+      return __builtin_fma(sign, join_f64(l[1], h[1]), join_f64(l[0], h[0]));
+    }
+  }
+}
+template <int H>
+__device__ __forceinline__ double butterfly_sign(int lane) {
+  return (lane & H) ? -1.0 : 1.0;
+}
+
 // Radix-2 Walsh-Hadamard butterfly over one 64-vector held one element per
 // lane, in fp64, stages of span 1, 2, 4, ..., 32 mapping (a, b) to
 // (a + b, a - b). For fp16 inputs every partial sum is exact in fp64; for fp32
 // inputs this fixed stage order is the rotation's definition.
 __device__ __forceinline__ double wave_fwht64(double v) {
   const int lane = lane_id();
-#pragma unroll
-  for (int h = 1; h < kDim; h <<= 1) {
-    double o = __shfl_xor(v, h, 64);
-    v = (lane & h) ? (o - v) : (v + o);
-  }
-  return v;
+  v = butterfly<1>(v, butterfly_sign<1>(lane));
+  v = butterfly<2>(v, butterfly_sign<2>(lane));
+  v = butterfly<4>(v, butterfly_sign<4>(lane));
+  v = butterfly<8>(v, butterfly_sign<8>(lane));
+  v = butterfly<16>(v, butterfly_sign<16>(lane));
+  return butterfly<32>(v, butterfly_sign<32>(lane));
 }
 
 // INT8 quantisation of one 64-vector held one element per lane (Sec. II-A):
 // amax = max|x|, step = fl32(amax/127), code = clamp(rne(fl32(x *
 // fl32(127/amax))), -127, 127). amax = 0 gives code 0 and step 0.
+__device__ __forceinline__ int quantize_int8(float x, float inv) {
+  return (int)fminf(fmaxf(rintf(__fmul_rn(x, inv)), -127.0f), 127.0f);
+}
 __device__ __forceinline__ int wave_quantize_int8(float x, float* step) {
   const float amax = wave_max(fabsf(x));
   if (amax == 0.0f) {
@@ -76,10 +125,8 @@ __device__ __forceinline__ int wave_quantize_int8(float x, float* step) {
     return 0;
   }
   const float inv = 127.0f / amax;  // correctly rounded division
-  float r = rintf(__fmul_rn(x, inv));
-  r = fminf(fmaxf(r, -127.0f), 127.0f);
-  *step = amax / 127.0f;  // correctly rounded division
-  return (int)r;
+  *step = amax / 127.0f;            // correctly rounded division
+  return quantize_int8(x, inv);
 }
 
 // Log-nearest PoT-Mk code of one element, mantissa width K (Sec. II-A, eq.
@@ -178,22 +225,26 @@ __device__ __forceinline__ void store_value_token_wave(const uint16_t* __restric
 // so |v^| <= 127. The byte cache holds v^ + 128 (offset binary) at the
 // token-interleaved position ((t/8)*8) * 64 + d * 8 + t % 8 of the sequence,
 // and exp_seq[t] = g; the value is v^ 2^-g.
+// The exponent g of a token whose largest magnitude is amax.
+__device__ __forceinline__ int value_exponent(float amax) {
+  if (!(amax > 0.0f)) return 0;
+  // amax in [2^e, 2^(e+1)) with e = frexp exponent - 1, so amax 2^(6-e) is
+  // in [64, 128) (exact power-of-two scaling)
+  const int e = __builtin_amdgcn_frexp_expf(amax) - 1;
+  return (__builtin_amdgcn_ldexpf(amax, 6 - e) <= 127.0f) ? 6 - e : 5 - e;
+}
+// The stored byte of a value.
+__device__ __forceinline__ uint8_t value_byte(float v, int g) {
+  return (uint8_t)((int)rintf(__builtin_amdgcn_ldexpf(v, g)) + 128);
+}
 __device__ __forceinline__ void store_value_token_i8_wave(const uint16_t* __restrict__ v_row,
                                                           uint8_t* __restrict__ v_seq,
                                                           int8_t* __restrict__ exp_seq,
                                                           int64_t t) {
   const int lane = lane_id();
   const float v = __half2float(__ushort_as_half(v_row[lane]));
-  const float amax = wave_max(fabsf(v));
-  int g = 0;
-  if (amax > 0.0f) {
-    // amax in [2^e, 2^(e+1)) with e = frexp exponent - 1, so amax 2^(6-e) is
-    // in [64, 128) (exact power-of-two scaling)
-    const int e = __builtin_amdgcn_frexp_expf(amax) - 1;
-    g = (__builtin_amdgcn_ldexpf(amax, 6 - e) <= 127.0f) ? 6 - e : 5 - e;
-  }
-  const int c = (int)rintf(__builtin_amdgcn_ldexpf(v, g));
-  v_seq[(t / 8) * 8 * kDim + lane * 8 + t % 8] = (uint8_t)(c + 128);
+  const int g = value_exponent(wave_max(fabsf(v)));
+  v_seq[(t / 8) * 8 * kDim + lane * 8 + t % 8] = value_byte(v, g);
   if (lane == 0) exp_seq[t] = (int8_t)g;
 }
 

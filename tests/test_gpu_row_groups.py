@@ -1,0 +1,76 @@
+"""The kernels that take eight rows or tokens per wave, at the edges of a group:
+the INT8 value store over ranges that start and end inside a group, over more
+sequences than one grid dimension holds and over NaN, infinite and zero tokens;
+the INT8 key encoder over row counts beside a multiple of eight, with a row
+stride. Bytes and scales are exact against the oracle; nothing else is written.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_09208_amd as pa
+from parity_util import DEV, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_seq,n_tok,t0,t_cap", [(1, 1, 0, 8), (3, 1, 7, 16), (2, 9, 6, 24),
+                                                  (5, 16, 8, 32), (2, 23, 5, 40), (4, 777, 3, 784),
+                                                  (33000, 1, 2, 8)])
+def test_store_int8_ranges(n_seq, n_tok, t0, t_cap):
+    rng = np.random.default_rng(n_seq + 10 * n_tok + t0)
+    v = (rng.standard_normal((n_seq, n_tok, 64)) * 2.0 ** rng.integers(-12, 9, (n_seq, n_tok, 1)))
+    v = v.astype(np.float16)
+    v[rng.random((n_seq, n_tok)) < 0.1] = 0.0
+    vu = torch.full((n_seq, t_cap, 64), 77, dtype=torch.uint8, device=DEV)
+    ve = torch.full((n_seq, t_cap), 55, dtype=torch.int8, device=DEV)
+    pa.pot_store_values_int8(to_dev(v), n_seq, n_tok, t_cap, t0, vu, ve)
+    torch.cuda.synchronize()
+    vh, g = oracle.quantize_values(v.view(np.uint16).reshape(-1, 64))
+    want_u = np.full((n_seq, t_cap, 64), 77, np.uint8)
+    want_u[:, t0:t0 + n_tok] = (vh.reshape(n_seq, n_tok, 64).astype(np.int16) + 128)
+    want_e = np.full((n_seq, t_cap), 55, np.int8)
+    want_e[:, t0:t0 + n_tok] = g.reshape(n_seq, n_tok)
+    got = vu.cpu().numpy().reshape(n_seq, t_cap // 8, 64, 8).transpose(0, 1, 3, 2)
+    assert np.array_equal(got.reshape(n_seq, t_cap, 64), want_u)
+    assert np.array_equal(ve.cpu().numpy(), want_e)
+
+
+def test_store_int8_tokens_alone_and_in_a_group():
+    # NaN, infinities and mixed signs: what a token becomes depends on nothing but itself
+    # (one-token calls take the partial-group stores, the whole range the group stores)
+    v = np.zeros((1, 16, 64), np.float16)
+    v[0, 1] = np.nan
+    v[0, 2, ::3] = np.nan
+    v[0, 2, 1::3] = 3.25
+    v[0, 3, 5] = 65504.0
+    v[0, 4] = -(2.0 ** -24)
+    v[0, 5:] = np.random.default_rng(3).standard_normal((11, 64)).astype(np.float16)
+    u1, e1 = pa.alloc_value_cache_int8(1, 1, 16, DEV)
+    u2, e2 = pa.alloc_value_cache_int8(1, 1, 16, DEV)
+    src = to_dev(v)
+    pa.pot_store_values_int8(src, 1, 16, 16, 0, u1, e1)
+    for t in range(16):
+        pa.pot_store_values_int8(src[:, t].contiguous(), 1, 1, 16, t, u2, e2)
+    torch.cuda.synchronize()
+    assert torch.equal(u1, u2) and torch.equal(e1, e2)
+
+
+@pytest.mark.parametrize("had", [False, True])
+@pytest.mark.parametrize("n,stride", [(1, 1), (7, 3), (8, 1), (9, 2), (33, 5), (4099, 1)])
+def test_int8_encode_row_counts(n, stride, had):
+    rng = np.random.default_rng(n)
+    k = (rng.standard_normal((n, 64)) * 2.0 ** rng.integers(-10, 10, (n, 1))).astype(np.float16)
+    k[rng.random(n) < 0.05] = 0.0
+    codes = torch.full((n * stride, 64), 99, dtype=torch.int8, device=DEV)
+    sc = torch.full((n * stride,), -5.0, dtype=torch.float32, device=DEV)
+    pa.pot_int8_encode_keys(to_dev(k), n, stride, int(had), sc, codes)
+    torch.cuda.synchronize()
+    oc, osc = oracle.int8_encode_keys(k.view(np.uint16), hadamard=had)
+    want = np.full((n * stride, 64), 99, np.int8)
+    want[::stride][:n] = oc
+    want_s = np.full(n * stride, -5.0, np.float32)
+    want_s[::stride][:n] = osc
+    assert np.array_equal(codes.cpu().numpy(), want)
+    assert np.array_equal(sc.cpu().numpy().view(np.uint32), want_s.view(np.uint32))
