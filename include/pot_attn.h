@@ -115,15 +115,16 @@ typedef struct pot_format {
  *  force_wg_waves (in) 0: the planner picks the decode workgroup size; 4:
  *               four-wave workgroups, each wave taking every fourth 64-key
  *               tile of its split; or the wave count of the engine's
- *               CU-wide variant: one workgroup per CU whose waves claim the
+ *               CU-wide variant: one workgroup per CU whose waves may claim the
  *               split's tiles from a counter in LDS (shift-accumulate
  *               kernels, fp16 or INT8 values: 16 at k <= 2, 12 at k = 3
  *               and 4; decoded-code engines: 16, or 12 for PoT-4 bytes over
  *               fp16 values or with power-of-two weights; INT8 comparator:
  *               12; the fp16 comparator has none). Other values return
  *               POT_ERR_INVALID_ARG. Scores and maxima do not
- *               depend on it; O does to fp32 rounding (with claimed tiles the
- *               order of the sums varies from call to call).
+ *               depend on it; O does to fp32 rounding (claimed tiles, whose
+ *               order varies from call to call, are used where the grid
+ *               fills the chip and a wave has more than four tiles).
  *  wg_waves     (out) the waves per workgroup used (written on the host)
  */
 typedef struct pot_debug {
@@ -242,8 +243,8 @@ pot_status pot_workspace_init(void* workspace, size_t ws_bytes, void* stream);
  * order; the running maximum is the integer M = ceil(max x)
  * (eq. logsm) so rescales are exact powers of two; weights 2^(x-M) multiply
  * the fp16 values with fp32 accumulation (matrix cores, weights split into
- * fp16 high and low parts); key splits (chosen to fill the GPU's resident
- * workgroup slots in one round) are merged with exact 2^(M_s - M) factors.
+ * fp16 high and low parts); key splits (chosen to give every CU at most one
+ * workgroup) are merged with exact 2^(M_s - M) factors.
  * Launches: the split decode kernel (which prepares the queries) and, with
  * more than one split, a combine kernel, both on `stream`.
  */

@@ -81,9 +81,7 @@ struct Plan {
   int n_splits, split_len;
 };
 
-// Key splits: enough workgroups to fill the GPU's resident slots in a single
-// dispatch round (slots = CUs x resident workgroups per CU); one split when
-// the (batch, kv head) pairs alone fill it. Splits are whole 256-key tiles.
+// S key splits of T keys, in whole 256-key tiles.
 Plan plan_from_count(int T, int S) {
   const int tiles = (T + kTile - 1) / kTile;
   S = std::max(1, std::min(S, tiles));
@@ -98,21 +96,6 @@ int split_count_for_slots(long units, long slots) {
   return units >= slots ? 1 : (int)(slots / units);
 }
 
-// Split count when the grid would fill the GPU's resident slots with short
-// splits: splits of at least two 256-key tiles, unless that leaves fewer
-// than 256 workgroups (one per CU) when the keys allow more. Measured with
-// the four-wave split combine: B = 1, T = 32768: 18.6 us with 64 two-tile
-// splits, 19.2 us with 128 one-tile splits, 22.5 us with 32 four-tile
-// splits; B = 1, T = 4096: 17.1 us with 16 one-tile splits, 17.5 us with 8.
-constexpr int kMinTilesPerSplit = 2;
-constexpr long kMinWorkgroups = 256;
-
-int split_count_short_ranges(long units, int tiles) {
-  const int s_len = std::max(1, tiles / kMinTilesPerSplit);
-  const int s_spread = (int)std::min<long>(tiles, (kMinWorkgroups + units - 1) / units);
-  return std::max(s_len, s_spread);
-}
-
 // Upper bound used to size workspaces without a device query: 256 CUs x 8
 // resident workgroups (the decode kernels reach at most 4 per CU: 4 waves per SIMD).
 constexpr long kMaxSlots = 256L * 8;
@@ -122,9 +105,6 @@ Plan plan_bound(int B, int Hkv, int T) {
 }
 
 std::atomic<int> g_cus[64];
-// [default / CU-wide variant][score mode][value format][G][mant_bits]
-std::atomic<int> g_occ[2][4][3][9][5];
-
 int device_cus() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
@@ -138,22 +118,52 @@ int device_cus() {
   return cus;
 }
 
-long device_slots(int mode, int G, int mant_bits, int vf, bool pool) {
-  const int cus = device_cus();
-  std::atomic<int>& slot = g_occ[pool ? 1 : 0][mode][vf][G][mant_bits];
-  int occ = slot.load(std::memory_order_relaxed);
-  if (occ <= 0) {
-    occ = decode_occupancy(mode, G, mant_bits, vf, pool);
-    if (occ <= 0) occ = pool ? 1 : 2;
-    slot.store(occ, std::memory_order_relaxed);
+// How a decode call is split: (batch, kv head) units times key splits, on
+// four-wave or CU-wide (pw waves, 0: the engine has none) workgroups.
+//  - Up to one unit per CU: CU-wide workgroups and as many splits as give every
+//    CU at most one. More splits cost a second round of prologues, fewer leave
+//    CUs idle; four-wave workgroups take longer over the prologue (two heads'
+//    queries per wave) and the merge. PoT-4, graph replays, us: B = 16 (64
+//    units) T = 4096 14.4 with 4 splits, 15.1 with 8 on four waves, 16.4 with 4;
+//    B = 40 (160 units) T = 16384 70.2 with 1, 75 with 3, 72.8 with 3 on four
+//    waves; B = 6 T = 16384 17.4 with 10, 18.0 with 8, 18.3 with 32 on four.
+//  - Where every wave of one workgroup has at most one 64-key tile, one split
+//    and no merge kernel: up to 768 keys (T = 512, B = 1 7.9 against 9.3 with
+//    two splits, B = 64 9.3 against 10.8), and up to 16 tiles on 16 waves if a
+//    quarter of the CUs has a unit (T = 1024, B = 16 10.4 against 10.8 with four
+//    splits, B = 32 10.7 against 12.2 with two; B = 4 9.7 against 9.5).
+//  - More units than CUs: one split of four-wave workgroups, several of which
+//    share a CU, for up to 8191 keys (B = 128: T = 256 10.1 against 12.7
+//    CU-wide, T = 4096 58.1 against 59.1; B = 80 43.3 against 48.7); CU-wide
+//    above, whose waves claim tiles (B = 512, T = 4096 222 against 226), in
+//    three splits where the second round of one would leave over 30% of the CUs
+//    idle (B = 80, T = 16384 143 against 165).
+constexpr int kShortKeys = 768, kLongKeys = 8192;
+struct Launch {
+  Plan plan;
+  bool pool;
+};
+
+Launch plan_launch(long units, int T, int pw, int cus, int bound) {
+  const bool one_tile = pw > 0 && (T <= kShortKeys || (T <= pw * 64 && 4 * units >= cus));
+  int S = 1;
+  bool pool = pw > 0;
+  if (units <= cus) {
+    if (!one_tile) S = (int)(cus / units);
+  } else {
+    pool = pool && T >= kLongKeys;
+    if (pool && 10 * units < 14L * cus) S = 3;
   }
-  return (long)cus * occ;
+  return {plan_from_count(T, std::min(S, bound)), pool};
 }
 
-// The CU-wide variant (one workgroup of pool_waves(...) waves per CU, tiles
-// claimed from a shared counter) replaces the four-wave workgroups when its
-// plan still gives every CU a workgroup and every wave two tiles on average.
-constexpr int kPoolTilesPerWave = 2;
+// CU-wide workgroups claim their tiles from a counter when the grid fills the
+// chip and every wave has over four (long streams drift apart: PoT-4, B = 64, T
+// = 32768 201 us against 206 in fixed order; at four tiles per wave 33.8
+// against 33.5). In fixed order the sums are the same from call to call.
+bool claims_tiles(long units, const Plan& p, int pw, int cus) {
+  return units * p.n_splits >= cus && p.split_len > 4 * pw * 64;
+}
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -235,28 +245,17 @@ pot_status decode_common(int mode, int mant_bits, DecodeArgs& a, const int32_t* 
     return fail(POT_ERR_INVALID_ARG, "force_wg_waves %d is neither 0, %d nor %d", want,
                 kBlock / 64, pw);
   const long units = (long)B * Hkv;
+  const int cus = device_cus();
   Plan p;
-  bool pool = false;
+  bool pool;
   if (force > 0) {
     p = plan_from_count(T, force);
-    pool = pw > 0 && (want == pw || (want == 0 && units * p.n_splits >= device_cus() &&
-                                     p.split_len >= kPoolTilesPerWave * pw * 64));
+    pool = pw > 0 && want != kBlock / 64 && (want == pw || units * p.n_splits <= cus);
   } else {
-    if (pw > 0 && want != kBlock / 64) {
-      const int S = split_count_for_slots(units, device_slots(mode, G, mbits, vf, true));
-      const Plan pp = plan_from_count(T, std::min(S, plan_bound(B, Hkv, T).n_splits));
-      if (want == pw ||
-          (units * pp.n_splits >= device_cus() && pp.split_len >= kPoolTilesPerWave * pw * 64)) {
-        p = pp;
-        pool = true;
-      }
-    }
-    if (!pool) {
-      const int S = split_count_for_slots(units, device_slots(mode, G, mbits, vf, false));
-      const int tiles = (T + kTile - 1) / kTile;
-      const int s_short = split_count_short_ranges(units, tiles);
-      p = plan_from_count(T, std::min({S, s_short, plan_bound(B, Hkv, T).n_splits}));
-    }
+    const Launch l = plan_launch(units, T, want == kBlock / 64 ? 0 : pw, cus,
+                                 plan_bound(B, Hkv, T).n_splits);
+    p = l.plan;
+    pool = pw > 0 && (want == pw || l.pool);
   }
   const WsLayout w = ws_layout(B, Hq, Hkv, p.n_splits);
   if (ws_bytes < w.total)
@@ -274,6 +273,7 @@ pot_status decode_common(int mode, int mant_bits, DecodeArgs& a, const int32_t* 
   a.n_splits = p.n_splits;
   a.split_len = p.split_len;
   a.wg_waves = pool ? pw : kBlock / 64;
+  a.claim_tiles = pool && claims_tiles(units, p, pw, cus);
   bool debug = false;
   hipEvent_t ev_begin = nullptr, ev_end = nullptr;
   if (dbg) {

@@ -6,10 +6,9 @@
 // kv head (GQA), so every code and value byte is read from HBM once and used
 // G times. Inside the workgroup each wave streams its own 64-key tiles
 // (tile j of the range goes to wave j % 4; in the CU-wide variant the waves
-// claim tiles from a counter in LDS) with the next tile's keys (and, for
-// the short score cores, value fragments) prefetched into registers while
-// the current one is processed; waves only meet at the end to merge their
-// partial sums.
+// may claim tiles from a counter in LDS), with the next tile's keys requested
+// before a tile is scored and its values once this tile's are used; waves only
+// meet at the end to merge their partial sums.
 //
 // Per 64-key tile and wave:
 //  1. Scores (Sec. II-B eq. sac). Shift-accumulate: exact integer sums on the
@@ -156,6 +155,13 @@ struct ValRegs<true> {
 // that the compiler can count outstanding loads statically and keep the
 // prefetch of the next tile in flight while the current one is processed; keys
 // past the range are masked when the tile is consumed.
+// A lane's offset, opaque in each tile: the constant distances of a tile's loads
+// then fold into the instructions' immediate offsets, where the compiler would
+// otherwise keep every sum in a register of its own across the loop.
+__device__ __forceinline__ int tile_offset(int off, int t0) {
+  asm("" : "+v"(off) : "s"(t0));
+  return off;
+}
 __device__ __forceinline__ uint4 load_b128(BufRsrc rs, int off, bool aux_nt) {
   const u32x4v v = aux_nt ? __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kAuxNt)
                           : __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
@@ -176,36 +182,38 @@ __device__ __forceinline__ void load_keys(const Streams& st, int t0, int lane,
   if constexpr (MODE == kScoreInt8 || MODE == kScoreFp16) {
     constexpr int kRow = MODE == kScoreInt8 ? kDim : 2 * kDim, kLoads = kRow / 32;
     const BufRsrc rk = tile_rsrc(st.codes, t0, st.t_end, kRow);
+    const int off = tile_offset(key * kRow + 16 * kLoads * half, t0);
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
       for (int c = 0; c < kLoads; ++c)
-        r.k[s][c] = load_b128(rk, (key + 4 * s) * kRow + 16 * (kLoads * half + c), false);
+        r.k[s][c] = load_b128(rk, off + 4 * s * kRow + 16 * c, false);
     return;
   } else {
   const BufRsrc rc = tile_rsrc(st.codes, t0, st.t_end, kDim / 2);
+  const int off = tile_offset(key * 32 + 16 * half, t0);
 #pragma unroll
-  for (int s = 0; s < 2; ++s) r.c[s] = load_b128(rc, (key + 4 * s) * 32 + 16 * half, true);
+  for (int s = 0; s < 2; ++s) r.c[s] = load_b128(rc, off + 128 * s, true);
   if constexpr (K > 0) {
     const BufRsrc rp = tile_rsrc(st.planes, t0, st.t_end, 8 * K);
+    const int pair = tile_offset(key * 8 * K + (K == 4 ? 16 : 8) * half, t0);
+    const int last = tile_offset(key * 8 * K + 8 * (K - 1) + 4 * half, t0);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const int row = (key + 4 * s) * 8 * K;
       if constexpr (K == 4) {
-        const uint4 v = load_b128(rp, row + 16 * half, true);
+        const uint4 v = load_b128(rp, pair + 32 * K * s, true);
         r.pl[s][0] = v.x;
         r.pl[s][1] = v.y;
         r.pl[s][2] = v.z;
         r.pl[s][3] = v.w;
       } else {
         if constexpr (K >= 2) {
-          const u32x2v v = __builtin_amdgcn_raw_buffer_load_b64(rp, row + 8 * half, 0, kAuxNt);
+          const u32x2v v = __builtin_amdgcn_raw_buffer_load_b64(rp, pair + 32 * K * s, 0, kAuxNt);
           r.pl[s][0] = v.x;
           r.pl[s][1] = v.y;
         }
         if constexpr (K & 1)
-          r.pl[s][K - 1] =
-              __builtin_amdgcn_raw_buffer_load_b32(rp, row + 8 * (K - 1) + 4 * half, 0, kAuxNt);
+          r.pl[s][K - 1] = __builtin_amdgcn_raw_buffer_load_b32(rp, last + 32 * K * s, 0, kAuxNt);
       }
     }
   }
@@ -217,7 +225,7 @@ __device__ __forceinline__ void load_keys(const Streams& st, int t0, int lane,
 __device__ __forceinline__ void load_scales(const Streams& st, int t0, int lane,
                                             uint4 (&s)[2]) {
   const BufRsrc rs = tile_rsrc(st.scales, t0, st.v_end, 4);
-  const int off = (32 * ((lane >> 3) & 1) + 8 * (lane >> 4)) * 4;
+  const int off = tile_offset((32 * ((lane >> 3) & 1) + 8 * (lane >> 4)) * 4, t0);
   s[0] = load_b128(rs, off, true);
   s[1] = load_b128(rs, off + 16, true);
 }
@@ -256,7 +264,7 @@ __device__ __forceinline__ void load_values_buf(const Streams& st, int t0, int l
                                                 ValRegs<V8>& v) {
   constexpr int kGroupBytes = V8 ? 8 * kDim : 16 * kDim;  // one 8-token group
   const BufRsrc rv = tile_rsrc(st.values, t0, st.v_end, kGroupBytes / 8);
-  const int voff = (lane >> 4) * kGroupBytes + (lane & 15) * (V8 ? 8 : 16);
+  const int voff = tile_offset((lane >> 4) * kGroupBytes + (lane & 15) * (V8 ? 8 : 16), t0);
 #pragma unroll
   for (int kb = kFirst; kb < kEnd; ++kb) {
 #pragma unroll
@@ -274,7 +282,8 @@ __device__ __forceinline__ void load_values_buf(const Streams& st, int t0, int l
   if constexpr (V8 && kFirst == 0) {
     const int part = (lane & 15) >> 3, grp = lane >> 4;
     const BufRsrc re = tile_rsrc(st.exps, t0, st.v_end, 1);
-    const u32x2v g = __builtin_amdgcn_raw_buffer_load_b64(re, 32 * part + 8 * grp, 0, 0);
+    const u32x2v g =
+        __builtin_amdgcn_raw_buffer_load_b64(re, tile_offset(32 * part + 8 * grp, t0), 0, 0);
     v.g = make_uint2(g.x, g.y);
   }
 }
@@ -320,7 +329,7 @@ __device__ __forceinline__ void mask_values(int t0, int t_end, int lane, ValRegs
 template <int NW>
 struct alignas(16) MergeSmem {
   alignas(16) float wo[NW][16][kDim];  // per-wave P.V (rows: heads x {hi, lo})
-  float wp[NW][64];  // per-lane sums of the weights
+  float wl[NW][8];   // sums of the weights per head
   int wm[NW][8];
   int gm[NW];        // INT8 values: per-wave minimum exponent
   int next;          // CU-wide variant: the next unclaimed tile of the range
@@ -346,23 +355,42 @@ struct DecodeSmem<kScoreInt8, NW> : MergeSmem<NW> {
 // (Sec. II-F, a cache that holds only codes): wave 0 encodes the key with the
 // row absmax scale, wave 1 stores the values (fp16, or INT8 with their
 // exponent). Only the workgroup whose key range holds row T - 1 calls it.
+// Returns the exponent of INT8 values in wave 1, INT_MAX elsewhere.
 template <int K>
-__device__ __forceinline__ void append_token(const DecodeArgs& a, int64_t seq, int wave) {
+__device__ __forceinline__ int append_token(const DecodeArgs& a, int64_t seq, int wave) {
   const int64_t row = seq * a.t_cap + (a.T - 1);
   if (wave == 0)
     encode_key_row_wave<K>(reinterpret_cast<const __half*>(a.app_k) + seq * kDim, a.hadamard, 0,
                         a.app_key_scale + row, a.app_codes_se + row * (kDim / 2),
                         a.app_codes_m + row * 8 * K, a.app_tab);
   else if (wave == 1 && a.app_v8 != nullptr)
-    store_value_token_i8_wave(a.app_v + seq * kDim, a.app_v8 + seq * a.t_cap * kDim,
-                              a.app_v_exp + seq * a.t_cap, a.T - 1);
+    return store_value_token_i8_wave(a.app_v + seq * kDim, a.app_v8 + seq * a.t_cap * kDim,
+                                     a.app_v_exp + seq * a.t_cap, a.T - 1);
   else if (wave == 1)
     store_value_token_wave(a.app_v + seq * kDim, a.app_v_cache + seq * a.t_cap * kDim, a.T - 1);
+  return INT_MAX;
 }
 
-// The query elements of the heads this wave prepares (wave w of NW: heads w,
-// w + NW), one per lane; loaded first thing so that their latency overlaps
-// the rest of the prologue.
+// Minimum over the wave.
+__device__ __forceinline__ int wave_min(int v) {
+  v = min(v, (int)lane_xor_u32<1>((uint32_t)v));
+  v = min(v, (int)lane_xor_u32<2>((uint32_t)v));
+  v = min(v, (int)lane_xor_u32<4>((uint32_t)v));
+  v = min(v, (int)lane_xor_u32<8>((uint32_t)v));
+  const auto r16 = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+  v = min((int)r16[0], (int)r16[1]);
+  const auto r32 = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+  return min((int)r32[0], (int)r32[1]);
+}
+
+// The query elements of the heads this wave prepares (heads p, p + NW of
+// p = prep_head(wave)), one per lane; loaded first thing so that their latency
+// overlaps the rest of the prologue. Waves 0 and 1, which append the new
+// token, come last.
+template <int NW>
+__device__ __forceinline__ int prep_head(int wave) {
+  return wave >= 2 ? wave - 2 : wave + NW - 2;
+}
 template <int G, int NW>
 struct QueryIn {
   static constexpr int kHeadsPerWave = (G + NW - 1) / NW;
@@ -370,11 +398,12 @@ struct QueryIn {
 };
 template <int G, int NW>
 __device__ __forceinline__ QueryIn<G, NW> load_queries(const DecodeArgs& a, int kvh, int b) {
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const int lane = lane_id();
+  const int head = prep_head<NW>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
   QueryIn<G, NW> qin;
 #pragma unroll
   for (int i = 0; i < QueryIn<G, NW>::kHeadsPerWave; ++i) {
-    const int h = wave + NW * i;
+    const int h = head + NW * i;
     qin.v[i] = h < G ? a.q[((int64_t)b * a.Hq + a.q_of_kv[kvh * G + h]) * kDim + lane] : 0.0f;
   }
   return qin;
@@ -382,17 +411,17 @@ __device__ __forceinline__ QueryIn<G, NW> load_queries(const DecodeArgs& a, int 
 
 // Rotates (optionally) and quantises the G query vectors of one (batch, kv
 // head) and writes the operands and per-head score factors into LDS. Called by
-// all NW waves of the workgroup; wave w handles heads w, w + NW, whose
-// elements qin holds. taps: also write the q^ and Delta debug taps.
+// all NW waves of the workgroup, each for the heads whose elements qin holds. taps: also write the q^ and Delta debug taps.
 template <int MODE, int G, int K, int NW>
 __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, int b,
                                                 DecodeSmem<MODE, NW>& sm, bool taps,
                                                 const QueryIn<G, NW>& qin) {
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const int lane = lane_id();
+  const int head = prep_head<NW>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
   constexpr int kHeadsPerWave = QueryIn<G, NW>::kHeadsPerWave;
 #pragma unroll
   for (int i = 0; i < kHeadsPerWave; ++i) {
-    const int h = wave + NW * i;
+    const int h = head + NW * i;
     if (h >= G) break;
     const int64_t bq = (int64_t)b * a.Hq + a.q_of_kv[kvh * G + h];
     float qv = qin.v[i];
@@ -430,8 +459,8 @@ __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, in
 // 4: 168 of three) without spills. A wave has about 4 us per tile there and
 // can wait for a load; the four-wave kernels load all of them first.
 template <int MODE, int K>
-constexpr int kEarlyValueBlocks = MODE == kScorePot    ? (K == 0 || K == 3 ? 2 : K == 2 ? 0 : 1)
-                                  : MODE == kScoreDs4a ? (K >= 2 ? 1 : 2)
+constexpr int kEarlyValueBlocks = MODE == kScorePot    ? (K == 2 ? 0 : 1)
+                                  : MODE == kScoreDs4a ? (K >= 1 ? 0 : 1)
                                                        : 2;
 
 // NW: waves per workgroup, kWaves or kPoolWaves<MODE, K, VF> (the CU-wide
@@ -461,16 +490,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   const bool hvalid = hrow < G;
 
   const QueryIn<G, NW> qin = load_queries<G, NW>(a, kvh, b);
-  // The sequence's new token (fused append) is written before any of this
-  // workgroup's cache loads: only the workgroup whose range holds row T - 1
-  // reads that row.
-  if constexpr (MODE == kScorePot || MODE == kScoreDs4a) {
-    if (a.app_k != nullptr && split == a.n_splits - 1) {  // uniform per workgroup
-      append_token<K>(a, seq, wave);
-      wait_stores_in_l2();
-      __syncthreads();
-    }
-  }
+  // The sequence's new token (fused append) belongs to the workgroup whose
+  // range holds row T - 1.
+  const bool appends = (MODE == kScorePot || MODE == kScoreDs4a) && a.app_k != nullptr &&
+                       split == a.n_splits - 1;  // uniform per workgroup
   int gref = 0;
   float lsum = 0.0f;  // this lane's sum of the weights
 
@@ -510,39 +533,69 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   auto load_keys_tile = [&](int jt, KeyRegs<MODE, K>& kk) {
     load_keys<MODE, K>(st, t_begin + kWTile * jt, lane, kk);
   };
-  // Tiles: wave w starts with tiles w and w + NW; after that the default
-  // variant takes every NW-th tile and the CU-wide one claims the next
-  // unclaimed tile (from 2 NW on) one tile ahead of its use.
+  // Tiles: wave w starts with tiles w and w + NW; after that it takes every
+  // NW-th tile or, with claim_tiles, claims the next unclaimed tile (from 2 NW
+  // on) one tile ahead of its use.
   int j = wave;
   int jn = wave + NW;  // CU-wide variant: this wave's next tile
-  int jc = 0;          // CU-wide variant: the tile claimed during the current one
+  int jc = 0;          // CU-wide variant: the tile after that
   const int j_last = n_tiles - 1;
-  if (j < n_tiles) load_keys_tile(j, kr[0]);
+  // Besides its keys a tile needs its scales and values: requested once the
+  // previous tile's values are used, so that they arrive during the scores. (A
+  // second set of value registers, one tile further ahead, made the engines
+  // with short scores slower: PoT-4 decoded to weights 211 us against 200 at
+  // B = 64, T = 32768, 34.5 against 33.3 at B = 16, T = 16384.)
+  constexpr int kEarlyV = kPool ? kEarlyValueBlocks<MODE, K> : 2;
+  ValRegs<V8> vr;
+  uint4 ksc[2];
+  auto load_rest = [&](int jt) {
+    const int t0 = t_begin + kWTile * jt;
+    if constexpr (MODE != kScoreFp16) load_scales(st, t0, lane, ksc);
+    load_values_buf<V8, 0, kEarlyV>(st, t0, lane, vr);
+  };
+  auto load_first = [&]() {
+    load_keys_tile(j, kr[0]);
+    load_rest(j);
+  };
+  // A wave's first tile is requested at once, unless it holds the row that is
+  // being appended: then after the barrier below.
+  const bool late_first = appends && j == j_last;
+  if (j < n_tiles && !late_first) load_first();
   if constexpr (kPool) {
     if (tid == 0) sm.next = 2 * NW;
   }
 
-  // Query preparation into LDS while the first codes load;
-  // with INT8 values also the reference exponent g_ref = min g over this
+  // With INT8 values, the reference exponent g_ref = min g over this
   // workgroup's keys (Sec. II-E eq. av): weights are formed as p 2^(g_ref -
   // g_j) <= p, so they stay in fp16 range for any g, and the sums are scaled
-  // by 2^-g_ref at the end (fp32). One barrier then publishes both.
+  // by 2^-g_ref at the end (fp32). The appended token's g comes from its store.
+  int gmin = INT_MAX;
+  const int g_end = V8 && appends ? t_end - 1 : t_end;
+  uint2 g8 = make_uint2(0u, 0u);  // the first 8 exponents of this thread
+  if constexpr (V8) {
+    if (t_begin + 8 * tid < g_end) g8 = *reinterpret_cast<const uint2*>(eseq + t_begin + 8 * tid);
+  }
+  // The append and the query preparation while the first tiles load; one
+  // barrier publishes all of it.
+  if constexpr (MODE == kScorePot || MODE == kScoreDs4a) {
+    if (appends) gmin = append_token<K>(a, seq, wave);
+  }
   prepare_queries<MODE, G, K, NW>(a, kvh, b, sm, DEBUG && split == 0, qin);
   if constexpr (V8) {
-    int gmin = INT_MAX;
-    for (int t = t_begin + 8 * tid; t < t_end; t += 8 * kBlk) {
-      const uint2 w = *reinterpret_cast<const uint2*>(eseq + t);
+    for (int t = t_begin + 8 * tid; t < g_end; t += 8 * kBlk) {
+      const uint2 w = t < t_begin + 8 * kBlk ? g8 : *reinterpret_cast<const uint2*>(eseq + t);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int gi = (int)(int8_t)(((i < 4) ? w.x : w.y) >> (8 * (i & 3)));
-        gmin = (t + i < t_end) ? min(gmin, gi) : gmin;
+        gmin = (t + i < g_end) ? min(gmin, gi) : gmin;
       }
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) gmin = min(gmin, __shfl_xor(gmin, o, 64));
+    gmin = wave_min(gmin);
     if (lane == 0) sm.gm[wave] = gmin;
   }
+  if (appends && wave < 2) wait_stores_in_l2();
   __syncthreads();
+  if (j < n_tiles && late_first) load_first();
   if constexpr (V8) {
     gref = sm.gm[0];
 #pragma unroll
@@ -554,48 +607,36 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
       qop;
   if constexpr (MODE == kScorePot) qop = load_plane_query<G>(sm.qh, sm.ql, a.frac_bits);
   else if constexpr (MODE == kScoreInt8) qop = load_byte_query<G>(sm.qb);
-  else qop = load_half_query<G>(sm.qh);
+  else qop = load_half_query<G>(sm.qh, lane);
+  // CU-wide decoded weights with a mantissa: the 16 registers of the operand are
+  // read again from LDS in each tile, so that the values can have them meanwhile
+  constexpr bool kReloadQ = MODE == kScoreDs4a && K > 0 && kPool;
   // decoded weights: their sums to the int32 score at head-room F
   const float to_int = MODE == kScoreDs4a ? __builtin_amdgcn_ldexpf(1.0f, a.frac_bits + K) : 1.0f;
 
-  // The plane sums are long enough to cover the latency of value loads issued
-  // at the start of the tile; the other scores are not, so those engines
-  // prefetch the values of this wave's next tile as well.
-  constexpr bool kPrefetchV = !(MODE == kScorePot || (MODE == kScoreDs4a && K > 0));
-  ValRegs<V8> vr[kPrefetchV ? 2 : 1];
-  constexpr int kEarlyV = kPool ? kEarlyValueBlocks<MODE, K> : 2;
-  if constexpr (kPrefetchV) {
-    if (j < n_tiles) load_values_buf<V8>(st, t_begin + kWTile * j, lane, vr[0]);
-  }
-
-  // Stage 1 of a tile: issue the loads it still needs and those of this
-  // wave's next tile, score (the loads land meanwhile) and find the tile's
-  // integer maximum per head (returned in m_new).
+  // Stage 1 of a tile: request this wave's next keys, score (the loads land
+  // meanwhile) and find the tile's integer maximum per head (in m_new).
   float xv[8];
   int m_new = m_run;
-  auto stage1 = [&](const KeyRegs<MODE, K>& ks, KeyRegs<MODE, K>& knext, ValRegs<V8>& vs,
-                    ValRegs<V8>& vnext, int jt) {
+  bool first = true;
+  auto stage1 = [&](const KeyRegs<MODE, K>& ks, KeyRegs<MODE, K>& knext, int jt) {
     const int t0 = t_begin + kWTile * jt;
-    uint4 ksc[2];  // this tile's scales
-    if constexpr (MODE != kScoreFp16) load_scales(st, t0, lane, ksc);
     // the next tile's keys (past the range: the last tile again, unused)
     const int jl = min(kPool ? jn : jt + NW, j_last);
-    if constexpr (kPrefetchV) {
-      load_keys_tile(jl, knext);
-      load_values_buf<V8>(st, t_begin + kWTile * jl, lane, vnext);
-    } else {
-      load_values_buf<V8, 0, kEarlyV>(st, t0, lane, vs);
-      load_keys_tile(jl, knext);
-    }
+    load_keys_tile(jl, knext);
     if constexpr (kPool) {
       // claim the tile after jn now; it is needed one tile from now
-      int c = 0;
-      if (lane == 0) c = __hip_atomic_fetch_add(&sm.next, 1, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_WORKGROUP);
-      jc = __builtin_amdgcn_readfirstlane(c);
+      jc = jn + NW;
+      if (a.claim_tiles) {  // uniform
+        int c = 0;
+        if (lane == 0) c = __hip_atomic_fetch_add(&sm.next, 1, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+        jc = __builtin_amdgcn_readfirstlane(c);
+      }
     }
     // ---- 1. scores: keys t0 + 32 part + 8 grp ..+7 of head hrow ----
     {
+      if constexpr (kReloadQ) qop = load_half_query<G>(sm.qh, tile_offset(lane, t0));
       f32x4 d[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -605,6 +646,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
           if constexpr (K > 0) plane_bits<MODE, K>(ks, i, pl);
           if constexpr (MODE == kScorePot) d[i] = score_set<K>(w, pl, m22, qop);
           else d[i] = score_set_decoded<K>(w, pl, qop, to_int);
+          if constexpr (MODE == kScoreDs4a && K > 0 && kPool) asm volatile("" : "+v"(d[i]));
         } else if constexpr (MODE == kScoreInt8) {
           d[i] = score_set_int8(ks.k[i], qop);
         } else {
@@ -614,7 +656,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
       // keeps the matrix instructions above here (and so their operands' live
       // ranges short): the compiler would sink them to their first use
       asm volatile("" : "+v"(d[0]), "+v"(d[1]));
-      if constexpr (kEarlyV < 2) load_values_buf<V8, kEarlyV, 2>(st, t0, lane, vs);
+      if constexpr (kEarlyV < 2) load_values_buf<V8, kEarlyV, 2>(st, t0, lane, vr);
       // ---- 2. scores to the log2 domain ----
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -641,7 +683,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
       for (int i = 0; i < 8; ++i) xv[i] = (k0 + i < t_end) ? xv[i] : -INFINITY;
       // weights past the range are 0; fp16 value bytes there could be inf or
       // NaN and are cleared, INT8 value bytes are always finite numbers
-      if constexpr (!V8) mask_values(t0, t_end, lane, vs);
+      if constexpr (!V8) mask_values(t0, t_end, lane, vr);
     }
 
     // ---- 3. integer running maximum per head ----
@@ -671,6 +713,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   // element gets one exact power-of-two product. It runs outside the hot
   // loop below, so the accumulators stay in the matrix-core registers there.
   auto rescale = [&]() {
+    if (first) {  // nothing is summed yet
+      first = false;
+      m_run = m_new;
+      return;
+    }
     const float f = (m_run == INT_MIN) ? 0.0f : __builtin_amdgcn_ldexpf(1.0f, m_run - m_new);
     const int arow = lane & 15, acol = lane >> 4;
 #pragma unroll
@@ -687,7 +734,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   };
 
   // Stage 2 of a tile: weights from the scores and P.V on the matrix cores.
-  auto stage2 = [&](const ValRegs<V8>& vs) {
+  auto stage2 = [&]() {
     // ---- 4. weights (fp16 high / low parts) and P.V on the matrix cores ----
     // Each lane splits its 8 weights into hi = rtz(p) and lo = rtz(p - hi)
     // and hands lo to its partner lane (row ^ 8). Block kb = 0 then takes
@@ -722,7 +769,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
       lsum += p1;
       if constexpr (V8) {
         // the softmax sum takes p; A.V takes p 2^(g_ref - g) (exact scaling)
-        const uint32_t gw = (i < 2) ? vs.g.x : vs.g.y;
+        const uint32_t gw = (i < 2) ? vr.g.x : vr.g.y;
         p0 = __builtin_amdgcn_ldexpf(p0, gref - (int)(int8_t)(gw >> (16 * (i & 1))));
         p1 = __builtin_amdgcn_ldexpf(p1, gref - (int)(int8_t)(gw >> (16 * (i & 1) + 8)));
       }
@@ -743,8 +790,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     const half8 af0 = __builtin_bit_cast(half8, make_uint4(a0w[0], a0w[1], a0w[2], a0w[3]));
     const half8 af1 = __builtin_bit_cast(half8, make_uint4(a1w[0], a1w[1], a1w[2], a1w[3]));
     auto bfrag = [&](int kb, int nb) -> half8 {
-      if constexpr (V8) return int8_value_fragment(vs.f[kb][nb]);
-      else return __builtin_bit_cast(half8, vs.f[kb][nb]);
+      if constexpr (V8) return int8_value_fragment(vr.f[kb][nb]);
+      else return __builtin_bit_cast(half8, vr.f[kb][nb]);
     };
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb)
@@ -760,58 +807,70 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   // that every tile uses the same registers.
   auto advance = [&]() {
     kr[0] = kr[1];
-    if constexpr (kPrefetchV) vr[0] = vr[1];
     if constexpr (kPool) {
       j = jn;
       jn = jc;
     } else {
       j += NW;
     }
+    if (j < n_tiles) load_rest(j);
   };
 #pragma nounroll
   while (j < n_tiles) {
 #pragma nounroll
     for (;;) {
-      stage1(kr[0], kr[1], vr[0], vr[kPrefetchV ? 1 : 0], j);
+      stage1(kr[0], kr[1], j);
       if (__any(m_new != m_run)) break;
-      stage2(vr[0]);
+      stage2();
       advance();
       if (j >= n_tiles) break;
     }
     if (j >= n_tiles) break;
     rescale();
-    stage2(vr[0]);
+    stage2();
     advance();
   }
 
-  // ---- merge the four waves ---------------------------------------------------
+  // ---- merge the waves ------------------------------------------------------
+  // sum of the weights over the 8 lanes that formed a head's
+  lsum += dpp_move<kDppRowRor8>(lsum);
+  {
+    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(lsum), __float_as_uint(lsum),
+                                                      false, false);
+    lsum = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
+    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum),
+                                                      false, false);
+    lsum = __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+  }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) sm.wo[wave][4 * grp + r][16 * nb + row] = acc[nb][r];
   }
-  if (lane < 8) sm.wm[wave][lane] = m_run;
-  sm.wp[wave][lane] = lsum;
+  if (lane < 8) {
+    sm.wm[wave][lane] = m_run;
+    sm.wl[wave][lane] = lsum;
+  }
   __syncthreads();
 
   const int Sn = a.n_splits;
   for (int idx = tid; idx < G * kDim; idx += kBlk) {
     const int h = idx / kDim, d = idx % kDim;
     const int64_t bq = (int64_t)b * a.Hq + a.q_of_kv[kvh * G + h];
-    int M = INT_MIN;
+    // branch-free, so that the LDS reads of all waves are in flight together;
+    // a wave without tiles has zero sums and takes part with factor 0
+    int m[NW], M = INT_MIN;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = max(M, sm.wm[w][h]);
+    for (int w = 0; w < NW; ++w) {
+      m[w] = sm.wm[w][h];
+      M = max(M, m[w]);
+    }
     float o = 0.0f, l = 0.0f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      if (sm.wm[w][h] == INT_MIN) continue;
-      const float f = __builtin_amdgcn_ldexpf(1.0f, sm.wm[w][h] - M);
-      // the 8 lanes that formed head h's weights
-      float lw = 0.0f;
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) lw += sm.wp[w][16 * gq + h] + sm.wp[w][16 * gq + h + 8];
+      const float f = m[w] == INT_MIN ? 0.0f : __builtin_amdgcn_ldexpf(1.0f, m[w] - M);
       o = fmaf(f, sm.wo[w][h][d] + sm.wo[w][h + 8][d], o);
-      l = fmaf(f, lw, l);
+      l = fmaf(f, sm.wl[w][h], l);
     }
     if constexpr (V8) o = __builtin_amdgcn_ldexpf(o, -gref);
     if (Sn == 1) {
@@ -949,28 +1008,6 @@ static hipError_t launch_t(const DecodeArgs& a, hipStream_t stream, hipEvent_t e
   }
 }
 
-template <int MODE, int G, int K, int VF>
-static int occupancy_t(bool pool) {
-  constexpr int PW = kPoolWaves<MODE, K, VF>;
-  int n = 0;
-  hipError_t e;
-  if constexpr (PW > 0) {
-    if (pool)
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &n, reinterpret_cast<const void*>(&decode_kernel<MODE, G, K, false, VF, PW>), 64 * PW,
-          0);
-    else
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &n, reinterpret_cast<const void*>(&decode_kernel<MODE, G, K, false, VF, kWaves>), kBlock,
-          0);
-  } else {
-    if (pool) return 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &n, reinterpret_cast<const void*>(&decode_kernel<MODE, G, K, false, VF, kWaves>), kBlock, 0);
-  }
-  return e == hipSuccess ? n : 0;
-}
-
 template <int MODE, int G, bool DEBUG, int VF>
 static hipError_t launch_k(int mant_bits, const DecodeArgs& a, hipStream_t stream, hipEvent_t e0,
                            hipEvent_t e1) {
@@ -1011,30 +1048,6 @@ hipError_t launch_mode_vf(int G, int mant_bits, bool debug, const DecodeArgs& a,
   else
     return debug ? launch_g<MODE, true, VF>(G, mant_bits, a, stream, e0, e1)
                  : launch_g<MODE, false, VF>(G, mant_bits, a, stream, e0, e1);
-}
-
-template <int MODE, int VF>
-int occupancy_mode_vf(int G, int mant_bits, bool pool) {
-  auto by_k = [&](auto g_tag) -> int {
-    constexpr int GG = decltype(g_tag)::value;
-    if constexpr (MODE == kScorePot || (MODE == kScoreDs4a && VF == 0)) {
-      switch (mant_bits) {
-        case 0: return occupancy_t<MODE, GG, 0, VF>(pool);
-        case 1: return occupancy_t<MODE, GG, 1, VF>(pool);
-        case 2: return occupancy_t<MODE, GG, 2, VF>(pool);
-        case 3: return occupancy_t<MODE, GG, 3, VF>(pool);
-        default: return occupancy_t<MODE, GG, 4, VF>(pool);
-      }
-    } else {
-      return occupancy_t<MODE, GG, 0, VF>(pool);
-    }
-  };
-  switch (G) {
-    case 1: return by_k(std::integral_constant<int, 1>{});
-    case 2: return by_k(std::integral_constant<int, 2>{});
-    case 4: return by_k(std::integral_constant<int, 4>{});
-    default: return by_k(std::integral_constant<int, 8>{});
-  }
 }
 
 }  // namespace potattn

@@ -219,13 +219,8 @@ __device__ __forceinline__ void store_value_token_wave(const uint16_t* __restric
   v_seq[(t / 8) * 8 * kDim + lane * 8 + t % 8] = v_row[lane];
 }
 
-// INT8 values with a power-of-two per-token scale (Sec. II-E) for one token,
-// quantised and stored by the calling wave (lane = dim): g is the largest
-// integer with max|v| 2^g <= 127 (0 for an all-zero row) and v^ = rne(v 2^g),
-// so |v^| <= 127. The byte cache holds v^ + 128 (offset binary) at the
-// token-interleaved position ((t/8)*8) * 64 + d * 8 + t % 8 of the sequence,
-// and exp_seq[t] = g; the value is v^ 2^-g.
-// The exponent g of a token whose largest magnitude is amax.
+// The exponent g of a token whose largest magnitude is amax: the largest
+// integer with amax 2^g <= 127, 0 for amax = 0.
 __device__ __forceinline__ int value_exponent(float amax) {
   if (!(amax > 0.0f)) return 0;
   // amax in [2^e, 2^(e+1)) with e = frexp exponent - 1, so amax 2^(6-e) is
@@ -237,7 +232,14 @@ __device__ __forceinline__ int value_exponent(float amax) {
 __device__ __forceinline__ uint8_t value_byte(float v, int g) {
   return (uint8_t)((int)rintf(__builtin_amdgcn_ldexpf(v, g)) + 128);
 }
-__device__ __forceinline__ void store_value_token_i8_wave(const uint16_t* __restrict__ v_row,
+// INT8 values with a power-of-two per-token scale (Sec. II-E) for one token,
+// quantised and stored by the calling wave (lane = dim): g is the largest
+// integer with max|v| 2^g <= 127 (0 for an all-zero row) and v^ = rne(v 2^g),
+// so |v^| <= 127. The byte cache holds v^ + 128 (offset binary) at the
+// token-interleaved position ((t/8)*8) * 64 + d * 8 + t % 8 of the sequence,
+// and exp_seq[t] = g; the value is v^ 2^-g.
+// Returns g.
+__device__ __forceinline__ int store_value_token_i8_wave(const uint16_t* __restrict__ v_row,
                                                           uint8_t* __restrict__ v_seq,
                                                           int8_t* __restrict__ exp_seq,
                                                           int64_t t) {
@@ -246,6 +248,7 @@ __device__ __forceinline__ void store_value_token_i8_wave(const uint16_t* __rest
   const int g = value_exponent(wave_max(fabsf(v)));
   v_seq[(t / 8) * 8 * kDim + lane * 8 + t % 8] = value_byte(v, g);
   if (lane == 0) exp_seq[t] = (int8_t)g;
+  return g;
 }
 
 }  // namespace potattn

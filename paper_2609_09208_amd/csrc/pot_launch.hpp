@@ -92,6 +92,7 @@ struct DecodeArgs {
   int32_t B, Hq, Hkv, T;
   int32_t n_splits, split_len;
   int32_t frac_bits, hadamard;
+  int32_t claim_tiles;         // CU-wide workgroups: tiles from a counter, else in fixed order
   int32_t wg_waves;            // waves per decode workgroup: 4, or pool_waves(...)
   int32_t q_of_kv[kMaxHqArg];  // [Hkv][G] query heads served by each kv head
 };
@@ -121,11 +122,6 @@ constexpr int kMaxKeys = (1 << 24) - 8;
 // and allocate by are part of the interface, so this part of them stays.
 constexpr int query_words(int G) { return (33 * G + 63) / 64 * 64; }
 
-// Resident workgroups per CU of the (non-debug) decode kernel for this
-// variant (pool: its CU-wide variant), from the HIP occupancy calculator; 0 if
-// the query fails.
-int decode_occupancy(int mode, int G, int mant_bits, int vf, bool pool);
-
 // vf: value format. 0: fp16 value cache (a.v); 1: INT8 value cache (a.v8,
 // a.v_exp); 2: INT8 values with the power-of-two weights of eq. logsm.
 // Formats 1 and 2 exist for the score modes kScorePot and kScoreDs4a only.
@@ -135,12 +131,10 @@ hipError_t launch_decode(int mode, int G, int mant_bits, bool debug, int vf,
                          const DecodeArgs& a, hipStream_t stream, hipEvent_t ev_begin = nullptr,
                          hipEvent_t ev_end = nullptr);
 
-// The launch and occupancy query of one score mode and value format; each
+// The launch of one score mode and value format; each
 // mode's kernels are instantiated in a translation unit of their own.
 template <int MODE, int VF>
 hipError_t launch_mode_vf(int G, int mant_bits, bool debug, const DecodeArgs& a,
                           hipStream_t stream, hipEvent_t e0, hipEvent_t e1);
-template <int MODE, int VF>
-int occupancy_mode_vf(int G, int mant_bits, bool pool);
 
 }  // namespace potattn

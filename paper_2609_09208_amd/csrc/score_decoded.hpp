@@ -69,8 +69,8 @@ __device__ __forceinline__ bool query_block_used(int lane, int G) {
 }
 
 template <int G>
-__device__ __forceinline__ HalfQuery load_half_query(const _Float16 (*q)[kDim]) {
-  const int lane = lane_id(), h = lane & 7;
+__device__ __forceinline__ HalfQuery load_half_query(const _Float16 (*q)[kDim], int lane) {
+  const int h = lane & 7;
   const bool used = query_block_used(lane, G);
   const uint4* p = reinterpret_cast<const uint4*>(&q[h < G ? h : 0][32 * ((lane >> 4) & 1)]);
   HalfQuery r;
@@ -114,6 +114,7 @@ __device__ __forceinline__ f32x4 score_set_decoded(const uint32_t (&w)[4], const
       j |= x & (0x11111111u << b);
     }
     d = __builtin_amdgcn_mfma_f32_16x16x32_f16(decode_weights<K>(c4[c], j), q.h[c], d, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);  // one operand at a time: registers
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) d[r] = __fmul_rn(d[r], to_int);
