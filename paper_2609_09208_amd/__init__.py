@@ -15,6 +15,9 @@ from __future__ import annotations
 import ctypes
 import os
 
+import numpy as np
+import torch  # its HIP runtime has to be loaded before the library (see _load_library)
+
 HEAD_DIM = 64
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libpotattn.so")
 
@@ -52,11 +55,10 @@ def make_format(mant_bits: int = 0, frac_bits: int = 7, hadamard: bool = False,
 
 
 def _load_library():
-    # torch ships its own HIP runtime with the same soname as ROCm's; load it
-    # first so that this library binds to the one runtime torch uses for the
-    # device memory and streams it hands over (two runtimes in one process do
+    # torch ships its own HIP runtime with the same soname as ROCm's; it is
+    # loaded first so that this library binds to the one runtime torch uses for
+    # the device memory and streams it hands over (two runtimes in one process do
     # not share devices).
-    import torch  # noqa: F401
     if not os.path.exists(_LIB_PATH):
         raise ImportError(
             f"{_LIB_PATH} is not built; run __graft_entry__.build() (hipcc, gfx950)")
@@ -123,19 +125,29 @@ def _ptr(t) -> int | None:
     return t.data_ptr()
 
 
+# The current stream of the current device as an address, without the checks
+# and the Stream object of torch.cuda.current_stream() (3.6 us a call with
+# torch.cuda.is_available() before it, as long as a kernel launch). None where
+# this torch has no such call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int | None:
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
-    import torch
+    if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+        return _raw_stream(_raw_device())
     if not torch.cuda.is_available():
         return None
     return torch.cuda.current_stream().cuda_stream
 
 
 def _heads(kv_head_of_q):
-    import numpy as np
-    arr = np.ascontiguousarray(kv_head_of_q, dtype=np.int32)
-    return arr, arr.ctypes.data_as(ctypes.c_void_p)
+    if not (type(kv_head_of_q) is np.ndarray and kv_head_of_q.dtype == np.int32
+            and kv_head_of_q.flags.c_contiguous):
+        kv_head_of_q = np.ascontiguousarray(kv_head_of_q, dtype=np.int32)
+    return kv_head_of_q, kv_head_of_q.ctypes.data
 
 
 # ---- C ABI mirrors ---------------------------------------------------------
@@ -322,7 +334,6 @@ def alloc_pot_cache(B: int, Hkv: int, t_cap: int, mant_bits: int, device):
 
     Returns dict(codes_se uint8 [B,Hkv,t_cap,32], codes_m uint8
     [B,Hkv,t_cap,8k] or None, key_scale fp32 [B,Hkv,t_cap])."""
-    import torch
     se = torch.zeros((B, Hkv, t_cap, HEAD_DIM // 2), dtype=torch.uint8, device=device)
     cm = (torch.zeros((B, Hkv, t_cap, 8 * mant_bits), dtype=torch.uint8, device=device)
           if mant_bits else None)
@@ -332,14 +343,12 @@ def alloc_pot_cache(B: int, Hkv: int, t_cap: int, mant_bits: int, device):
 
 def alloc_value_cache(B: int, Hkv: int, t_cap: int, device):
     """Value cache of B*Hkv sequences of t_cap tokens (token-interleaved)."""
-    import torch
     return torch.zeros((B, Hkv, t_cap, HEAD_DIM), dtype=torch.float16, device=device)
 
 
 def alloc_value_cache_int8(B: int, Hkv: int, t_cap: int, device):
     """INT8 value cache: (value bytes uint8 [B,Hkv,t_cap,64] token-interleaved,
     exponents int8 [B,Hkv,t_cap])."""
-    import torch
     return (torch.zeros((B, Hkv, t_cap, HEAD_DIM), dtype=torch.uint8, device=device),
             torch.zeros((B, Hkv, t_cap), dtype=torch.int8, device=device))
 
@@ -347,5 +356,4 @@ def alloc_value_cache_int8(B: int, Hkv: int, t_cap: int, device):
 def alloc_workspace(nbytes: int, device):
     """Workspace buffer for the decode calls (zero-filled; the kernels write
     every word they read, so any contents would do)."""
-    import torch
     return torch.zeros(max(int(nbytes), 256), dtype=torch.uint8, device=device)

@@ -10,7 +10,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <string>
-#include <vector>
 
 #include "pot_attn.h"
 #include "pot_device.hpp"
@@ -193,14 +192,15 @@ pot_status check_heads(const int32_t* map, int Hq, int Hkv, DecodeArgs* a, int* 
   const int G = Hq / Hkv;
   if (G != 1 && G != 2 && G != 4 && G != 8)
     return fail(POT_ERR_UNSUPPORTED, "group size %d (1, 2, 4 or 8)", G);
-  std::vector<int> fill(Hkv, 0);
+  int fill[kMaxHqArg] = {};
   for (int i = 0; i < Hq; ++i) {
     const int h = map[i];
     if (h < 0 || h >= Hkv)
       return fail(POT_ERR_INVALID_ARG, "kv_head_of_q[%d] = %d outside [0, %d)", i, h, Hkv);
     if (fill[h] >= G)
       return fail(POT_ERR_UNSUPPORTED, "kv head %d serves more than %d query heads", h, G);
-    a->q_of_kv[h * G + fill[h]++] = i;
+    const int at = h * G + fill[h]++;
+    a->q_of_kv[at >> 2] |= (uint32_t)i << (8 * (at & 3));
   }
   *G_out = G;
   return POT_OK;
@@ -372,7 +372,7 @@ pot_status pot_encode_keys(const pot_format* fmt, const uint16_t* k_fp16, int64_
       (codes_m && !aligned(codes_m, 8)))
     return fail(POT_ERR_INVALID_ARG, "misaligned k_fp16 / codes_se / key_scale / codes_m");
   if (n_rows > (int64_t)1 << 36) return fail(POT_ERR_INVALID_ARG, "n_rows too large");
-  const EncodeTables tab = make_encode_tables(fmt->mant_bits);
+  const EncodeTables& tab = encode_tables(fmt->mant_bits);
   return hip_status(launch_encode_pot(k_fp16, n_rows, out_row_stride, scale_mode, fmt->hadamard,
                                       key_scale, codes_se, codes_m, tab,
                                       static_cast<hipStream_t>(stream)),
@@ -499,7 +499,7 @@ pot_status pot_append_decode_attention(const pot_format* fmt, const float* q,
   a.app_codes_m = codes_m;
   a.app_key_scale = key_scale;
   a.app_v_cache = v_cache;
-  a.app_tab = make_encode_tables(fmt->mant_bits);
+  a.app_tab = encode_tables(fmt->mant_bits);
   return decode_common(kScorePot, fmt->mant_bits, a, kv_head_of_q, B, Hq, Hkv, T, t_cap,
                        workspace, ws_bytes, dbg, stream);
 }
@@ -565,7 +565,7 @@ pot_status pot_append_decode_attention_v8(const pot_format* fmt, int32_t engine,
   a.app_key_scale = key_scale;
   a.app_v8 = v_u8;
   a.app_v_exp = v_exp;
-  a.app_tab = make_encode_tables(fmt->mant_bits);
+  a.app_tab = encode_tables(fmt->mant_bits);
   return decode_common(engine == 0 ? kScorePot : kScoreDs4a, fmt->mant_bits, a, kv_head_of_q, B,
                        Hq, Hkv, T, t_cap, workspace, ws_bytes, dbg, stream, 1);
 }

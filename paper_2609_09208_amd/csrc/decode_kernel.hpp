@@ -404,7 +404,7 @@ __device__ __forceinline__ QueryIn<G, NW> load_queries(const DecodeArgs& a, int 
 #pragma unroll
   for (int i = 0; i < QueryIn<G, NW>::kHeadsPerWave; ++i) {
     const int h = head + NW * i;
-    qin.v[i] = h < G ? a.q[((int64_t)b * a.Hq + a.q_of_kv[kvh * G + h]) * kDim + lane] : 0.0f;
+    qin.v[i] = h < G ? a.q[((int64_t)b * a.Hq + a.q_head(kvh * G + h)) * kDim + lane] : 0.0f;
   }
   return qin;
 }
@@ -423,7 +423,7 @@ __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, in
   for (int i = 0; i < kHeadsPerWave; ++i) {
     const int h = head + NW * i;
     if (h >= G) break;
-    const int64_t bq = (int64_t)b * a.Hq + a.q_of_kv[kvh * G + h];
+    const int64_t bq = (int64_t)b * a.Hq + a.q_head(kvh * G + h);
     float qv = qin.v[i];
     if constexpr (MODE == kScoreFp16) {
       sm.qh[h][lane] = (_Float16)qv;
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
           if constexpr (DEBUG) {
             const int key = t0 + 32 * part + 8 * grp + 4 * i + r;
             if (a.dbg_scores && hvalid && key < t_end)
-              a.dbg_scores[((int64_t)b * a.Hq + a.q_of_kv[kvh * G + hrow]) * a.T + key] =
+              a.dbg_scores[((int64_t)b * a.Hq + a.q_head(kvh * G + hrow)) * a.T + key] =
                   (int32_t)d[i][r];
           }
         }
@@ -855,8 +855,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
 
   const int Sn = a.n_splits;
   for (int idx = tid; idx < G * kDim; idx += kBlk) {
-    const int h = idx / kDim, d = idx % kDim;
-    const int64_t bq = (int64_t)b * a.Hq + a.q_of_kv[kvh * G + h];
+    const int h = __builtin_amdgcn_readfirstlane(idx / kDim), d = idx % kDim;
+    const int64_t bq = (int64_t)b * a.Hq + a.q_head(kvh * G + h);
     // branch-free, so that the LDS reads of all waves are in flight together;
     // a wave without tiles has zero sums and takes part with factor 0
     int m[NW], M = INT_MIN;

@@ -42,8 +42,6 @@ float rd_sqrt_ratio(uint64_t num, uint64_t den) {
   return std::ldexp((float)m, -23);  // m < 2^25 so exact in fp32
 }
 
-}  // namespace
-
 EncodeTables make_encode_tables(int mant_bits) {
   EncodeTables t{};
   const uint64_t n = 1ull << mant_bits;
@@ -53,6 +51,15 @@ EncodeTables make_encode_tables(int mant_bits) {
   t.zero_cut = std::ldexp(rd_sqrt_ratio(2, 1), -(kExpMax + 1));
   t.mant_bits = mant_bits;
   return t;
+}
+
+}  // namespace
+
+const EncodeTables& encode_tables(int mant_bits) {
+  static const EncodeTables all[5] = {make_encode_tables(0), make_encode_tables(1),
+                                      make_encode_tables(2), make_encode_tables(3),
+                                      make_encode_tables(4)};
+  return all[mant_bits];
 }
 
 // The row-per-wave kernels below step over rows with the grid's stride: a

@@ -9,7 +9,7 @@
 
 namespace potattn {
 
-constexpr int kMaxHqArg = 128;  // query heads addressable through kernel args
+constexpr int kMaxHqArg = 128;  // query heads addressable through kernel args (a byte each)
 
 // Encoder tables passed by value as kernel arguments (no device globals).
 struct EncodeTables {
@@ -22,8 +22,8 @@ struct EncodeTables {
   int32_t mant_bits;
 };
 
-// Computes EncodeTables for mantissa width k with exact integer square roots.
-EncodeTables make_encode_tables(int mant_bits);
+// EncodeTables for mantissa width k (0..4), from exact integer square roots.
+const EncodeTables& encode_tables(int mant_bits);
 
 hipError_t launch_encode_pot(const uint16_t* k, int64_t n_rows, int64_t out_stride,
                              int scale_mode, int hadamard, float* key_scale,
@@ -94,7 +94,10 @@ struct DecodeArgs {
   int32_t frac_bits, hadamard;
   int32_t claim_tiles;         // CU-wide workgroups: tiles from a counter, else in fixed order
   int32_t wg_waves;            // waves per decode workgroup: 4, or pool_waves(...)
-  int32_t q_of_kv[kMaxHqArg];  // [Hkv][G] query heads served by each kv head
+  uint32_t q_of_kv[kMaxHqArg / 4];  // [Hkv][G] query heads served by each kv head, a byte each
+
+  // Query head g of a group in [Hkv][G] order (kvh * G + g).
+  __host__ __device__ int q_head(int i) const { return (q_of_kv[i >> 2] >> (8 * (i & 3))) & 0xFF; }
 };
 
 // Waves per workgroup of a decode kernel's CU-wide variant, 0 if it has
