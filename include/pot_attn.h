@@ -245,8 +245,8 @@ pot_status pot_workspace_init(void* workspace, size_t ws_bytes, void* stream);
  * the fp16 values with fp32 accumulation (matrix cores, weights split into
  * fp16 high and low parts); key splits (chosen to give every CU at most one
  * workgroup) are merged with exact 2^(M_s - M) factors.
- * Launches: the split decode kernel (which prepares the queries) and, with
- * more than one split, a combine kernel, both on `stream`.
+ * Launches: the split decode kernel (which prepares the queries and merges up
+ * to 32 splits) and, with more splits, a combine kernel, both on `stream`.
  */
 pot_status pot_decode_attention(const pot_format* fmt, const float* q,
                                 const uint8_t* codes_se,

@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cstdarg>
 #include <cstdio>
 #include <string>
@@ -170,7 +171,8 @@ struct WsLayout {
   size_t part_m, part_l, part_o, total;
 };
 
-// Workspace: query_words per decode workgroup (unused), then the split partials.
+// Workspace: query_words per decode workgroup (the tickets are in them), then the
+// split partials.
 WsLayout ws_layout(long B, long Hq, long Hkv, long S) {
   WsLayout w;
   w.part_m = align_up((size_t)(B * Hkv * S) * query_words((int)(Hq / Hkv)) * 4, 256);
@@ -178,6 +180,18 @@ WsLayout ws_layout(long B, long Hq, long Hkv, long S) {
   w.part_o = w.part_l + align_up((size_t)(B * Hq * S) * 4, 256);
   w.total = w.part_o + align_up((size_t)(B * Hq * S) * 64 * 4, 256);
   return w;
+}
+
+// A tag that a workspace does not hold by chance: 52 bits, never 0, another one
+// for each call.
+unsigned long long next_ticket() {
+  static std::atomic<unsigned long long> n{
+      (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count()};
+  unsigned long long z = n.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;  // splitmix64
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  z = (z ^ (z >> 31)) >> 12;
+  return z != 0 ? z : 1;
 }
 
 bool shape_ok(int B, int Hq, int Hkv, int T) {
@@ -262,6 +276,8 @@ pot_status decode_common(int mode, int mant_bits, DecodeArgs& a, const int32_t* 
     return fail(POT_ERR_WORKSPACE, "workspace %zu bytes < %zu needed for %d splits", ws_bytes,
                 w.total, p.n_splits);
   uint8_t* ws = static_cast<uint8_t*>(workspace);
+  a.tickets = reinterpret_cast<unsigned long long*>(ws);
+  a.ticket = pool && p.n_splits > 1 && p.n_splits <= kMaxMergedSplits ? next_ticket() : 0;
   a.part_m = reinterpret_cast<int32_t*>(ws + w.part_m);
   a.part_l = reinterpret_cast<float*>(ws + w.part_l);
   a.part_o = reinterpret_cast<float*>(ws + w.part_o);

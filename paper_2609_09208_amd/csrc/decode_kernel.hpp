@@ -34,10 +34,8 @@
 //     lane in fp32. The value cache is stored token-interleaved
 //     ([t/8][d][t%8]) so a lane's 16-byte load is exactly its B fragment.
 // With one split the workgroup writes O directly; otherwise it writes its
-// (M_s, l_s, o_s) and a small combine kernel merges the splits with exact
-// 2^(M_s - M) weights. (A last-workgroup merge inside this kernel would need
-// an agent-scope release/acquire per workgroup, which on a multi-XCD part
-// writes back and invalidates the XCD's L2 each time and serialises.)
+// (M_s, l_s, o_s), and the last workgroup of a unit, or for many splits a small
+// combine kernel, merges the splits with exact 2^(M_s - M) weights.
 // (Kernel templates; the instantiations live in decode_pot*.hip,
 // decode_dot.hip and decode_cmp.hip, one translation unit per score mode and
 // value format.)
@@ -328,11 +326,12 @@ __device__ __forceinline__ void mask_values(int t0, int t_end, int lane, ValRegs
 // ---- shared memory of the decode kernel -------------------------------------
 template <int NW>
 struct alignas(16) MergeSmem {
-  alignas(16) float wo[NW][16][kDim];  // per-wave P.V (rows: heads x {hi, lo})
+  alignas(16) float wo[NW][8][kDim];  // per-wave P.V
   float wl[NW][8];   // sums of the weights per head
   int wm[NW][8];
   int gm[NW];        // INT8 values: per-wave minimum exponent
   int next;          // CU-wide variant: the next unclaimed tile of the range
+  int last;          // this workgroup merges its unit's splits
 };
 template <int MODE, int NW>
 struct DecodeSmem : MergeSmem<NW> {
@@ -451,6 +450,104 @@ __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, in
   }
 }
 
+// ---- merge of the key splits by the last workgroup of a unit ------------------
+// A unit is one (batch, kv head) sequence. Its workgroups write their partials
+// (M_s, l_s, o_s) and count themselves on the unit's ticket word in the
+// workspace; the one that counts last merges, which saves the merge kernel's
+// launch. Everything that passes between workgroups goes by agent-scope
+// accesses (relaxed atomics: written through and read from beyond the XCD's
+// own L2), and a wave waits until its stores have arrived before the barrier in
+// front of the count. No fence: an agent-scope release or acquire fence writes
+// back or invalidates the whole L2 of the XCD, per workgroup (that took B = 64
+// from 258 to 541 us). Nothing ever waits for another workgroup.
+//
+// The workspace may hold anything before a call. The ticket word is the
+// call's tag (52 bits, never 0) and the count (12 bits); every workgroup first
+// puts {tag, 0} there unless the tag is there already (one compare-and-swap
+// against what it read: it can only fail because another workgroup of the call
+// put the tag there), and the last one clears the word, so that a replay of a
+// captured call, which has the same tag, starts over.
+constexpr int kTicketCountBits = 12;
+constexpr int kTicketStride = 32;  // 64-bit words between tickets: a 256-byte line pair each
+
+template <typename T>
+__device__ __forceinline__ void store_agent(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T load_agent(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ int wave_max_i32(int v) { return ~wave_min(~v); }
+// Sum over the wave.
+__device__ __forceinline__ float wave_sum(float v) {
+  v += __uint_as_float(lane_xor_u32<1>(__float_as_uint(v)));
+  v += __uint_as_float(lane_xor_u32<2>(__float_as_uint(v)));
+  v += __uint_as_float(lane_xor_u32<4>(__float_as_uint(v)));
+  v += __uint_as_float(lane_xor_u32<8>(__float_as_uint(v)));
+  const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false,
+                                                    false);
+  v = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
+  const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false,
+                                                    false);
+  return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+}
+
+// One head's merge by one wave: lane s holds split s's M_s and l_s, and every
+// lane its dimension of all splits' sums, N >= Sn of them requested together
+// (loads in a loop or behind branches wait for each other: 0.6 us a turn).
+// Splits past the last read the last one and get factor 0.
+template <int N, bool DEBUG>
+__device__ __forceinline__ void merge_head(const DecodeArgs& a, int64_t bq, int lane) {
+  const int Sn = a.n_splits, s_l = min(lane, Sn - 1);
+  const int m_l = load_agent(a.part_m + bq * Sn + s_l);
+  const float l_l = load_agent(a.part_l + bq * Sn + s_l);
+  const float* po = a.part_o + bq * Sn * kDim + lane;
+  float v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = load_agent(po + min(i, Sn - 1) * kDim);
+  const int M = wave_max_i32(m_l);
+  const float f_l = lane < Sn && m_l != INT_MIN ? __builtin_amdgcn_ldexpf(1.0f, m_l - M) : 0.0f;
+  const float l = wave_sum(f_l * l_l);
+  float o = 0.0f;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    o = fmaf(__uint_as_float(
+                 (uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(f_l), i)),
+             v[i], o);
+  a.out[bq * kDim + lane] = o / l;
+  if constexpr (DEBUG) {
+    if (lane == 0 && a.dbg_m_final) a.dbg_m_final[bq] = M;
+  }
+}
+
+template <int G, bool DEBUG, int NW, typename Smem>
+__device__ __forceinline__ void merge_splits(const DecodeArgs& a, int64_t seq, int kvh, int b,
+                                             Smem& sm) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int Sn = a.n_splits;
+  unsigned long long* ticket = a.tickets + seq * kTicketStride;
+  wait_stores_in_l2();  // this wave's partials (and ticket) have arrived
+  __syncthreads();
+  if (tid == 0) {
+    const unsigned long long old =
+        __hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sm.last = (int)(old & ((1u << kTicketCountBits) - 1)) == Sn - 1;
+  }
+  __syncthreads();
+  if (!sm.last) return;
+  if (tid == 0) store_agent(ticket, 0ull);
+  for (int h = wave; h < G; h += NW) {
+    const int64_t bq = (int64_t)b * a.Hq + a.q_head(kvh * G + h);
+    if (Sn <= 4) merge_head<4, DEBUG>(a, bq, lane);
+    else if (Sn <= 8) merge_head<8, DEBUG>(a, bq, lane);
+    else if (Sn <= 16) merge_head<16, DEBUG>(a, bq, lane);
+    else merge_head<kMaxMergedSplits, DEBUG>(a, bq, lane);
+  }
+}
+
 // VF: value format, 0 fp16 values, 1 INT8 values, 2 INT8 values with the
 // power-of-two weights of eq. logsm.
 // CU-wide kernels: value blocks (of two, 16 registers each) loaded before the
@@ -489,6 +586,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   const int row = lane & 15, grp = lane >> 4, hrow = row & 7, part = row >> 3;
   const bool hvalid = hrow < G;
 
+  // the ticket of this unit (merge_splits): read now, set below
+  const bool tickets = kPool && a.ticket != 0 && wave == NW - 1;  // uniform per wave
+  unsigned long long* ticket = a.tickets + seq * kTicketStride;
+  unsigned long long seen = 0;
+  if (tickets) seen = load_agent(ticket);
   const QueryIn<G, NW> qin = load_queries<G, NW>(a, kvh, b);
   // The sequence's new token (fused append) belongs to the workgroup whose
   // range holds row T - 1.
@@ -593,6 +695,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     gmin = wave_min(gmin);
     if (lane == 0) sm.gm[wave] = gmin;
   }
+  if (tickets && lane == 0 && (seen >> kTicketCountBits) != a.ticket)
+    __hip_atomic_compare_exchange_strong(ticket, &seen, a.ticket << kTicketCountBits,
+                                         __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
   if (appends && wave < 2) wait_stores_in_l2();
   __syncthreads();
   if (j < n_tiles && late_first) load_first();
@@ -842,14 +948,25 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
                                                       false, false);
     lsum = __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
   }
+  // Only waves that had a tile take part, in whole groups of four (a wave of
+  // such a group without tiles has zero sums and factor 0). Rows h and h + 8 of
+  // the products (weights' high and low parts) sit in the two halves of the
+  // wave and are added on the way to LDS.
+  const int n_act = kPool ? min(NW, (n_tiles + 3) & ~3) : NW;
+  if (wave < n_act) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+    for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) sm.wo[wave][4 * grp + r][16 * nb + row] = acc[nb][r];
-  }
-  if (lane < 8) {
-    sm.wm[wave][lane] = m_run;
-    sm.wl[wave][lane] = lsum;
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t v = __float_as_uint(acc[nb][r]);
+        const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        const float sum = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+        if (lane < 32) sm.wo[wave][4 * grp + r][16 * nb + row] = sum;
+      }
+    if (lane < 8) {
+      sm.wm[wave][lane] = m_run;
+      sm.wl[wave][lane] = lsum;
+    }
   }
   __syncthreads();
 
@@ -857,20 +974,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   for (int idx = tid; idx < G * kDim; idx += kBlk) {
     const int h = __builtin_amdgcn_readfirstlane(idx / kDim), d = idx % kDim;
     const int64_t bq = (int64_t)b * a.Hq + a.q_head(kvh * G + h);
-    // branch-free, so that the LDS reads of all waves are in flight together;
-    // a wave without tiles has zero sums and takes part with factor 0
-    int m[NW], M = INT_MIN;
+    int M = INT_MIN;
+    for (int w = 0; w < n_act; w += 4) {
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      m[w] = sm.wm[w][h];
-      M = max(M, m[w]);
+      for (int i = 0; i < 4; ++i) M = max(M, sm.wm[w + i][h]);
     }
     float o = 0.0f, l = 0.0f;
+    for (int w = 0; w < n_act; w += 4) {
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float f = m[w] == INT_MIN ? 0.0f : __builtin_amdgcn_ldexpf(1.0f, m[w] - M);
-      o = fmaf(f, sm.wo[w][h][d] + sm.wo[w][h + 8][d], o);
-      l = fmaf(f, sm.wl[w][h], l);
+      for (int i = 0; i < 4; ++i) {
+        const int m = sm.wm[w + i][h];
+        const float f = m == INT_MIN ? 0.0f : __builtin_amdgcn_ldexpf(1.0f, m - M);
+        o = fmaf(f, sm.wo[w + i][h][d], o);
+        l = fmaf(f, sm.wl[w + i][h], l);
+      }
     }
     if constexpr (V8) o = __builtin_amdgcn_ldexpf(o, -gref);
     if (Sn == 1) {
@@ -881,16 +998,28 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
       }
     } else {
       const int64_t ps = bq * Sn + split;
-      a.part_o[ps * kDim + d] = o;
+      if (kPool && a.ticket != 0) {  // uniform
+        store_agent(&a.part_o[ps * kDim + d], o);
+        if (d == 0) {
+          store_agent(&a.part_l[ps], l);
+          store_agent(&a.part_m[ps], M);
+        }
+      } else {
+        a.part_o[ps * kDim + d] = o;
+        if (d == 0) {
+          a.part_l[ps] = l;
+          a.part_m[ps] = M;
+        }
+      }
       if (d == 0) {
-        a.part_l[ps] = l;
-        a.part_m[ps] = M;
         if constexpr (DEBUG) {
           if (a.dbg_m_split) a.dbg_m_split[ps] = M;
         }
       }
     }
   }
+  if constexpr (kPool)
+    if (Sn > 1 && a.ticket != 0) merge_splits<G, DEBUG, NW>(a, seq, kvh, b, sm);
 }
 
 // Merges the key splits of one (batch, query head): M = max_s M_s and
@@ -1001,7 +1130,7 @@ static hipError_t launch_t(const DecodeArgs& a, hipStream_t stream, hipEvent_t e
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev_end != nullptr && (e = hipEventRecord(ev_end, stream)) != hipSuccess) return e;
-  if (a.n_splits == 1) return hipSuccess;
+  if (a.n_splits == 1 || a.ticket != 0) return hipSuccess;
   hipLaunchKernelGGL((combine_kernel<DEBUG>), dim3((uint32_t)(a.B * a.Hq)),
                      dim3(64 * kCombineWaves), 0, stream, a);
   return hipGetLastError();

@@ -53,6 +53,16 @@ pot_status report_error(pot_status st, const char* fmt, ...);
 // multiply path, kept beside the shift path for measurement)
 enum ScoreMode : int { kScorePot = 0, kScoreInt8 = 1, kScoreFp16 = 2, kScoreDs4a = 3 };
 
+// Splits that the last workgroup of a unit merges (CU-wide workgroups); more go
+// to the combine kernel, whose workgroups share the reading: one CU gets about
+// 32 KB per us of partials that other XCDs wrote. PoT-4 graph replays, us, in
+// the kernel and with the combine kernel: B = 1, T = 1024 (4 splits) 7.5 and
+// 8.2, T = 4096 (16) 8.0 and 8.9, T = 8192 (32) 8.3 and 9.0, T = 32768 (64) 12.8
+// and 10.7; B = 4, T = 4096 (16) 8.6 and 9.6. A launch of the combine kernel also
+// costs the host 3 us. Four-wave workgroups, with two heads to a wave, took 9.1
+// and 8.2 at 4 splits of fp16 keys and keep the combine kernel.
+constexpr int kMaxMergedSplits = 32;
+
 // Everything one decode launch needs. Passed by value as the kernel argument.
 struct DecodeArgs {
   const float* q;
@@ -69,6 +79,8 @@ struct DecodeArgs {
   int32_t* part_m;           // [B*Hq*S]
   float* part_l;             // [B*Hq*S]
   float* part_o;             // [B*Hq*S*64]
+  unsigned long long* tickets;  // one word per (batch, kv head), merge_splits
+  unsigned long long ticket;    // this call's tag; 0: a combine kernel merges the splits
   // debug taps (nullable)
   int8_t* dbg_qhat;
   float* dbg_delta;
@@ -120,9 +132,10 @@ constexpr int pool_waves(int mode, int mant_bits, int vf) {
 // (fp16 values: 128 bytes per key, rounded up to whole 8-key groups).
 constexpr int kMaxKeys = (1 << 24) - 8;
 
-// 32-bit words per decode workgroup at the head of the workspace. The kernels
-// keep the prepared queries in LDS; the workspace sizes that callers compute
-// and allocate by are part of the interface, so this part of them stays.
+// 32-bit words per decode workgroup at the head of the workspace (256 bytes at
+// the least). The tickets of the split merge take a little of that room. The
+// sizes that callers compute and allocate by are part of the interface, so the
+// rest of it stays.
 constexpr int query_words(int G) { return (33 * G + 63) / 64 * 64; }
 
 // vf: value format. 0: fp16 value cache (a.v); 1: INT8 value cache (a.v8,
