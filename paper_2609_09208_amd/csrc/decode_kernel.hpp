@@ -650,19 +650,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   constexpr int kEarlyV = kPool ? kEarlyValueBlocks<MODE, K> : 2;
   ValRegs<V8> vr;
   uint4 ksc[2];
-  auto load_rest = [&](int jt) {
-    const int t0 = t_begin + kWTile * jt;
-    if constexpr (MODE != kScoreFp16) load_scales(st, t0, lane, ksc);
-    load_values_buf<V8, 0, kEarlyV>(st, t0, lane, vr);
+  auto load_tile_scales = [&](int jt) {
+    if constexpr (MODE != kScoreFp16) load_scales(st, t_begin + kWTile * jt, lane, ksc);
   };
-  auto load_first = [&]() {
-    load_keys_tile(j, kr[0]);
-    load_rest(j);
+  auto load_tile_values = [&](int jt) {
+    load_values_buf<V8, 0, kEarlyV>(st, t_begin + kWTile * jt, lane, vr);
   };
-  // A wave's first tile is requested at once, unless it holds the row that is
-  // being appended: then after the barrier below.
+  // A wave's first keys and scales are requested at once, unless the tile holds
+  // the row that is being appended: then after the barrier below. The first
+  // values follow after the barrier in any case: they are not needed before the
+  // scores, and on a full chip the requests of all waves' values would hold up
+  // the queries that the barrier waits for.
   const bool late_first = appends && j == j_last;
-  if (j < n_tiles && !late_first) load_first();
+  if (j < n_tiles && !late_first) {
+    load_keys_tile(j, kr[0]);
+    load_tile_scales(j);
+  }
   if constexpr (kPool) {
     if (tid == 0) sm.next = 2 * NW;
   }
@@ -701,7 +704,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
                                          __HIP_MEMORY_SCOPE_AGENT);
   if (appends && wave < 2) wait_stores_in_l2();
   __syncthreads();
-  if (j < n_tiles && late_first) load_first();
+  if (j < n_tiles) {
+    if (late_first) {
+      load_keys_tile(j, kr[0]);
+      load_tile_scales(j);
+    }
+    load_tile_values(j);
+  }
   if constexpr (V8) {
     gref = sm.gm[0];
 #pragma unroll
@@ -919,7 +928,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     } else {
       j += NW;
     }
-    if (j < n_tiles) load_rest(j);
+    if (j < n_tiles) {
+      load_tile_scales(j);
+      load_tile_values(j);
+    }
   };
 #pragma nounroll
   while (j < n_tiles) {
@@ -948,8 +960,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
                                                       false, false);
     lsum = __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
   }
-  // Only waves that had a tile take part, in whole groups of four (a wave of
-  // such a group without tiles has zero sums and factor 0). Rows h and h + 8 of
+  // Only the sums of waves that had a tile are merged, in whole groups of four (a
+  // wave of such a group without tiles has zero sums and factor 0). Rows h and h + 8 of
   // the products (weights' high and low parts) sit in the two halves of the
   // wave and are added on the way to LDS.
   const int n_act = kPool ? min(NW, (n_tiles + 3) & ~3) : NW;
@@ -963,10 +975,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
         const float sum = __uint_as_float(h[0]) + __uint_as_float(h[1]);
         if (lane < 32) sm.wo[wave][4 * grp + r][16 * nb + row] = sum;
       }
-    if (lane < 8) {
-      sm.wm[wave][lane] = m_run;
-      sm.wl[wave][lane] = lsum;
-    }
+  }
+  if (lane < 8) {
+    sm.wm[wave][lane] = m_run;
+    sm.wl[wave][lane] = lsum;
   }
   __syncthreads();
 
@@ -974,20 +986,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   for (int idx = tid; idx < G * kDim; idx += kBlk) {
     const int h = __builtin_amdgcn_readfirstlane(idx / kDim), d = idx % kDim;
     const int64_t bq = (int64_t)b * a.Hq + a.q_head(kvh * G + h);
-    int M = INT_MIN;
-    for (int w = 0; w < n_act; w += 4) {
+    // lane w holds wave w's maximum, factor and sum of the head
+    static_assert(NW <= 64, "a lane per wave");
+    const int m_w = lane < NW ? sm.wm[lane < NW ? lane : 0][h] : INT_MIN;
+    const float l_w = lane < NW ? sm.wl[lane < NW ? lane : 0][h] : 0.0f;
+    const int M = wave_max_i32(m_w);
+    const float f_w = m_w == INT_MIN ? 0.0f : __builtin_amdgcn_ldexpf(1.0f, m_w - M);
+    const float l = wave_sum(f_w * l_w);
+    float o = 0.0f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) M = max(M, sm.wm[w + i][h]);
-    }
-    float o = 0.0f, l = 0.0f;
-    for (int w = 0; w < n_act; w += 4) {
+    for (int w = 0; w < NW; w += 4) {
+      if (w >= n_act) break;  // uniform
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int m = sm.wm[w + i][h];
-        const float f = m == INT_MIN ? 0.0f : __builtin_amdgcn_ldexpf(1.0f, m - M);
-        o = fmaf(f, sm.wo[w + i][h][d], o);
-        l = fmaf(f, sm.wl[w + i][h], l);
-      }
+      for (int i = w; i < w + 4; ++i)
+        o = fmaf(__uint_as_float(
+                     (uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(f_w), i)),
+                 sm.wo[i][h][d], o);
     }
     if constexpr (V8) o = __builtin_amdgcn_ldexpf(o, -gref);
     if (Sn == 1) {
