@@ -13,7 +13,7 @@
 // the ratio's bits with integer operations (an add that carries into the
 // exponent exactly above the cut point, a shift and a clamp) and its sign
 // bits from the inputs' sign bits eight at a time by byte permutes; PoT-Mk
-// (K > 0) compares the mantissa against the fp32 cut points. (The INT8
+// (K > 0) squares the mantissa against the product of its two grid points. (The INT8
 // comparator's encoder takes the same shape; the fused per-token append in the
 // decode kernel encodes one row per wavefront, one element per lane.)
 #include <hip/hip_fp16.h>
@@ -153,38 +153,36 @@ __device__ __forceinline__ uint32_t pot4_word(const float (&c)[8], uint32_t sgn,
 // PoT-Mk code word and mantissa-plane bytes of 8 elements from their clamped
 // half ratios v_i = min(RN(|x_i| / (2 s)), 1) (0 for NaN): ratios up to 2 on
 // the unit interval, so that caller scales with |x| / s in [1, 2) still see
-// their mantissa. With v = (1 + M 2^-23) 2^(E-127) and Mc the mantissa of the
-// largest cut point (the one between the binade's top value and the next
-// binade), F = E + [M > Mc] - 119 (bits + 2^23 - 1 - Mc - (119 << 23), shifted)
-// gives the exponent field 7 - clamp(F, 1, 7) for a ratio above the zero cut
-// (F >= 8: the top value; F <= 0: the smallest magnitude), 7 for the zero
-// code. The mantissa is the number of cut points below m = 1 + M 2^-23 modulo
-// 2^k: with t = floor(m 2^k) = 2^k + j0, m lies above the cut between grid
-// points j0 and j0 + 1, RD(sqrt(t (t + 1)) / 2^k), exactly when (m 2^k)^2 >
-// t (t + 1) (the root is irrational), which one fused multiply-add decides
-// by its sign. Saturated ratios take j = 2^k - 1, the smallest magnitude and
-// the zero code j = 0. Returns the code word (signs as in pot4_word) and
-// writes the K plane bytes (bit i of plane b: bit b of element i's j).
+// their mantissa. With v = (1 + M 2^-23) 2^(E-127) and m = 1 + M 2^-23, the top
+// K bits of M are j0, t = floor(m 2^k) = 2^k + j0, and m lies above the cut
+// between grid points j0 and j0 + 1, RD(sqrt(t (t + 1)) / 2^k), exactly when
+// (m 2^k)^2 > t (t + 1) (the root is irrational), which one fused multiply-add
+// decides by its sign. E and j0 stand next to each other in v's bits, so adding
+// that decision to the bits above them carries from the last grid point into
+// the next binade by itself: u = (E - 119) 2^k + j0 + [above], clamped to 2^k
+// .. 2^(k+3) - 1 (ratios past the top value and below the smallest magnitude)
+// and 0 for a ratio at or below the zero cut, holds 7 - e above the mantissa.
+// (Deciding exponent and mantissa apart took about 20 operations per element,
+// this 14: 2 M rows k = 1 85 -> 81, k = 4 109 -> 96 us.) Returns the code word
+// (signs as in pot4_word) and writes the K plane bytes (bit i of plane b: bit b
+// of element i's j).
 template <int K>
-__device__ __forceinline__ uint32_t potmk_word(const float (&v)[8], uint32_t sgn, uint32_t cmk,
+__device__ __forceinline__ uint32_t potmk_word(const float (&v)[8], uint32_t sgn,
                                                uint32_t zc_half, uint32_t (&planes)[K]) {
-  constexpr uint32_t n = 1u << K;
+  constexpr int n = 1 << K;
   uint32_t w = 0, jw = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const uint32_t vb = __float_as_uint(v[i]);
-    const int f1 = (int)(vb + cmk) >> 23;
-    const uint32_t g = (vb > zc_half) ? (uint32_t)min(max(f1, 1), 7) : 0u;
-    w |= g << (4 * i);
     const float mn = __uint_as_float((vb & 0x007FFFFFu) | ((127u + K) << 23));  // m 2^k
-    const uint32_t j0 = (vb >> (23 - K)) & (n - 1);
     const float t = truncf(mn);                  // 2^k + j0
     const float p = __builtin_fmaf(t, t, t);     // t (t + 1) <= 992, exact
-    const uint32_t above = (__builtin_fmaf(mn, mn, -p) > 0.0f) ? 1u : 0u;
-    uint32_t j = (j0 + above) & (n - 1);
-    j = (f1 > 7) ? n - 1 : j;
-    j = (f1 < 1) ? 0u : j;  // also every zero code
-    jw |= j << (4 * i);
+    const int above = __builtin_fmaf(mn, mn, -p) > 0.0f ? 1 : 0;
+    const int q = ((int)(vb - (119u << 23)) >> (23 - K)) + above;
+    uint32_t u = (uint32_t)min(max(q, n), 8 * n - 1);
+    u = vb > zc_half ? u : 0u;
+    w |= (u >> K) << (4 * i);
+    jw |= (u & (n - 1)) << (4 * i);
   }
 #pragma unroll
   for (int b = 0; b < K; ++b) {  // bits 4i + b of jw to bit i
@@ -256,11 +254,9 @@ __global__ __launch_bounds__(kBlock) void encode_pot_kernel(
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t groups = (uint32_t)((n_rows + 7) / 8);
   const uint32_t stride = gridDim.x * (kBlock / 64);
-  // K = 0: bits-to-G offset of pot4_word (Mc from the fp32 cut point); K > 0:
-  // the offset of potmk_word (the largest cut point) and half the zero cut
-  const uint32_t cst =
-      K == 0 ? 0x007FFFFFu - (__float_as_uint(tab.cut[0]) & 0x007FFFFFu) - (120u << 23)
-             : 0x007FFFFFu - (__float_as_uint(tab.cut[(1 << K) - 1]) & 0x007FFFFFu) - (119u << 23);
+  // the bits-to-G offset of pot4_word (Mc from the fp32 cut point) and half the
+  // zero cut
+  const uint32_t cst = 0x007FFFFFu - (__float_as_uint(tab.cut[0]) & 0x007FFFFFu) - (120u << 23);
   const uint32_t zc_half = __float_as_uint(tab.zero_cut) - (1u << 23);
   // lane parts of the addresses; a group's bases are uniform
   const uint32_t in_off = (uint32_t)(rl * kDim * 2 + 16 * g);
@@ -335,7 +331,7 @@ __global__ __launch_bounds__(kBlock) void encode_pot_kernel(
     if constexpr (K == 0) {
       word = pot4_word(c, sign_nibbles(sa, sb), cst);
     } else {
-      word = potmk_word<K>(c, sign_nibbles(sa, sb), cst, zc_half, plane);
+      word = potmk_word<K>(c, sign_nibbles(sa, sb), zc_half, plane);
     }
     uint32_t pq = 0;
     if constexpr (K > 0) pq = quad_planes<K>(plane, lane);

@@ -2,7 +2,9 @@
 the INT8 value store over ranges that start and end inside a group, over more
 sequences than one grid dimension holds and over NaN, infinite and zero tokens;
 the INT8 key encoder over row counts beside a multiple of eight, with a row
-stride. Bytes and scales are exact against the oracle; nothing else is written.
+stride; the PoT key encoder likewise, plain and rotated (16 rows per wave), over
+values that fall on both of the rotation's paths and at the mantissa cut points.
+Bytes and scales are exact against the oracle; nothing else is written.
 """
 import numpy as np
 import pytest
@@ -73,4 +75,47 @@ def test_int8_encode_row_counts(n, stride, had):
     want_s = np.full(n * stride, -5.0, np.float32)
     want_s[::stride][:n] = osc
     assert np.array_equal(codes.cpu().numpy(), want)
+    assert np.array_equal(sc.cpu().numpy().view(np.uint32), want_s.view(np.uint32))
+
+
+def pot_rows(n, had):
+    """Rows over the whole fp16 range, some all zero, tiny, subnormal or constant (the
+    rotation then leaves one element); for the rotation, which is exact on the matrix cores
+    up to 4096, rows at and above that bound beside others; NaN and infinities."""
+    rng = np.random.default_rng(n + 1000 * had)
+    k = rng.standard_normal((n, 64)) * 2.0 ** rng.integers(-26, 9, (n, 1))
+    k *= 2.0 ** rng.integers(-9, 2, (n, 64))
+    k = np.clip(k, -4096, 4096).astype(np.float16)
+    pick = rng.random(n)
+    k[pick < 0.05] = 0.0
+    k[(pick > 0.1) & (pick < 0.15)] = -3.25
+    if n >= 16:
+        k[3, 5], k[3, 9], k[3, 11] = 4096.0, 2.0 ** -24, 15.992
+    if n >= 33:  # the second group of 16 takes the butterflies
+        k[17, 1], k[18, 2], k[19, 3], k[20, 4] = 4098.0, 65504.0, np.inf, np.nan
+        k[21] = np.nan
+        k[22, 0::2], k[22, 1::2] = 65504.0, -65504.0
+    return k
+
+
+@pytest.mark.parametrize("had", [False, True])
+@pytest.mark.parametrize("mant_bits", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("n,stride", [(1, 1), (7, 3), (15, 1), (16, 2), (17, 1), (33, 5),
+                                      (4099, 1)])
+def test_pot_encode_row_counts(n, stride, mant_bits, had):
+    k = pot_rows(n, had)
+    se = torch.full((n * stride, 32), 99, dtype=torch.uint8, device=DEV)
+    cm = torch.full((n * stride, 8 * max(mant_bits, 1)), 98, dtype=torch.uint8, device=DEV)
+    sc = torch.full((n * stride,), -5.0, dtype=torch.float32, device=DEV)
+    fmt = pa.make_format(mant_bits=mant_bits, hadamard=had)
+    pa.pot_encode_keys(fmt, to_dev(k), n, stride, 0, sc, se, cm if mant_bits else None)
+    torch.cuda.synchronize()
+    ose, ocm, osc = oracle.encode_keys(k.view(np.uint16), mant_bits, hadamard=had)
+    for got, ref, fill in ((se, ose, 99), (cm, ocm if mant_bits else None, 98)):
+        want = np.full(got.shape, fill, np.uint8)
+        if ref is not None:
+            want[::stride][:n] = ref
+        assert np.array_equal(got.cpu().numpy(), want)
+    want_s = np.full(n * stride, -5.0, np.float32)
+    want_s[::stride][:n] = osc
     assert np.array_equal(sc.cpu().numpy().view(np.uint32), want_s.view(np.uint32))
