@@ -4,10 +4,10 @@
 // The bulk PoT encoder works on 8 key rows per wavefront at a time: lane l
 // takes row l / 8 of the group and elements 8g .. 8g + 7 of it (g = l % 8),
 // so a row is one 16-byte load per lane over 8 lanes and its code word g (the
-// 8 nibbles of those elements) is one 4-byte store. The optional Walsh-
-// Hadamard rotation is an exact fp64 butterfly (spans 1, 2, 4 inside the
-// lane, 8, 16, 32 across the row's lanes), the row scale a max over 8 values
-// and three DPP lane exchanges. Each ratio |x| / s is correctly rounded from
+// 8 nibbles of those elements) is one 4-byte store; the row scale is a max over
+// 8 values and three DPP lane exchanges. With the optional Walsh-Hadamard
+// rotation it works on 16 rows and rotates them on the matrix cores, exactly
+// (rows with elements above 4096 by fp64 butterflies, eight at a time). Each ratio |x| / s is correctly rounded from
 // one reciprocal per row (a Newton-corrected hardware reciprocal, then
 // Markstein's correction of the quotient). PoT-4 then takes its code from
 // the ratio's bits with integer operations (an add that carries into the
@@ -234,8 +234,7 @@ __device__ __forceinline__ void unpack_row(const uint32_t (&w4)[4], int lane, fl
 // The K plane bytes of each lane of a quad (code words 4h .. 4h + 3 of a row)
 // to one dword of plane j in lane j: a 4 x 4 byte transpose by two DPP moves
 // and byte permutes, for one dword store per lane. (With a byte store per lane
-// and plane, and the rotation's exchanges through LDS: 2 M rows at k = 4 182 us
-// rotated and 117 not, now 164 and 108; k = 0 rotated 147, now 103.)
+// and plane 2 M rows at k = 4 took 117 us, so 108.)
 template <int K>
 __device__ __forceinline__ uint32_t quad_planes(const uint32_t (&plane)[K], int lane) {
   uint32_t w = 0;
@@ -245,105 +244,278 @@ __device__ __forceinline__ uint32_t quad_planes(const uint32_t (&plane)[K], int 
   return __builtin_amdgcn_perm(lane_xor_u32<2>(w), w, lane & 2 ? 0x03020706u : 0x05040100u);
 }
 
+// The bits-to-G offset of pot4_word (Mc from the fp32 cut point) and half the
+// zero cut.
+struct CutBits {
+  uint32_t cst, zc_half;
+};
+__device__ __forceinline__ CutBits cut_bits(const EncodeTables& tab) {
+  return {0x007FFFFFu - (__float_as_uint(tab.cut[0]) & 0x007FFFFFu) - (120u << 23),
+          __float_as_uint(tab.zero_cut) - (1u << 23)};
+}
+
+// Sign nibbles of 8 fp32 numbers (selector 9 / 11: bit 31 of the low / high
+// source, 12: zero byte).
+__device__ __forceinline__ uint32_t float_signs(const float* x) {
+  uint32_t xb[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) xb[i] = __float_as_uint(x[i]);
+  return sign_nibbles(__builtin_amdgcn_perm(xb[1], xb[0], 0x0C0C0B09u) |
+                          __builtin_amdgcn_perm(xb[3], xb[2], 0x0B090C0Cu),
+                      __builtin_amdgcn_perm(xb[5], xb[4], 0x0C0C0B09u) |
+                          __builtin_amdgcn_perm(xb[7], xb[6], 0x0B090C0Cu));
+}
+
+// A row's scale as its elements use it.
+// The clamped ratio c = min(RN(|x| / ss), 1) per element (ss = s for PoT-4, 2 s
+// for PoT-Mk), NaN -> 0 (zero code), comes from one correctly rounded reciprocal
+// per row; other scales (zero, negative, NaN, infinite, or too small or too
+// large for a normal reciprocal) divide instead. The quotient q = RN(|x| r) is
+// clamped too: min(q, 1) is still within an ulp of a quotient below 1, any q >=
+// 1 gives c >= 1, and an infinite or NaN q (infinite or NaN x) cannot poison
+// the residual.
+struct RowScale {
+  float s, ss, r;
+  bool fast;
+};
+template <int K>
+__device__ __forceinline__ RowScale row_scale(float s) {
+  const float ss = K == 0 ? s : 2.0f * s;
+  return {s, ss, recip_rn(ss), recip_in_range(ss)};
+}
+
+// Code word and plane bytes of 8 elements.
+template <int K>
+__device__ __forceinline__ uint32_t encode_word(const float* x, const RowScale& sc, uint32_t sgn,
+                                                const CutBits& cut,
+                                                uint32_t (&plane)[K > 0 ? K : 1]) {
+  float c[8];
+  if (sc.fast) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float a = fabsf(x[i]);
+      const float q = clamp01(a * sc.r);
+      c[i] = clamp01(__builtin_fmaf(__builtin_fmaf(-q, sc.ss, a), sc.r, q));
+    }
+  } else {
+    // (|x| / 2) / s rounds as |x| / (2 s) and stays finite-safe for huge s
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      c[i] = (sc.s > 0.0f) ? clamp01((K == 0 ? fabsf(x[i]) : fabsf(x[i]) * 0.5f) / sc.s) : 0.0f;
+  }
+  if constexpr (K == 0) return pot4_word(c, sgn, cut.cst);
+  else return potmk_word<K>(c, sgn, cut.zc_half, plane);
+}
+
+// The arguments of one encode launch.
+struct EncodeArgs {
+  const __half* k;
+  int64_t n_rows, out_stride;
+  int scale_mode;
+  float* key_scale;
+  uint8_t* codes_se;
+  uint8_t* codes_m;
+};
+
+// Rows row0 .. row0 + 7 (row0 uniform) by the calling wave.
 template <int K, bool HAD>
-__global__ __launch_bounds__(kBlock) void encode_pot_kernel(
-    const __half* __restrict__ k, int64_t n_rows, int64_t out_stride, int scale_mode,
-    float* __restrict__ key_scale, uint8_t* __restrict__ codes_se,
-    uint8_t* __restrict__ codes_m, EncodeTables tab) {
-  const int lane = threadIdx.x & 63, g = lane & 7, rl = lane >> 3;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t groups = (uint32_t)((n_rows + 7) / 8);
-  const uint32_t stride = gridDim.x * (kBlock / 64);
-  // the bits-to-G offset of pot4_word (Mc from the fp32 cut point) and half the
-  // zero cut
-  const uint32_t cst = 0x007FFFFFu - (__float_as_uint(tab.cut[0]) & 0x007FFFFFu) - (120u << 23);
-  const uint32_t zc_half = __float_as_uint(tab.zero_cut) - (1u << 23);
+__device__ __forceinline__ void encode_rows8(const EncodeArgs& a, int64_t row0,
+                                             const CutBits& cut) {
+  const int lane = lane_id(), g = lane & 7, rl = lane >> 3;
   // lane parts of the addresses; a group's bases are uniform
   const uint32_t in_off = (uint32_t)(rl * kDim * 2 + 16 * g);
-  const int64_t out_row = (int64_t)rl * out_stride;
+  const int64_t out_row = (int64_t)rl * a.out_stride;
   const int64_t se_off = out_row * (kDim / 2) + 4 * g;
-  for (uint32_t grp_iv = blockIdx.x * (kBlock / 64) + wave; grp_iv < groups;
-       grp_iv += stride) {
+  const bool valid = row0 + rl < a.n_rows;  // uniform over the row's 8 lanes
+  uint4 raw = make_uint4(0u, 0u, 0u, 0u);
+  if (valid)
+    raw = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.k) + row0 * kDim * 2 +
+                                          in_off);
+  const uint32_t w4[4] = {raw.x, raw.y, raw.z, raw.w};
+  float x[8];
+  unpack_row<HAD>(w4, lane, x);
+  const int64_t orow = (row0 * a.out_stride) + out_row;
+  float s;
+  if (a.scale_mode == 0) {
+    // max |x| ignoring NaN (0 for a row of zeros and NaNs)
+    s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s = fmaxf(s, fabsf(x[i]));
+    s = max_over_8_lanes(s);
+  } else {
+    s = valid ? a.key_scale[orow] : 0.0f;
+  }
+  // sign bits of the inputs: selectors 8..11 are bits 15, 31 of the low and of
+  // the high source
+  const uint32_t sgn =
+      HAD ? float_signs(x)
+          : sign_nibbles(__builtin_amdgcn_perm(w4[1], w4[0], 0x0B0A0908u),
+                         __builtin_amdgcn_perm(w4[3], w4[2], 0x0B0A0908u));
+  uint32_t plane[K > 0 ? K : 1];
+  const uint32_t word = encode_word<K>(x, row_scale<K>(s), sgn, cut, plane);
+  uint32_t pq = 0;
+  if constexpr (K > 0) pq = quad_planes<K>(plane, lane);
+  if (valid) {
+    const int64_t urow = row0 * a.out_stride;  // uniform part of orow
+    *reinterpret_cast<uint32_t*>(a.codes_se + urow * (kDim / 2) + se_off) = word;
+    if constexpr (K > 0) {
+      // lane j < K of a quad: plane j's bytes of the quad's four code words
+      if ((g & 3) < K)
+        *reinterpret_cast<uint32_t*>(a.codes_m + orow * 8 * K + 8 * (g & 3) + 4 * (g >> 2)) = pq;
+    }
+    if (a.scale_mode == 0 && g == 0) a.key_scale[orow] = s;
+  }
+}
+
+template <int K>
+__global__ __launch_bounds__(kBlock) void encode_pot_kernel(const EncodeArgs a,
+                                                            const EncodeTables tab) {
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t groups = (uint32_t)((a.n_rows + 7) / 8);
+  const uint32_t stride = gridDim.x * (kBlock / 64);
+  const CutBits cut = cut_bits(tab);
+  for (uint32_t grp = blockIdx.x * (kBlock / 64) + wave; grp < groups; grp += stride)
     // the group index as an opaque uniform value: addresses are rebuilt from
     // it each trip as scalar bases plus the fixed lane offsets
-    const uint32_t grp = __builtin_amdgcn_readfirstlane(grp_iv);
-    const int64_t row0 = (int64_t)grp * 8;
-    const bool valid = row0 + rl < n_rows;  // uniform over the row's 8 lanes
-    uint4 raw = make_uint4(0u, 0u, 0u, 0u);
-    if (valid) raw = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(k) + row0 * kDim * 2 + in_off);
-    const uint32_t w4[4] = {raw.x, raw.y, raw.z, raw.w};
-    float x[8];
-    unpack_row<HAD>(w4, lane, x);
-    const int64_t orow = (row0 * out_stride) + out_row;
+    encode_rows8<K, false>(a, (int64_t)__builtin_amdgcn_readfirstlane(grp) * 8, cut);
+}
+
+// Rotated keys: the 64 x 64 Hadamard matrix on the matrix cores, 16 rows per
+// wave at a time, exactly. Every fp16 element x is split as hi + lo: lo is what
+// rounding min(|x|, 16) to a multiple of 2^-5 leaves (below 2^-6, a multiple of
+// 2^-24; 0 from 16 on) and hi = x - lo is a multiple of 2^-6; both are fp16
+// numbers. v_mfma_f32_16x16x32_f16 with +-1 then sums 64 hi's (below 2^18 if
+// |x| <= 4096: exact in fp32 with unit 2^-6) and 64 lo's (as lo 2^12, which is
+// never subnormal: at most 2^12 with unit 2^-12), and fma(LO, 2^-12, HI) is the
+// rotation's one rounding, as fp64 butterflies and a conversion round it. Rows
+// with a larger, infinite or NaN element take the butterflies. A = H with rows
+// in such an order that lane l gets elements 16 (l / 16) ..+15 of row l % 16: two
+// code words. Butterflies cost about 250 VALU operations per 8 rows, this 45 per
+// 16 and 16 matrix instructions. Butterflies -> here: 131072 rows k = 0 10.5 -> 9.6,
+// k = 4 14.3 -> 13.6; 2 M rows k = 0 105 -> 86, k = 4 150 -> 132 us; up to 16384
+// rows, one group per wave either way, no difference.
+typedef _Float16 half8e __attribute__((ext_vector_type(8)));
+typedef _Float16 half2e __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2e __attribute__((ext_vector_type(2)));
+typedef float f32x4e __attribute__((ext_vector_type(4)));
+constexpr uint32_t kExactHalf = 0x6C00;  // 4096 in fp16
+
+// amdgpu_waves_per_eu(4): 98..104 VGPRs; at five waves the matrix spills.
+template <int K>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
+void encode_pot_had_kernel(const EncodeArgs a, const EncodeTables tab) {
+  const int lane = lane_id(), col = lane & 15, blk = lane >> 4;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t groups = (uint32_t)((a.n_rows + 15) / 16);
+  const uint32_t stride = gridDim.x * (kBlock / 64);
+  const CutBits cut = cut_bits(tab);
+  // Row col of block nb of H is element m = 16 (col / 4) + 4 nb + col % 4, its
+  // columns are k = 32 kb + 8 blk + j, and the sign is the parity of m & k: bits
+  // 0..2 of j against col % 4 and nb's low bit, k's bits 3, 4 against nb's high
+  // bit and bit 2 of col, bit 5 against bit 3 of col (h5, at kb = 1).
+  constexpr uint32_t kSigns = 0x80008000u;
+  const uint32_t h5 = (col & 8) ? kSigns : 0u;
+  uint32_t h[4][4];
+#pragma unroll
+  for (int nb = 0; nb < 4; ++nb) {
+    const bool odd = (((nb >> 1) & blk) ^ ((col >> 2) & (blk >> 1))) & 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)  // j = 2q, 2q + 1
+      h[nb][q] = 0x3C003C00u ^ (odd ? kSigns : 0u) ^ ((col & 1) ? 0x80000000u : 0u) ^
+                 ((q & 1) && (col & 2) ? kSigns : 0u) ^ ((q & 2) && (nb & 1) ? kSigns : 0u);
+  }
+  for (uint32_t iv = blockIdx.x * (kBlock / 64) + wave; iv < groups; iv += stride) {
+    const int64_t row0 = (int64_t)__builtin_amdgcn_readfirstlane(iv) * 16;
+    const bool valid = row0 + col < a.n_rows;
+    uint4 raw[2] = {make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u)};
+    if (valid) {
+      const char* src = reinterpret_cast<const char*>(a.k) + row0 * kDim * 2 + col * kDim * 2;
+      raw[0] = *reinterpret_cast<const uint4*>(src + 16 * blk);
+      raw[1] = *reinterpret_cast<const uint4*>(src + 64 + 16 * blk);
+    }
+    const uint32_t w8[8] = {raw[0].x, raw[0].y, raw[0].z, raw[0].w,
+                            raw[1].x, raw[1].y, raw[1].z, raw[1].w};
+    u16x2e big = {0, 0};
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      big = __builtin_elementwise_max(big, __builtin_bit_cast(u16x2e, w8[i] & 0x7FFF7FFFu));
+    if (__any(big[0] > kExactHalf || big[1] > kExactHalf)) {
+      encode_rows8<K, true>(a, row0, cut);
+      if (row0 + 8 < a.n_rows) encode_rows8<K, true>(a, row0 + 8, cut);
+      continue;
+    }
+    uint32_t hw[8], lw[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const half2e v = __builtin_bit_cast(half2e, w8[i]);
+      const half2e c16 = {(_Float16)16.0f, (_Float16)16.0f},
+                   c48 = {(_Float16)48.0f, (_Float16)48.0f},
+                   c4k = {(_Float16)4096.0f, (_Float16)4096.0f};
+      const half2e y = __builtin_elementwise_max(__builtin_elementwise_min(v, c16), -c16);
+      const half2e lo = y - ((y + c48) - c48);
+      hw[i] = __builtin_bit_cast(uint32_t, v - lo);
+      lw[i] = __builtin_bit_cast(uint32_t, lo * c4k);
+    }
+    float x[16];
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+      f32x4e dh = {0.0f, 0.0f, 0.0f, 0.0f}, dl = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        const half8e bh = __builtin_bit_cast(
+            half8e, make_uint4(hw[4 * kb], hw[4 * kb + 1], hw[4 * kb + 2], hw[4 * kb + 3]));
+        const half8e bl = __builtin_bit_cast(
+            half8e, make_uint4(lw[4 * kb], lw[4 * kb + 1], lw[4 * kb + 2], lw[4 * kb + 3]));
+        const uint32_t f = kb ? h5 : 0u;
+        const half8e ha = __builtin_bit_cast(
+            half8e, make_uint4(h[nb][0] ^ f, h[nb][1] ^ f, h[nb][2] ^ f, h[nb][3] ^ f));
+        dh = __builtin_amdgcn_mfma_f32_16x16x32_f16(ha, bh, dh, 0, 0, 0);
+        dl = __builtin_amdgcn_mfma_f32_16x16x32_f16(ha, bl, dl, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        x[4 * nb + r] = __fmul_rn(__builtin_fmaf(dl[r], 0x1p-12f, dh[r]), 0.125f);
+    }
+    const int64_t orow = (row0 + col) * a.out_stride;
     float s;
-    if (scale_mode == 0) {
-      // max |x| ignoring NaN (0 for a row of zeros and NaNs)
+    if (a.scale_mode == 0) {
       s = 0.0f;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) s = fmaxf(s, fabsf(x[i]));
-      s = max_over_8_lanes(s);
+      for (int i = 0; i < 16; ++i) s = fmaxf(s, fabsf(x[i]));
+      uint32_t b = __float_as_uint(s);  // not negative: compares as its bits
+      const auto r16 = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+      b = max(r16[0], r16[1]);
+      const auto r32 = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+      s = __uint_as_float(max(r32[0], r32[1]));
     } else {
-      s = valid ? key_scale[orow] : 0.0f;
+      s = valid ? a.key_scale[orow] : 0.0f;
     }
-    // The clamped ratio c = min(RN(|x| / ss), 1) per element (ss = s for
-    // PoT-4, 2 s for PoT-Mk), NaN -> 0 (zero code), from one correctly
-    // rounded reciprocal per row; other scales (zero, negative, NaN,
-    // infinite, or too small or too large for a normal reciprocal) divide
-    // instead. The quotient q = RN(|x| r) is clamped too: min(q, 1) is still
-    // within an ulp of a quotient below 1, any q >= 1 gives c >= 1, and an
-    // infinite or NaN q (infinite or NaN x) cannot poison the residual.
-    const float ss = K == 0 ? s : 2.0f * s;
-    const bool fast = recip_in_range(ss);
-    const float r = recip_rn(ss);
-    float c[8];
-    if (fast) {
+    const RowScale sc = row_scale<K>(s);
+    uint32_t p0[K > 0 ? K : 1], p1[K > 0 ? K : 1];
+    uint2 word;
+    word.x = encode_word<K>(x, sc, float_signs(x), cut, p0);
+    asm volatile("" : "+v"(word.x));  // one word at a time: registers
+    word.y = encode_word<K>(x + 8, sc, float_signs(x + 8), cut, p1);
+    // 16 bits per plane and lane to 8 bytes of plane j in the lanes of block j:
+    // plane bits against block bits, by the lane-half and the row exchange
+    uint32_t t[2] = {0u, 0u};
+    if constexpr (K > 0) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float a = fabsf(x[i]);
-        const float q = clamp01(a * r);
-        c[i] = clamp01(__builtin_fmaf(__builtin_fmaf(-q, ss, a), r, q));
+      for (int b = 0; b < K; ++b) t[b / 2] |= (p0[b] | (p1[b] << 8)) << (16 * (b & 1));
+      const auto r32 = __builtin_amdgcn_permlane32_swap(t[0], t[1], false, false);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const auto r16 = __builtin_amdgcn_permlane16_swap(r32[i], r32[i], false, false);
+        t[i] = __builtin_amdgcn_perm(r16[1], r16[0], (blk & 1) ? 0x07060302u : 0x05040100u);
       }
-    } else {
-      // (|x| / 2) / s rounds as |x| / (2 s) and stays finite-safe for huge s
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        c[i] = (s > 0.0f) ? clamp01((K == 0 ? fabsf(x[i]) : fabsf(x[i]) * 0.5f) / s) : 0.0f;
     }
-    uint32_t sa, sb;  // sign bytes 0x00 / 0xFF of elements 0..3 and 4..7
-    if constexpr (HAD) {
-      const uint32_t xb[8] = {__float_as_uint(x[0]), __float_as_uint(x[1]),
-                              __float_as_uint(x[2]), __float_as_uint(x[3]),
-                              __float_as_uint(x[4]), __float_as_uint(x[5]),
-                              __float_as_uint(x[6]), __float_as_uint(x[7])};
-      // selector 9 / 11: bit 31 of the low / high source, 12: zero byte
-      sa = __builtin_amdgcn_perm(xb[1], xb[0], 0x0C0C0B09u) |
-           __builtin_amdgcn_perm(xb[3], xb[2], 0x0B090C0Cu);
-      sb = __builtin_amdgcn_perm(xb[5], xb[4], 0x0C0C0B09u) |
-           __builtin_amdgcn_perm(xb[7], xb[6], 0x0B090C0Cu);
-    } else {
-      // selectors 8..11: bits 15, 31 of the low and of the high source,
-      // the sign bits of the four halves
-      sa = __builtin_amdgcn_perm(w4[1], w4[0], 0x0B0A0908u);
-      sb = __builtin_amdgcn_perm(w4[3], w4[2], 0x0B0A0908u);
-    }
-    uint32_t word;
-    uint32_t plane[K > 0 ? K : 1];
-    if constexpr (K == 0) {
-      word = pot4_word(c, sign_nibbles(sa, sb), cst);
-    } else {
-      word = potmk_word<K>(c, sign_nibbles(sa, sb), zc_half, plane);
-    }
-    uint32_t pq = 0;
-    if constexpr (K > 0) pq = quad_planes<K>(plane, lane);
     if (valid) {
-      const int64_t urow = row0 * out_stride;  // uniform part of orow
-      *reinterpret_cast<uint32_t*>(codes_se + urow * (kDim / 2) + se_off) = word;
+      *reinterpret_cast<uint2*>(a.codes_se + orow * (kDim / 2) + 8 * blk) = word;
       if constexpr (K > 0) {
-        // lane j < K of a quad: plane j's bytes of the quad's four code words
-        if ((g & 3) < K)
-          *reinterpret_cast<uint32_t*>(codes_m + orow * 8 * K + 8 * (g & 3) + 4 * (g >> 2)) = pq;
+        if (blk < K)
+          *reinterpret_cast<uint2*>(a.codes_m + orow * 8 * K + 8 * blk) = make_uint2(t[0], t[1]);
       }
-      if (scale_mode == 0 && g == 0) key_scale[orow] = s;
+      if (a.scale_mode == 0 && blk == 0) a.key_scale[orow] = s;
     }
   }
 }
@@ -577,28 +749,21 @@ __global__ void fill_zero_kernel(uint32_t* __restrict__ p, size_t n_words, uint8
   }
 }
 
-template <int K, bool HAD>
-static void launch_encode_pot_t(const uint16_t* k, int64_t n_rows, int64_t out_stride,
-                                int scale_mode, float* key_scale, uint8_t* codes_se,
-                                uint8_t* codes_m, const EncodeTables& tab, hipStream_t stream) {
-  hipLaunchKernelGGL((encode_pot_kernel<K, HAD>), dim3(encode_grid(n_rows)), dim3(kBlock), 0,
-                     stream, reinterpret_cast<const __half*>(k), n_rows, out_stride, scale_mode,
-                     key_scale, codes_se, codes_m, tab);
-}
-
 hipError_t launch_encode_pot(const uint16_t* k, int64_t n_rows, int64_t out_stride,
                              int scale_mode, int hadamard, float* key_scale,
                              uint8_t* codes_se, uint8_t* codes_m, const EncodeTables& tab,
                              hipStream_t stream) {
   if (n_rows == 0) return hipSuccess;
+  const EncodeArgs a{reinterpret_cast<const __half*>(k), n_rows, out_stride, scale_mode, key_scale,
+                     codes_se, codes_m};
   auto go = [&](auto k_tag) {
     constexpr int KK = decltype(k_tag)::value;
     if (hadamard)
-      launch_encode_pot_t<KK, true>(k, n_rows, out_stride, scale_mode, key_scale, codes_se,
-                                    codes_m, tab, stream);
+      hipLaunchKernelGGL((encode_pot_had_kernel<KK>), dim3(encode_grid((n_rows + 1) / 2)),
+                         dim3(kBlock), 0, stream, a, tab);
     else
-      launch_encode_pot_t<KK, false>(k, n_rows, out_stride, scale_mode, key_scale, codes_se,
-                                     codes_m, tab, stream);
+      hipLaunchKernelGGL((encode_pot_kernel<KK>), dim3(encode_grid(n_rows)), dim3(kBlock), 0,
+                         stream, a, tab);
   };
   switch (tab.mant_bits) {
     case 0: go(std::integral_constant<int, 0>{}); break;
