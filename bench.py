@@ -59,9 +59,9 @@ COMPARE_ROUNDS = 3  # interleaved timing rounds per comparator engine
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "decode_pot4_b64_t32768_traffic.txt")
 PROFILE_READ_CEILING = os.path.join(ROOT, "profiles", "stream_read_ceiling.md")
 PROFILE_VALU = os.path.join(ROOT, "profiles", "decode_valu_counters.txt")
-# wave64 VALU instructions per ns per CU that shifts, v_perm, v_dot2 / v_dot4,
-# packed 16-bit ops and SGPR-operand forms issue at (profiles/valu_issue_rates.md):
-# the issue term of the roofline for the score cores
+# wave64 VALU instructions per ns per CU that shifts, v_perm, conversions and
+# SGPR-operand forms issue at (profiles/valu_issue_rates.md), an upper estimate for
+# a mix with faster ones: the issue term of the roofline
 ISSUE_RATE = 2.2
 N_CU = 256
 CSRC = os.path.join(ROOT, "paper_2609_09208_amd", "csrc")
@@ -141,7 +141,7 @@ def issue_term(lane_ops, rows: int, us: float):
             "peak_rate": ISSUE_RATE, "rate_unit": "wave64 VALU instr/ns/CU",
             "frac": floor_us / us,
             "source": "SQ_INSTS_VALU from profiles/decode_valu_counters.txt; issue rate of "
-                      "the shift / dot / SGPR-operand class from profiles/valu_issue_rates.md"}
+                      "the shift / SGPR-operand class from profiles/valu_issue_rates.md"}
 
 
 def read_ceiling():
@@ -527,7 +527,7 @@ def bulk_encode(pa, lay, dev):
     gbs = n * per_row / (us * 1e-6) / 1e9
     return {"rows": n, "us_per_call": us, "alg_bytes_per_row": per_row, "achieved_gbs": gbs,
             "frac": gbs / HBM_PEAK_GBS, "same_codes_as_cache": same,
-            "kernel": f"potattn::encode_pot_kernel<{k}, false>",
+            "kernel": f"potattn::encode_pot_kernel<{k}>",
             "timing": f"mean of 10 passes over {len(cl)} layers, HIP events around the passes"}
 
 
@@ -564,11 +564,11 @@ def comparators(pa, lay, dev):
     engines["pot_v8_pow2"] = lambda i: pa.pot_decode_attention_v8_pow2(
         lay.fmt, 0, cl[i]["q"], cl[i]["codes_se"], cl[i]["codes_m"], cl[i]["key_scale"],
         v8[i][0], v8[i][1], T, heads, B, HQ, HKV, T, out, ws)
-    if lay.k > 0:  # PoT-Mk decoded to 16-bit weights + v_dot2 (a multiply path)
+    if lay.k > 0:  # PoT-Mk decoded to fp16 weights (a multiply path)
         engines["dot"] = lambda i: pa.pot_dot_decode_attention(
             lay.fmt, cl[i]["q"], cl[i]["codes_se"], cl[i]["codes_m"], cl[i]["key_scale"],
             cl[i]["v"], T, heads, B, HQ, HKV, T, out, ws)
-    if lay.k == 0:  # byte decode + v_dot4 on the same PoT-4 caches (a multiply path)
+    if lay.k == 0:  # codes decoded to fp16 weights on the same PoT-4 caches (a multiply path)
         engines["ds4a"] = lambda i: pa.pot_ds4a_decode_attention(
             lay.fmt, cl[i]["q"], cl[i]["codes_se"], cl[i]["key_scale"], cl[i]["v"], T, heads,
             B, HQ, HKV, T, out, ws)
@@ -595,14 +595,15 @@ def comparators(pa, lay, dev):
             "ds4a_us_per_layer": ds4a_us,
             "ds4a_hbm_frac": frac(row_bytes(0), ds4a_us) if ds4a_us else None,
             "ds4a_speedup_vs_fp16": f16_us / ds4a_us if ds4a_us else None,
-            "ds4a_note": "PoT-4 codes decoded to int8 bytes by v_perm and scored by v_dot4 "
-                         "(software packed shift-dot, a multiply path)",
+            "ds4a_note": "PoT-4 codes decoded to fp16 weights and scored by matrix "
+                         "instructions (software packed shift-dot, a multiply path)",
             "dot_us_per_layer": dot_us,
             "dot_hbm_frac": frac(row_bytes(lay.k), dot_us) if dot_us else None,
             "dot_speedup_vs_fp16": f16_us / dot_us if dot_us else None,
             "dot_speedup_vs_sac": pot_us / dot_us if dot_us else None,
-            "dot_note": "PoT-Mk codes decoded to 16-bit weights sigma (2^k + j) 2^(7-e) and "
-                        "scored by v_dot2 (pot_dot_decode_attention, a multiply path)",
+            "dot_note": "PoT-Mk codes decoded to fp16 weights sigma (2^k + j) 2^(7-e) (scaled) "
+                        "and scored by matrix instructions (pot_dot_decode_attention, a "
+                        "multiply path)",
             "int8_values": {
                 "bytes_per_row": row_bytes_v8(lay.k),
                 "pot_us_per_layer": pv8_us,
@@ -745,12 +746,11 @@ def main() -> int:
                 "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                 "traffic": read_traffic() if (B, T, k) == (64, 32768, 0) else None,
                 "kernel": f"potattn::decode_kernel<0, 8, {k}, false, 0> (SAC, G = 8, fp16 V: "
-                          "products by packed 16-bit shifts, signs and int32 sums by "
-                          "v_dot2_i32_i16 with weights -1/0/+1"
-                          + (", one sum per mantissa bit plane" if k else "") + ")",
-                "note": "score cores built from shifts and adds alone (v_lshl_add_u32, "
-                        "SDWA shift + v_xad_u32) measured 0.57-0.60 of 8 TB/s in this "
-                        "kernel; the v_dot2 accumulate is the one timed here",
+                          f"{7 + k} sums of q^ with fp4 weights -1/0/+1, one per bit "
+                          "position, on the matrix cores with power-of-two block scales)",
+                "note": "score cores on the VALU (packed 16-bit shifts + v_dot2_i32_i16) "
+                        "were bound by their issue at 0.69-0.78 of 8 TB/s (PoT-4), "
+                        "0.58-0.62 (PoT-M1) and 0.38-0.39 (PoT-M4)",
                 "alg_bytes_per_launch": alg, "launch_us": kern_s * 1e6,
                 "launch_us_median": float(np.median(kus)), "launch_us_best": float(kus.min()),
                 "launches_timed": int(kus.size),
@@ -762,9 +762,9 @@ def main() -> int:
                 "keys_scored_per_s_call": B * HQ * T / call_s}
     issue = issue_term(lane_ops_per_key("sac", k), B * HKV * T, kern_s * 1e6)
     roofline["issue"] = issue
-    if k > 0 and issue is not None:
-        # PoT-Mk's shift-accumulate core is bound by VALU issue (eq. roofline's
-        # second term): the headline fraction is the issue one, HBM beside it
+    if issue is not None and issue["frac"] > roofline["frac"]:
+        # eq. roofline's second term is the larger one: the headline fraction is the
+        # issue one, HBM beside it
         hbm = {key: roofline.pop(key) for key in ("achieved", "peak", "unit", "frac", "traffic")}
         roofline.pop("bound")
         roofline = {"bound": "valu", "achieved": issue["achieved_rate"], "peak": ISSUE_RATE,

@@ -851,7 +851,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   // Stage 2 of a tile: weights from the scores and P.V on the matrix cores.
   auto stage2 = [&]() {
     // ---- 4. weights (fp16 high / low parts) and P.V on the matrix cores ----
-    // Each lane splits its 8 weights into hi = rtz(p) and lo = rtz(p - hi)
+    // Each lane splits its 8 weights into hi = rtz(p) and lo = rn(p - hi)
     // and hands lo to its partner lane (row ^ 8). Block kb = 0 then takes
     // rows 0-7 = hi, 8-15 = lo of the part-0 weights; block kb = 1 takes rows
     // 0-7 = lo, 8-15 = hi of the part-1 weights. Rows h and h + 8 are summed

@@ -16,7 +16,6 @@ constexpr int kDim = 64;        // head dimension d
 constexpr int kExpMax = 6;      // E for a 3-bit exponent field (Sec. II-A)
 constexpr int kZeroField = 7;   // e = E + 1 is the exact zero (Sec. II-A)
 constexpr int kQMax = 127;      // symmetric INT8 query
-constexpr int kFInt = 7;        // internal head-room: every shift F_int - e >= 1
 constexpr int kBlock = 256;     // threads per workgroup (4 waves)
 constexpr int kTile = 256;      // keys per tile, one key per thread in scoring
 
