@@ -163,14 +163,19 @@ __device__ __forceinline__ uint32_t pot4_word(const float (&c)[8], uint32_t sgn,
 // .. 2^(k+3) - 1 (ratios past the top value and below the smallest magnitude)
 // and 0 for a ratio at or below the zero cut, holds 7 - e above the mantissa.
 // (Deciding exponent and mantissa apart took about 20 operations per element,
-// this 14: 2 M rows k = 1 85 -> 81, k = 4 109 -> 96 us.) Returns the code word
-// (signs as in pot4_word) and writes the K plane bytes (bit i of plane b: bit b
-// of element i's j).
+// this 14: 2 M rows k = 1 85 -> 81, k = 4 109 -> 96 us.) The u's are packed a byte
+// each (bytes of a: elements 0..3, of b: 4..7), so exponents and mantissas come
+// apart four at a time, and the mantissa nibbles (bit i of plane b: bit b of
+// element i's j) become plane bytes by two exchanges of bits between bytes, all
+// planes at once (a nibble each and a bit gather per plane: k = 1 80, k = 4 95 us;
+// now 77 and 83).
+// Returns the code word (signs as in pot4_word); byte b of planes is plane b's,
+// bytes from K on hold no plane.
 template <int K>
 __device__ __forceinline__ uint32_t potmk_word(const float (&v)[8], uint32_t sgn,
-                                               uint32_t zc_half, uint32_t (&planes)[K]) {
+                                               uint32_t zc_half, uint32_t& planes) {
   constexpr int n = 1 << K;
-  uint32_t w = 0, jw = 0;
+  uint32_t a = 0, b = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const uint32_t vb = __float_as_uint(v[i]);
@@ -181,16 +186,18 @@ __device__ __forceinline__ uint32_t potmk_word(const float (&v)[8], uint32_t sgn
     const int q = ((int)(vb - (119u << 23)) >> (23 - K)) + above;
     uint32_t u = (uint32_t)min(max(q, n), 8 * n - 1);
     u = vb > zc_half ? u : 0u;
-    w |= (u >> K) << (4 * i);
-    jw |= (u & (n - 1)) << (4 * i);
+    if (i < 4) a |= u << (8 * i);
+    else b |= u << (8 * i - 32);
   }
-#pragma unroll
-  for (int b = 0; b < K; ++b) {  // bits 4i + b of jw to bit i
-    uint32_t x = (jw >> b) & 0x11111111u;
-    x = (x | (x >> 3)) & 0x03030303u;
-    x = (x | (x >> 6)) & 0x000F000Fu;
-    planes[b] = (x | (x >> 12)) & 0xFFu;
-  }
+  const uint32_t even = __builtin_amdgcn_perm(b, a, 0x06040200u);
+  const uint32_t odd = __builtin_amdgcn_perm(b, a, 0x07050301u);
+  const uint32_t w = ((even >> K) & 0x07070707u) | (((odd >> K) & 0x07070707u) << 4);
+  // bit 8c + 4h + b of x: bit b of element 4h + c; exchange index bit 0 with 3, 1 with 4
+  uint32_t x = (a & 0x0F0F0F0Fu) | ((b << 4) & 0xF0F0F0F0u);
+  uint32_t t = (x ^ (x >> 7)) & 0x00AA00AAu;
+  x ^= t ^ (t << 7);
+  t = (x ^ (x >> 14)) & 0x0000CCCCu;
+  planes = x ^ t ^ (t << 14);
   return (w ^ 0x77777777u) | (sgn & (w + 0x77777777u) & 0x88888888u);
 }
 
@@ -231,15 +238,11 @@ __device__ __forceinline__ void unpack_row(const uint32_t (&w4)[4], int lane, fl
   }
 }
 
-// The K plane bytes of each lane of a quad (code words 4h .. 4h + 3 of a row)
+// The plane bytes of each lane of a quad (byte b: plane b; code words 4h .. 4h + 3 of a row)
 // to one dword of plane j in lane j: a 4 x 4 byte transpose by two DPP moves
 // and byte permutes, for one dword store per lane. (With a byte store per lane
 // and plane 2 M rows at k = 4 took 117 us, so 108.)
-template <int K>
-__device__ __forceinline__ uint32_t quad_planes(const uint32_t (&plane)[K], int lane) {
-  uint32_t w = 0;
-#pragma unroll
-  for (int b = 0; b < K; ++b) w |= plane[b] << (8 * b);
+__device__ __forceinline__ uint32_t quad_planes(uint32_t w, int lane) {
   w = __builtin_amdgcn_perm(lane_xor_u32<1>(w), w, lane & 1 ? 0x03070105u : 0x06020400u);
   return __builtin_amdgcn_perm(lane_xor_u32<2>(w), w, lane & 2 ? 0x03020706u : 0x05040100u);
 }
@@ -284,11 +287,10 @@ __device__ __forceinline__ RowScale row_scale(float s) {
   return {s, ss, recip_rn(ss), recip_in_range(ss)};
 }
 
-// Code word and plane bytes of 8 elements.
+// Code word and plane bytes (byte b: plane b) of 8 elements.
 template <int K>
 __device__ __forceinline__ uint32_t encode_word(const float* x, const RowScale& sc, uint32_t sgn,
-                                                const CutBits& cut,
-                                                uint32_t (&plane)[K > 0 ? K : 1]) {
+                                                const CutBits& cut, uint32_t& planes) {
   float c[8];
   if (sc.fast) {
 #pragma unroll
@@ -304,7 +306,7 @@ __device__ __forceinline__ uint32_t encode_word(const float* x, const RowScale& 
       c[i] = (sc.s > 0.0f) ? clamp01((K == 0 ? fabsf(x[i]) : fabsf(x[i]) * 0.5f) / sc.s) : 0.0f;
   }
   if constexpr (K == 0) return pot4_word(c, sgn, cut.cst);
-  else return potmk_word<K>(c, sgn, cut.zc_half, plane);
+  else return potmk_word<K>(c, sgn, cut.zc_half, planes);
 }
 
 // The arguments of one encode launch.
@@ -351,10 +353,10 @@ __device__ __forceinline__ void encode_rows8(const EncodeArgs& a, int64_t row0,
       HAD ? float_signs(x)
           : sign_nibbles(__builtin_amdgcn_perm(w4[1], w4[0], 0x0B0A0908u),
                          __builtin_amdgcn_perm(w4[3], w4[2], 0x0B0A0908u));
-  uint32_t plane[K > 0 ? K : 1];
-  const uint32_t word = encode_word<K>(x, row_scale<K>(s), sgn, cut, plane);
+  uint32_t planes = 0;
+  const uint32_t word = encode_word<K>(x, row_scale<K>(s), sgn, cut, planes);
   uint32_t pq = 0;
-  if constexpr (K > 0) pq = quad_planes<K>(plane, lane);
+  if constexpr (K > 0) pq = quad_planes(planes, lane);
   if (valid) {
     const int64_t urow = row0 * a.out_stride;  // uniform part of orow
     *reinterpret_cast<uint32_t*>(a.codes_se + urow * (kDim / 2) + se_off) = word;
@@ -392,7 +394,7 @@ __global__ __launch_bounds__(kBlock) void encode_pot_kernel(const EncodeArgs a,
 // in such an order that lane l gets elements 16 (l / 16) ..+15 of row l % 16: two
 // code words. Butterflies cost about 250 VALU operations per 8 rows, this 45 per
 // 16 and 16 matrix instructions. Butterflies -> here: 131072 rows k = 0 10.5 -> 9.6,
-// k = 4 14.3 -> 13.6; 2 M rows k = 0 105 -> 86, k = 4 150 -> 132 us; up to 16384
+// k = 4 14.2 -> 13.5 (now 12.4); 2 M rows k = 0 102 -> 85, k = 4 150 -> 130 us (now 116); up to 16384
 // rows, one group per wave either way, no difference.
 typedef _Float16 half8e __attribute__((ext_vector_type(8)));
 typedef _Float16 half2e __attribute__((ext_vector_type(2)));
@@ -491,7 +493,7 @@ void encode_pot_had_kernel(const EncodeArgs a, const EncodeTables tab) {
       s = valid ? a.key_scale[orow] : 0.0f;
     }
     const RowScale sc = row_scale<K>(s);
-    uint32_t p0[K > 0 ? K : 1], p1[K > 0 ? K : 1];
+    uint32_t p0 = 0, p1 = 0;
     uint2 word;
     word.x = encode_word<K>(x, sc, float_signs(x), cut, p0);
     asm volatile("" : "+v"(word.x));  // one word at a time: registers
@@ -500,8 +502,8 @@ void encode_pot_had_kernel(const EncodeArgs a, const EncodeTables tab) {
     // plane bits against block bits, by the lane-half and the row exchange
     uint32_t t[2] = {0u, 0u};
     if constexpr (K > 0) {
-#pragma unroll
-      for (int b = 0; b < K; ++b) t[b / 2] |= (p0[b] | (p1[b] << 8)) << (16 * (b & 1));
+      t[0] = __builtin_amdgcn_perm(p1, p0, 0x05010400u);
+      t[1] = __builtin_amdgcn_perm(p1, p0, 0x07030602u);
       const auto r32 = __builtin_amdgcn_permlane32_swap(t[0], t[1], false, false);
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
