@@ -68,12 +68,17 @@ const EncodeTables& encode_tables(int mant_bits) {
 constexpr int64_t kMaxGrid = 1 << 20;
 // Workgroups of the bulk encoders: eight per CU, each wave looping over row
 // groups, and up to 32 per CU while every wave still has eight groups (2 M rows:
-// k = 0 66 -> 64 us, k = 4 118 -> 108; 131072 rows, one group per wave instead
-// of two: 7.0 -> 7.4).
+// k = 0 66 -> 64 us, k = 4 90 -> 85; 131072 rows, one group per wave instead
+// of two: 7.0 -> 7.4). Past that many rows the kernels that the memory stream bounds
+// (PoT-4 and INT8, not rotated) go back to eight, whose waves pass over memory in
+// a narrower window (8.39 M rows: k = 0 292 -> 269 us, INT8 357 -> 327; 4.19 M 133 ->
+// 131, 162 -> 155); the others keep 32 (k = 1 321 against 336, rotated k = 4 453
+// against 462).
 constexpr int64_t kEncodeGrid = 256 * 8, kEncodeGridMax = 256 * 32;
-inline uint32_t encode_grid(int64_t n_rows) {
+inline uint32_t encode_grid(int64_t n_rows, bool stream_bound) {
   const int64_t groups = (n_rows + 7) / 8, wg = kBlock / 64;
-  const int64_t cap = std::max(kEncodeGrid, std::min(kEncodeGridMax, groups / (8 * wg)));
+  int64_t cap = std::max(kEncodeGrid, std::min(kEncodeGridMax, groups / (8 * wg)));
+  if (stream_bound && groups > 8 * wg * kEncodeGridMax) cap = kEncodeGrid;
   return (uint32_t)std::min((groups + wg - 1) / wg, cap);
 }
 
@@ -394,8 +399,8 @@ __global__ __launch_bounds__(kBlock) void encode_pot_kernel(const EncodeArgs a,
 // in such an order that lane l gets elements 16 (l / 16) ..+15 of row l % 16: two
 // code words. Butterflies cost about 250 VALU operations per 8 rows, this 45 per
 // 16 and 16 matrix instructions. Butterflies -> here: 131072 rows k = 0 10.5 -> 9.6,
-// k = 4 14.2 -> 13.5 (now 12.4); 2 M rows k = 0 102 -> 85, k = 4 150 -> 130 us (now 116); up to 16384
-// rows, one group per wave either way, no difference.
+// k = 4 14.2 -> 13.5 (now 12.4); 2 M rows k = 0 102 -> 85, k = 4 150 -> 130 us
+// (now 116); up to 16384 rows, one group per wave either way, no difference.
 typedef _Float16 half8e __attribute__((ext_vector_type(8)));
 typedef _Float16 half2e __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x2e __attribute__((ext_vector_type(2)));
@@ -761,11 +766,11 @@ hipError_t launch_encode_pot(const uint16_t* k, int64_t n_rows, int64_t out_stri
   auto go = [&](auto k_tag) {
     constexpr int KK = decltype(k_tag)::value;
     if (hadamard)
-      hipLaunchKernelGGL((encode_pot_had_kernel<KK>), dim3(encode_grid((n_rows + 1) / 2)),
+      hipLaunchKernelGGL((encode_pot_had_kernel<KK>), dim3(encode_grid((n_rows + 1) / 2, false)),
                          dim3(kBlock), 0, stream, a, tab);
     else
-      hipLaunchKernelGGL((encode_pot_kernel<KK>), dim3(encode_grid(n_rows)), dim3(kBlock), 0,
-                         stream, a, tab);
+      hipLaunchKernelGGL((encode_pot_kernel<KK>), dim3(encode_grid(n_rows, KK == 0)),
+                         dim3(kBlock), 0, stream, a, tab);
   };
   switch (tab.mant_bits) {
     case 0: go(std::integral_constant<int, 0>{}); break;
@@ -783,7 +788,7 @@ hipError_t launch_encode_int8(const uint16_t* k, int64_t n_rows, int64_t out_str
                               hipStream_t stream) {
   if (n_rows == 0) return hipSuccess;
   const __half* kh = reinterpret_cast<const __half*>(k);
-  const dim3 grid(encode_grid(n_rows));
+  const dim3 grid(encode_grid(n_rows, !hadamard));
   if (hadamard)
     hipLaunchKernelGGL((encode_int8_kernel<true>), grid, dim3(kBlock), 0, stream, kh, n_rows,
                        out_stride, key_scale, codes);
