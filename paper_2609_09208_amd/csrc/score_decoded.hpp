@@ -8,10 +8,12 @@
 // Decoded weights (kScoreDs4a): element m is sigma (1 + j / 2^k) 2^(-8 - e),
 // the fp16 number with sign bit sigma, exponent field 7 - e (the complement of
 // the code's exponent bits) and the mantissa bits j on top of its mantissa; the zero code
-// (e = 7, j = 0) is exponent field 0: zero. Two elements take 4 VALU operations
-// (6 with a mantissa). q^ 2^8 is an exact fp16 number, v_mfma_f32_16x16x32_f16
-// multiplies and sums, and 2^(k + F) makes the result the int32 score at
-// head-room F: exact, since with unit 2^(F - 6) every partial sum is an integer
+// (e = 7, with j taken as 0) is exponent field 0: zero. Two elements take 4 VALU
+// operations (6 with a mantissa; and about 19 per set that clear the mantissa bits
+// of zero codes, whose planes may hold anything: 0.1 us of a call of one tile per
+// wave, 6.87 -> 7.02 us at k = 1, B = 1, T = 1024). q^ 2^8 is an exact fp16 number,
+// v_mfma_f32_16x16x32_f16 multiplies and sums, and 2^(k + F) makes the result the
+// int32 score at head-room F: exact, since with unit 2^(F - 6) every partial sum is an integer
 // below 64 * 127 * 1984 < 2^24. (One key per lane on v_dot4 / v_dot2 took 414
 // VALU lane-operations per key at k = 0 and 817 at k = 4 and, like the other
 // engines, a transpose through LDS.)
@@ -43,6 +45,22 @@ __device__ __forceinline__ half8 decode_weights(uint32_t w, uint32_t j) {
     v[n] |= (w << (12 - 4 * n)) & 0x80008000u;
   }
   return __builtin_bit_cast(half8, make_uint4(v[0], v[1], v[2], v[3]));
+}
+
+// Bit 4i + c set where element 4i + c, nibble i of the transposed code dword
+// c4[c], is the zero code: adding 1 to the exponent bits (sign cleared, so no
+// carry between nibbles) sets bit 3 for exponent 7, and the dwords' bits merge in
+// the order of the plane bits.
+__device__ __forceinline__ uint32_t zero_codes(const uint32_t (&c4)[4]) {
+  uint32_t y[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) y[c] = (c4[c] & 0x77777777u) + 0x11111111u;
+  uint32_t z = y[3];
+  constexpr uint32_t kSelectTable = 0xCA;  // a ? b : c, bit by bit
+#pragma unroll
+  for (int c = 2; c >= 0; --c)
+    z = __builtin_amdgcn_bitop3_b32(0x11111111u << c, y[c] >> (3 - c), z, kSelectTable);
+  return z;
 }
 
 // Place of element m of a half in the fp16 query operand: dword c, nibble nib,
@@ -104,13 +122,19 @@ __device__ __forceinline__ f32x4 score_set_decoded(const uint32_t (&w)[4], const
   } else {
     transpose_codes(w, c4);
   }
+  uint32_t pm[K > 0 ? K : 1];  // plane bits, 0 for zero codes
+  if constexpr (K > 0) {
+    const uint32_t z = zero_codes(c4);
+#pragma unroll
+    for (int b = 0; b < K; ++b) pm[b] = pl[b] & ~z;
+  }
   f32x4 d = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     uint32_t j = 0;
 #pragma unroll
     for (int b = 0; b < K; ++b) {  // bit 4i + c of plane b to bit b of nibble i
-      const uint32_t x = c >= b ? pl[b] >> (c >= b ? c - b : 0) : pl[b] << (c < b ? b - c : 0);
+      const uint32_t x = c >= b ? pm[b] >> (c >= b ? c - b : 0) : pm[b] << (c < b ? b - c : 0);
       j |= x & (0x11111111u << b);
     }
     d = __builtin_amdgcn_mfma_f32_16x16x32_f16(decode_weights<K>(c4[c], j), q.h[c], d, 0, 0, 0);

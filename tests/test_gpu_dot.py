@@ -11,6 +11,7 @@ forced splits and degenerate rows.
 import numpy as np
 import pytest
 
+import oracle
 from parity_util import assert_pot_parity, gpu_encode, gpu_pot_decode
 from workloads import make_decode_inputs
 
@@ -68,3 +69,28 @@ def test_dot_scores_equal_shift_path(k):
     assert np.array_equal(a["scores"], b["scores"])
     assert np.array_equal(a["m_final"], b["m_final"])
     assert float(np.abs(a["out"] - b["out"]).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("k,waves", [(1, 16), (2, 16), (3, 16), (4, 16), (1, 4), (4, 4)])
+def test_dot_zero_codes_ignore_their_planes(k, waves):
+    # e = 7 is zero whatever its sign bit and mantissa bits hold (the encoder writes zeros
+    # there, another producer of the cache may not): in every place of a row, all at once too
+    d = make_decode_inputs(370 + k, B=1, Hq=8, Hkv=1, T=300)
+    se, cm, sc = gpu_encode(d["k_bits"].reshape(-1, 64), k)
+    rng = np.random.default_rng(k)
+    nib = np.stack([se & 15, se >> 4], axis=-1).reshape(-1, 64)
+    zero = rng.random(nib.shape) < 0.2
+    zero[:64] = np.eye(64, dtype=bool)
+    zero[64] = True
+    nib = np.where(zero, 7 | (nib & 8), nib).astype(np.uint8)
+    se = nib[:, 0::2] | (nib[:, 1::2] << 4)
+    bits = np.unpackbits(cm.reshape(-1, k, 8), axis=-1, bitorder="little") | zero[:, None, :]
+    cm = np.packbits(bits, axis=-1, bitorder="little").reshape(-1, 8 * k)
+    want = oracle.pot_decode(d["q"], se, cm, sc, d["v_bits"], d["t_cap"], d["kv_head_of_q"], 1, 8, 1,
+                             300, mant_bits=k)
+    for engine in ("dot", "sac"):
+        g = gpu_pot_decode(d, se, cm, sc, mant_bits=k, engine=engine, force_splits=1,
+                           wg_waves=4 if waves == 4 else (16 if engine == "dot" or k <= 2 else 12))
+        assert np.array_equal(g["scores"], want["scores"]), engine
+        assert np.array_equal(g["m_final"], want["m_final"]), engine
+        assert float(np.abs(g["out"] - want["out"]).max()) <= 2e-3, engine
