@@ -550,21 +550,35 @@ __device__ __forceinline__ void merge_splits(const DecodeArgs& a, int64_t seq, i
 
 // VF: value format, 0 fp16 values, 1 INT8 values, 2 INT8 values with the
 // power-of-two weights of eq. logsm.
-// CU-wide kernels: value blocks (of two, 16 registers each) loaded before the
-// scores; the others are loaded after them, since held meanwhile they would
-// not fit the 128 registers of four waves per SIMD (shift-accumulate at k = 3,
-// 4: 168 of three) without spills. A wave has about 4 us per tile there and
-// can wait for a load; the four-wave kernels load all of them first.
-template <int MODE, int K>
-constexpr int kEarlyValueBlocks = MODE == kScorePot    ? (K == 2 ? 0 : 1)
-                                  : MODE == kScoreDs4a ? (K >= 1 ? 0 : 1)
-                                                       : 2;
+// Value blocks (of two, 16 registers each; INT8 values 8) loaded before the
+// scores; the others are loaded after them, since held meanwhile they would not
+// fit the kernel's registers without spills. CU-wide kernels: 128 registers at
+// four waves per SIMD (shift-accumulate at k = 3, 4: 168 at three); a wave has
+// about 4 us per tile there and can wait for a load. The four-wave kernels keep
+// the same budget, so that as many of their waves share a SIMD: without it they
+// took 130 to 176 registers, three waves (two at k = 4). B * Hkv = 1024 in graph
+// replays, T = 64 and 1024, us: PoT-4 10.2 -> 6.9 and 35.0 -> 32.1, PoT-M1 10.8 ->
+// 7.6, PoT-M4 44.3 -> 40.4 at T = 1024, decoded M1 10.9 -> 7.1 and 36.0 -> 31.8, M1
+// with INT8 values 11.5 -> 7.6 and 33.5 -> 30.9, INT8 keys 9.1 -> 6.3 and 36.3 ->
+// 34.0; one tile per wave waits for the late values (PoT-M1, 260 units, T = 64 5.8
+// -> 6.1).
+template <int MODE, int K, int VF, bool POOL>
+constexpr int kEarlyValueBlocks =
+    POOL ? (MODE == kScorePot ? (K == 2 ? 0 : 1) : MODE == kScoreDs4a ? (K >= 1 ? 0 : 1) : 2)
+    : K == 0            ? 2
+    : VF != 0           ? (K == 2 ? 1 : 2)
+    : MODE == kScorePot ? (K == 3 ? 2 : K == 2 ? 0 : 1)
+                        : 0;
+
+// Waves per SIMD that the registers have to allow.
+template <int MODE, int K, int VF>
+constexpr int kSimdWaves = kPoolWaves<MODE, K, VF> > 0 ? kPoolWaves<MODE, K, VF> / 4 : 1;
 
 // NW: waves per workgroup, kWaves or kPoolWaves<MODE, K, VF> (the CU-wide
 // variant, whose waves take their tiles from the counter sm.next).
 template <int MODE, int G, int K, bool DEBUG, int VF, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
-    NW > kWaves ? NW / 4 : 1))) void decode_kernel(const DecodeArgs a) {
+    kSimdWaves<MODE, K, VF>))) void decode_kernel(const DecodeArgs a) {
   constexpr bool kPool = NW > kWaves;
   constexpr int kBlk = 64 * NW;
   __shared__ DecodeSmem<MODE, NW> sm;
@@ -647,7 +661,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   // second set of value registers, one tile further ahead, made the engines
   // with short scores slower: PoT-4 decoded to weights 211 us against 200 at
   // B = 64, T = 32768, 34.5 against 33.3 at B = 16, T = 16384.)
-  constexpr int kEarlyV = kPool ? kEarlyValueBlocks<MODE, K> : 2;
+  constexpr int kEarlyV = kEarlyValueBlocks<MODE, K, VF, kPool>;
   ValRegs<V8> vr;
   uint4 ksc[2];
   auto load_tile_scales = [&](int jt) {
@@ -723,9 +737,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   if constexpr (MODE == kScorePot) qop = load_plane_query<G>(sm.qh, sm.ql, a.frac_bits);
   else if constexpr (MODE == kScoreInt8) qop = load_byte_query<G>(sm.qb);
   else qop = load_half_query<G>(sm.qh, lane);
-  // CU-wide decoded weights with a mantissa: the 16 registers of the operand are
-  // read again from LDS in each tile, so that the values can have them meanwhile
-  constexpr bool kReloadQ = MODE == kScoreDs4a && K > 0 && kPool;
+  // decoded weights with a mantissa: the 16 registers of the operand are read
+  // again from LDS in each tile, so that the values can have them meanwhile
+  constexpr bool kReloadQ = MODE == kScoreDs4a && K > 0;
   // decoded weights: their sums to the int32 score at head-room F
   const float to_int = MODE == kScoreDs4a ? __builtin_amdgcn_ldexpf(1.0f, a.frac_bits + K) : 1.0f;
 
@@ -761,7 +775,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
           if constexpr (K > 0) plane_bits<MODE, K>(ks, i, pl);
           if constexpr (MODE == kScorePot) d[i] = score_set<K>(w, pl, m22, qop);
           else d[i] = score_set_decoded<K>(w, pl, qop, to_int);
-          if constexpr (MODE == kScoreDs4a && K > 0 && kPool) asm volatile("" : "+v"(d[i]));
+          if constexpr (kReloadQ) asm volatile("" : "+v"(d[i]));
         } else if constexpr (MODE == kScoreInt8) {
           d[i] = score_set_int8(ks.k[i], qop);
         } else {

@@ -82,6 +82,25 @@ def test_pool_rejects_other_wave_counts():
             gpu_pot_decode(d, se, cm, sc, force_splits=1, wg_waves=bad)
 
 
+# the four-wave kernels of every engine and mantissa width, ragged, with several tiles a wave:
+# what they load before and after the scores differs with the width
+@pytest.mark.parametrize("engine,k", [("sac", 0), ("sac", 1), ("sac", 2), ("sac", 3), ("sac", 4),
+                                      ("ds4a", 0), ("dot", 1), ("dot", 2), ("dot", 3), ("dot", 4)])
+@pytest.mark.parametrize("G", [1, 8])
+def test_four_waves_every_mantissa_width(engine, k, G):
+    d = make_decode_inputs(700 + 10 * k + G, B=2, Hq=2 * G, Hkv=2, T=1237)
+    assert_pot_parity(d, mant_bits=k, engine=engine, force_splits=2, wg_waves=4)
+
+
+@pytest.mark.parametrize("k", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("pow2", [False, True])
+def test_four_waves_int8_values(k, pow2):
+    d = make_decode_inputs(760 + k, B=2, Hq=16, Hkv=2, T=1237)
+    assert_v8_parity(d, mant_bits=k, force_splits=2, pow2=pow2, wg_waves=4)
+    if k == 0:
+        assert_v8_parity(d, engine=1, force_splits=2, pow2=pow2, wg_waves=4)
+
+
 # the other engines' CU-wide variants: decoded-code engines over fp16 values
 @pytest.mark.parametrize("engine,k,waves", [("ds4a", 0, 12), ("dot", 1, 16), ("dot", 4, 16)])
 def test_pool_decoded_code_engines(engine, k, waves):
