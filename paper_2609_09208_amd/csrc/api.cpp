@@ -119,37 +119,82 @@ int device_cus() {
 }
 
 // How a decode call is split: (batch, kv head) units times key splits, on
-// four-wave or CU-wide (pw waves, 0: the engine has none) workgroups.
+// four-wave or CU-wide (pw waves, 0: the engine has none) workgroups. Figures:
+// graph replays, us, eight heads to a unit, PoT-4 over fp16 values unless said.
 //  - Up to one unit per CU: CU-wide workgroups and as many splits as give every
 //    CU at most one. More splits cost a second round of prologues, fewer leave
 //    CUs idle; four-wave workgroups take longer over the prologue (two heads'
-//    queries per wave) and the merge. PoT-4, graph replays, us: B = 16 (64
-//    units) T = 4096 14.4 with 4 splits, 15.1 with 8 on four waves, 16.4 with 4;
-//    B = 40 (160 units) T = 16384 70.2 with 1, 75 with 3, 72.8 with 3 on four
-//    waves; B = 6 T = 16384 17.4 with 10, 18.0 with 8, 18.3 with 32 on four.
+//    queries per wave) and the merge. 64 units T = 4096 11.7 with 4 splits, 14.7
+//    with 8 on four waves, 15.3 with 4; 24 units T = 16384 16.1 with 10, 18.4 with
+//    32 on four waves; the fp16 comparator (four waves) at 96 units 69.4, 78.0
+//    with 4.
+//  - That rule rounds down: from half the CUs on it leaves one workgroup per unit
+//    and the other CUs without work. For long ranges (from 12288 keys; at 8192 one
+//    workgroup is as fast, 132 units 35.2 against 34.9) the fp16 comparator and the
+//    engines that are bound by their issue take three splits of four-wave
+//    workgroups up to two thirds of the CUs (T = 16384, 160 units: PoT-M1 80.4 ->
+//    76.5, PoT-M4 108 -> 93, fp16 119.9 -> 108.4), PoT-4 and INT8 keys over fp16 values,
+//    whose stream decides sooner, up to three fifths (132 units 68.6 -> 63.4, 152
+//    72.2 -> 70.3, 168 75.2 and 77.8). With INT8 values, where a unit takes a CU the
+//    longest, three to four workgroups per CU up to three quarters (132 units 68.0
+//    -> 55.1, 160 69.8 -> 61.2, 176 70.7 -> 66.9, 192 72.8 -> 67.7; T = 8192 38.0 ->
+//    32.5 and 39.6 -> 40.7).
 //  - Where every wave of one workgroup has at most one 64-key tile, one split
-//    and no merge kernel: up to 768 keys (T = 512, B = 1 7.9 against 9.3 with
-//    two splits, B = 64 9.3 against 10.8), and up to 16 tiles on 16 waves if a
-//    quarter of the CUs has a unit (T = 1024, B = 16 10.4 against 10.8 with four
-//    splits, B = 32 10.7 against 12.2 with two; B = 4 9.7 against 9.5).
+//    and no merge: up to 768 keys (T = 512, 4 units 5.8 against 6.8 with two
+//    splits, 64 units 6.1 against 7.2; T = 768, 4 units 6.6 against 6.9 with three;
+//    on 12 waves PoT-M4 7.4 and 7.6 at 512, but 8.9 and 7.9 at 768), and up to 16
+//    tiles on 16 waves if a quarter of the CUs has a unit (T = 1024: 16 units 7.6
+//    against 7.2 with four splits, 64 units 7.8 and 7.8, 128 units 8.0 against 9.0
+//    with two).
 //  - More units than CUs: one split of four-wave workgroups, several of which
-//    share a CU, for up to 8191 keys (B = 128: T = 256 10.1 against 12.7
-//    CU-wide, T = 4096 58.1 against 59.1; B = 80 43.3 against 48.7); CU-wide
-//    above, whose waves claim tiles (B = 512, T = 4096 222 against 226), in
-//    three splits where the second round of one would leave over 30% of the CUs
-//    idle (B = 80, T = 16384 143 against 165).
-constexpr int kShortKeys = 768, kLongKeys = 8192;
+//    share a CU, for up to 8191 keys (512 units: T = 256 8.1 against 10.3 CU-wide,
+//    T = 4096 57.4 against 59.9; 320 units 41.8 against 47.1); CU-wide above, whose
+//    waves claim tiles (512 units, T = 16384 205 against 208), in three splits where
+//    the second round of one would leave over 30% of the CUs idle (320 units, T =
+//    16384 145 against 159).
+constexpr int kShortKeys = 768, kLongKeys = 8192, kSpreadKeys = 12288;
 struct Launch {
   Plan plan;
   bool pool;
 };
 
-Launch plan_launch(long units, int T, int pw, int cus, int bound) {
+// Splits of four-wave workgroups, over two and up to four to a CU, that leave the
+// smallest share of the CUs' places empty.
+int spread_splits(long units, long cus) {
+  int best = 1;
+  long best_used = 0, best_places = 1;
+  for (long S = 2 * cus / units + 1; S * units <= 4 * cus; ++S) {
+    const long used = S * units, places = (used + cus - 1) / cus * cus;
+    if (used * best_places > best_used * places) {
+      best = (int)S;
+      best_used = used;
+      best_places = places;
+    }
+  }
+  return best;
+}
+
+// What of an engine the plan depends on.
+struct PlanEngine {
+  int pw;            // waves of its CU-wide workgroups, 0: none
+  bool int8_values;
+  bool light;        // PoT-4 or INT8 keys over fp16 values: the stream decides even on one CU
+};
+
+Launch plan_launch(long units, int T, const PlanEngine& e, int cus, int bound) {
+  const int pw = e.pw;
   const bool one_tile = pw > 0 && (T <= kShortKeys || (T <= pw * 64 && 4 * units >= cus));
   int S = 1;
   bool pool = pw > 0;
   if (units <= cus) {
     if (!one_tile) S = (int)(cus / units);
+    if (S == 1 && T >= kSpreadKeys) {
+      if (e.int8_values ? 4 * units <= 3L * cus
+                        : (e.light ? 5 * units <= 3L * cus : 3 * units <= 2L * cus)) {
+        S = e.int8_values ? spread_splits(units, cus) : 3;
+        pool = false;
+      }
+    }
   } else {
     pool = pool && T >= kLongKeys;
     if (pool && 10 * units < 14L * cus) S = 3;
@@ -158,9 +203,10 @@ Launch plan_launch(long units, int T, int pw, int cus, int bound) {
 }
 
 // CU-wide workgroups claim their tiles from a counter when the grid fills the
-// chip and every wave has over four (long streams drift apart: PoT-4, B = 64, T
-// = 32768 201 us against 206 in fixed order; at four tiles per wave 33.8
-// against 33.5). In fixed order the sums are the same from call to call.
+// chip and every wave has over four (long streams drift apart, graph replays of 256
+// units at T = 32768: PoT-4 203 us against 209 in fixed order, PoT-M4 247 against
+// 259, PoT-4 over INT8 values 145 against 163; four tiles per wave, 64 units at T =
+// 16384: 33.2 against 32.9). In fixed order the sums are the same from call to call.
 bool claims_tiles(long units, const Plan& p, int pw, int cus) {
   return units * p.n_splits >= cus && p.split_len > 4 * pw * 64;
 }
@@ -266,8 +312,9 @@ pot_status decode_common(int mode, int mant_bits, DecodeArgs& a, const int32_t* 
     p = plan_from_count(T, force);
     pool = pw > 0 && want != kBlock / 64 && (want == pw || units * p.n_splits <= cus);
   } else {
-    const Launch l = plan_launch(units, T, want == kBlock / 64 ? 0 : pw, cus,
-                                 plan_bound(B, Hkv, T).n_splits);
+    const PlanEngine e{want == kBlock / 64 ? 0 : pw, v8,
+                       mbits == 0 && mode != kScoreFp16 && !v8};
+    const Launch l = plan_launch(units, T, e, cus, plan_bound(B, Hkv, T).n_splits);
     p = l.plan;
     pool = pw > 0 && (want == pw || l.pool);
   }

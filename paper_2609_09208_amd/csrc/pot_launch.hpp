@@ -56,11 +56,11 @@ enum ScoreMode : int { kScorePot = 0, kScoreInt8 = 1, kScoreFp16 = 2, kScoreDs4a
 // Splits that the last workgroup of a unit merges (CU-wide workgroups); more go
 // to the combine kernel, whose workgroups share the reading: one CU gets about
 // 32 KB per us of partials that other XCDs wrote. PoT-4 graph replays, us, in
-// the kernel and with the combine kernel: B = 1, T = 1024 (4 splits) 7.5 and
-// 8.2, T = 4096 (16) 8.0 and 8.9, T = 8192 (32) 8.3 and 9.0, T = 32768 (64) 12.8
-// and 10.7; B = 4, T = 4096 (16) 8.6 and 9.6. A launch of the combine kernel also
-// costs the host 3 us. Four-wave workgroups, with two heads to a wave, took 9.1
-// and 8.2 at 4 splits of fp16 keys and keep the combine kernel.
+// the kernel and with the combine kernel: 4 units, T = 1024 (4 splits) 6.8 and
+// 7.6, T = 4096 (16) 7.3 and 7.7, T = 8192 (32) 7.8 and 7.9, T = 16384 (64) 9.0 and
+// 8.4, T = 32768 (64) 10.1 and 9.7; 16 units, T = 4096 (16) 7.8 and 8.4. A launch of the
+// combine kernel also costs the host 3 us. Four-wave workgroups, with two heads to
+// a wave, took 9.1 and 8.2 at 4 splits of fp16 keys and keep the combine kernel.
 constexpr int kMaxMergedSplits = 32;
 
 // Everything one decode launch needs. Passed by value as the kernel argument.
@@ -117,9 +117,9 @@ struct DecodeArgs {
 // allow (512 per lane and SIMD): the shift-accumulate kernels 4 at k <= 2
 // and 3 at k = 3, 4 (fp16 or INT8 values); the decoded-code engines 4, or 3
 // for PoT-4 bytes over fp16 values or with power-of-two weights; the INT8
-// comparator 3. The fp16 comparator has none: at its two waves per SIMD a
-// CU-wide workgroup of 8 waves measured slower than two four-wave ones
-// (B = 64, T = 32768: 339.6 against 318.4 us per call).
+// comparator 3. The fp16 comparator has none: with 12 waves it was no faster on
+// long ranges (graph replays, us: 256 units T = 32768 322 against 323 on four
+// waves, 64 units 86.2 and 85.8, 4 units 13.2 and 12.3).
 constexpr int pool_waves(int mode, int mant_bits, int vf) {
   return mode == kScorePot    ? (mant_bits <= 2 ? 16 : 12)
          : mode == kScoreDs4a ? ((mant_bits > 0 || vf == 1) ? 16 : 12)

@@ -1,8 +1,9 @@
 """The launch plan's cases at their borders: one split of CU-wide workgroups up
 to 768 keys (and up to 16 tiles when a quarter of the CUs has a unit), splits
 that give each CU at most one workgroup, one split of four-wave workgroups above
-one unit per CU and CU-wide ones from 8192 keys on, in three splits just above.
-Each call is compared with four-wave workgroups at one split on the same cache:
+one unit per CU and CU-wide ones from 8192 keys on, in three splits just above;
+between half the CUs and all of them more splits of four-wave workgroups for long
+ranges. Each call is compared with four-wave workgroups at one split on the same cache:
 scores and maxima bit-identical, O to fp32 rounding. A wave whose first tile
 holds the appended row loads it after the others: the appended calls go over
 lengths that put that row in every wave's place.
@@ -57,6 +58,46 @@ def test_plan_above_one_unit_per_cu(B, T):
         outs.append((out.cpu().numpy(), m.cpu().numpy(), dbg.n_splits, dbg.wg_waves))
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         want = {(33, 8191): (1, 4), (33, 8192): (3, 16), (46, 8192): (1, 16)}[(B, T)]
+        assert outs[0][2:] == want
+    assert np.array_equal(outs[0][1], outs[1][1])
+    assert np.abs(outs[0][0] - outs[1][0]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("units,T,k,values,want", [
+    (136, 12287, 0, "fp16", (1, 16)), (136, 12288, 0, "fp16", (3, 4)), (152, 12288, 0, "fp16", (3, 4)),
+    (160, 12288, 0, "fp16", (1, 16)), (168, 12288, 1, "fp16", (3, 4)), (176, 12288, 4, "fp16", (1, 12)),
+    (128, 12288, 0, "int8", (2, 16)), (136, 12288, 0, "int8", (7, 4)), (160, 12288, 1, "int8", (6, 4)),
+    (192, 12288, 0, "int8", (4, 4)), (200, 12288, 0, "int8", (1, 16))])
+def test_plan_between_half_the_cus_and_all(units, T, k, values, want):
+    # one CU-wide workgroup per unit would leave up to half of the CUs without work
+    B, Hkv = units // 8, 8
+    cap = -(-T // 8) * 8
+    d = make_decode_inputs_device(78, B, Hkv, Hkv, T, DEV, t_cap=cap)
+    fmt = pa.make_format(k)
+    c = pa.alloc_pot_cache(B, Hkv, cap, k, DEV)
+    pa.pot_encode_keys(fmt, d["k"], units * cap, 1, 0, c["key_scale"], c["codes_se"], c["codes_m"])
+    v = (pa.alloc_value_cache_int8(B, Hkv, cap, DEV) if values == "int8"
+         else (pa.alloc_value_cache(B, Hkv, cap, DEV),))
+    (pa.pot_store_values_int8 if values == "int8" else pa.pot_store_values)(d["v"], units, cap, cap,
+                                                                            0, *v)
+    ws = pa.alloc_workspace(pa.pot_decode_workspace_bytes(B, Hkv, Hkv, T), DEV)
+    outs = []
+    for splits, waves in ((0, 0), (1, 4)):
+        dbg = pa.pot_debug()
+        dbg.force_splits, dbg.force_wg_waves = splits, waves
+        m = torch.empty((B, Hkv), dtype=torch.int32, device=DEV)
+        dbg.m_final = m.data_ptr()
+        out = torch.empty((B, Hkv, 64), dtype=torch.float32, device=DEV)
+        a = (cap, d["kv_head_of_q"], B, Hkv, Hkv, T, out, ws)
+        if values == "int8":
+            pa.pot_decode_attention_v8(fmt, 0, d["q"], c["codes_se"], c["codes_m"], c["key_scale"],
+                                       *v, *a, dbg=dbg)
+        else:
+            pa.pot_decode_attention(fmt, d["q"], c["codes_se"], c["codes_m"], c["key_scale"], *v, *a,
+                                    dbg=dbg)
+        torch.cuda.synchronize()
+        outs.append((out.cpu().numpy(), m.cpu().numpy(), dbg.n_splits, dbg.wg_waves))
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert outs[0][2:] == want
     assert np.array_equal(outs[0][1], outs[1][1])
     assert np.abs(outs[0][0] - outs[1][0]).max() <= 1e-5
