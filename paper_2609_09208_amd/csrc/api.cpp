@@ -150,8 +150,8 @@ int device_cus() {
 //    share a CU, for up to 8191 keys (512 units: T = 256 8.1 against 10.3 CU-wide,
 //    T = 4096 57.4 against 59.9; 320 units 41.8 against 47.1); CU-wide above, whose
 //    waves claim tiles (512 units, T = 16384 205 against 208), in three splits where
-//    the second round of one would leave over 30% of the CUs idle (320 units, T =
-//    16384 145 against 159).
+//    those make at most four rounds instead of two whole ones (T = 16384, 320 units
+//    145 against 159 with one; 352 units, a fifth round, 168 against 162).
 constexpr int kShortKeys = 768, kLongKeys = 8192, kSpreadKeys = 12288;
 struct Launch {
   Plan plan;
@@ -197,7 +197,7 @@ Launch plan_launch(long units, int T, const PlanEngine& e, int cus, int bound) {
     }
   } else {
     pool = pool && T >= kLongKeys;
-    if (pool && 10 * units < 14L * cus) S = 3;
+    if (pool && 3 * units <= 4L * cus) S = 3;
   }
   return {plan_from_count(T, std::min(S, bound)), pool};
 }

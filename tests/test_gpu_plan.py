@@ -35,7 +35,7 @@ def test_plan_matches_one_split_of_four_waves(B, Hq, Hkv, T, k, splits, waves):
     assert np.abs(a["out"] - b["out"]).max() <= 1e-5
 
 
-@pytest.mark.parametrize("B,T", [(33, 8191), (33, 8192), (46, 8192)])
+@pytest.mark.parametrize("B,T", [(33, 8191), (33, 8192), (42, 8192), (43, 8192), (46, 8192)])
 def test_plan_above_one_unit_per_cu(B, T):
     Hq = Hkv = 8
     d = make_decode_inputs_device(77, B, Hq, Hkv, T, DEV, t_cap=8192)
@@ -57,7 +57,8 @@ def test_plan_above_one_unit_per_cu(B, T):
         torch.cuda.synchronize()
         outs.append((out.cpu().numpy(), m.cpu().numpy(), dbg.n_splits, dbg.wg_waves))
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
-        want = {(33, 8191): (1, 4), (33, 8192): (3, 16), (46, 8192): (1, 16)}[(B, T)]
+        want = {(33, 8191): (1, 4), (33, 8192): (3, 16), (42, 8192): (3, 16), (43, 8192): (1, 16),
+                (46, 8192): (1, 16)}[(B, T)]
         assert outs[0][2:] == want
     assert np.array_equal(outs[0][1], outs[1][1])
     assert np.abs(outs[0][0] - outs[1][0]).max() <= 1e-5
