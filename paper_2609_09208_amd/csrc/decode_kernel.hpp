@@ -30,8 +30,10 @@
 //     2^(M_old - M_new).
 //  4. A.V on the matrix cores: P (16 rows = 8 heads x {fp16 high part, fp16
 //     low part} of p = 2^(x - M + 12)) times V (fp16) with
-//     v_mfma_f32_16x16x32_f16, fp32 accumulation; the sums l of p are per
-//     lane in fp32. The value cache is stored token-interleaved
+//     v_mfma_f32_16x16x32_f16, fp32 accumulation; the sums l of p are one
+//     more column of it, values of 1 (the same parts, rounded and dropped
+//     alike: constant values come back constant), or, with INT8 values whose
+//     weights are scaled, per lane in fp32. The value cache is stored token-interleaved
 //     ([t/8][d][t%8]) so a lane's 16-byte load is exactly its B fragment.
 // With one split the workgroup writes O directly; otherwise it writes its
 // (M_s, l_s, o_s), and the last workgroup of a unit, or for many splits a small
@@ -611,11 +613,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   const bool appends = (MODE == kScorePot || MODE == kScoreDs4a) && a.app_k != nullptr &&
                        split == a.n_splits - 1;  // uniform per workgroup
   int gref = 0;
-  float lsum = 0.0f;  // this lane's sum of the weights
+  float lsum = 0.0f;  // INT8 values: this lane's sum of the unscaled weights
 
-  float4v acc[4];
+  // acc[4], fp16 values: the sums of the weights, as one more column of P.V
+  constexpr int kAcc = V8 ? 4 : 5;
+  float4v acc[kAcc];
 #pragma unroll
-  for (int nb = 0; nb < 4; ++nb) acc[nb] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int nb = 0; nb < kAcc; ++nb) acc[nb] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
   int m_run = INT_MIN;
   // -1 kept opaque so that p - hi stays one fma_mix reading hi as fp16
   float neg_one = -1.0f;
@@ -850,7 +854,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
     const float f = (m_run == INT_MIN) ? 0.0f : __builtin_amdgcn_ldexpf(1.0f, m_run - m_new);
     const int arow = lane & 15, acol = lane >> 4;
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
+    for (int nb = 0; nb < kAcc; ++nb) {
       float4v d = float4v{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj)
@@ -858,7 +862,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
                                                  0, 0, 0);
       acc[nb] = d;
     }
-    lsum *= f;
+    if constexpr (V8) lsum *= f;
     m_run = m_new;
   };
 
@@ -894,10 +898,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
         p0 = __builtin_amdgcn_exp2f(xv[2 * i] + bias);
         p1 = __builtin_amdgcn_exp2f(xv[2 * i + 1] + bias);
       }
-      lsum += p0;
-      lsum += p1;
       if constexpr (V8) {
         // the softmax sum takes p; A.V takes p 2^(g_ref - g) (exact scaling)
+        lsum += p0;
+        lsum += p1;
         const uint32_t gw = (i < 2) ? vr.g.x : vr.g.y;
         p0 = __builtin_amdgcn_ldexpf(p0, gref - (int)(int8_t)(gw >> (16 * (i & 1))));
         p1 = __builtin_amdgcn_ldexpf(p1, gref - (int)(int8_t)(gw >> (16 * (i & 1) + 8)));
@@ -922,12 +926,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
       if constexpr (V8) return int8_value_fragment(vr.f[kb][nb]);
       else return __builtin_bit_cast(half8, vr.f[kb][nb]);
     };
+    auto weight_sums = [&]() {
+      if constexpr (!V8) {
+        half8 ones;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ones[i] = (_Float16)1.0f;
+        acc[4] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af0, ones, acc[4], 0, 0, 0);
+        acc[4] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af1, ones, acc[4], 0, 0, 0);
+      }
+    };
+    // they do not wait for the values: before them, where the registers allow (PoT-4, 4
+    // to 64 units, T <= 1024: 1.0% of a call over sums per lane, 1.6% after the values)
+    constexpr bool kSumsLast = MODE == kScorePot && K == 2;
+    if constexpr (!kSumsLast) weight_sums();
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb)
       acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af0, bfrag(0, nb), acc[nb], 0, 0, 0);
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb)
       acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af1, bfrag(1, nb), acc[nb], 0, 0, 0);
+    if constexpr (kSumsLast) weight_sums();
   };
 
   // The hot loop runs the tiles that do not raise any head's maximum; a tile
@@ -964,16 +982,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   }
 
   // ---- merge the waves ------------------------------------------------------
-  // sum of the weights over the 8 lanes that formed a head's
-  lsum += dpp_move<kDppRowRor8>(lsum);
-  {
-    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(lsum), __float_as_uint(lsum),
-                                                      false, false);
-    lsum = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
-    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum),
-                                                      false, false);
-    lsum = __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
-  }
   // Only the sums of waves that had a tile are merged, in whole groups of four (a
   // wave of such a group without tiles has zero sums and factor 0). Rows h and h + 8 of
   // the products (weights' high and low parts) sit in the two halves of the
@@ -990,9 +998,24 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
         if (lane < 32) sm.wo[wave][4 * grp + r][16 * nb + row] = sum;
       }
   }
-  if (lane < 8) {
-    sm.wm[wave][lane] = m_run;
-    sm.wl[wave][lane] = lsum;
+  if (lane < 8) sm.wm[wave][lane] = m_run;
+  if constexpr (V8) {
+    // sum of the weights over the 8 lanes that formed a head's
+    lsum += dpp_move<kDppRowRor8>(lsum);
+    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(lsum), __float_as_uint(lsum),
+                                                      false, false);
+    lsum = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
+    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum),
+                                                      false, false);
+    lsum = __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+    if (lane < 8) sm.wl[wave][lane] = lsum;
+  } else {
+    // rows 4 grp + r, the same in every column: column r hands over row r
+    const float sum = row == 0 ? acc[4][0] : row == 1 ? acc[4][1] : row == 2 ? acc[4][2] : acc[4][3];
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum),
+                                                    false, false);
+    if (lane < 32 && row < 4)
+      sm.wl[wave][4 * grp + row] = __uint_as_float(h[0]) + __uint_as_float(h[1]);
   }
   __syncthreads();
 
