@@ -568,7 +568,7 @@ template <int MODE, int K, int VF, bool POOL>
 constexpr int kEarlyValueBlocks =
     POOL ? (MODE == kScorePot ? (K == 2 ? 0 : 1) : MODE == kScoreDs4a ? (K >= 1 ? 0 : 1) : 2)
     : K == 0            ? 2
-    : VF != 0           ? (K == 2 ? 1 : 2)
+    : VF != 0           ? (K == 2 ? 0 : 2)
     : MODE == kScorePot ? (K == 3 ? 2 : K == 2 ? 0 : 1)
                         : 0;
 
@@ -847,7 +847,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   // loop below, so the accumulators stay in the matrix-core registers there.
   auto rescale = [&]() {
     if (first) {  // nothing is summed yet
-      first = false;
       m_run = m_new;
       return;
     }
@@ -954,6 +953,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(
   // that every tile uses the same registers.
   auto advance = [&]() {
     kr[0] = kr[1];
+    // also after a tile that raised nothing: scores at -2^31, whose ceiling is INT_MIN
+    // itself, have had their weights summed, and a later maximum takes them out
+    first = false;
     if constexpr (kPool) {
       j = jn;
       jn = jc;

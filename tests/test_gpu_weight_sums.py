@@ -16,11 +16,14 @@ Q = 1.0                                     # every query element: q^ = 127, Del
 X_PER_S = 64 * Q / 8 / np.log(2.0)          # log2-domain score of a key with scale 1
 
 
-def decode(scales, v_bits, waves):
-    """O of one sequence of such keys, eight query heads, one split."""
+def decode(scales, v_bits, waves, negative=None):
+    """O of one sequence of such keys (codes -1 where negative), eight query heads, one split."""
     T = scales.size
     cap = -(-T // 8) * 8
-    se = torch.zeros((cap, 32), dtype=torch.uint8, device=DEV)
+    codes = np.zeros((cap, 32), np.uint8)
+    if negative is not None:
+        codes[:T][negative] = 0x88
+    se = to_dev(codes)
     sc = np.zeros(cap, np.float32)
     sc[:T] = scales
     v = store_values(v_bits, 1, 1, cap)
@@ -51,3 +54,23 @@ def test_constant_values_come_back(waves):
     rel = np.abs(out / v[0].astype(np.float64) - 1).max()
     print(f"waves={waves} |O / v - 1| {rel:.2e}")
     assert rel <= 2.0 ** -19
+
+
+@pytest.mark.parametrize("waves", [4, 16])
+def test_scores_at_minus_two_to_the_31(waves):
+    # -2^31 is its own ceiling and the integer maximum's "none yet". A wave whose first tile
+    # holds only such scores and that meets a higher one later has to drop their weights.
+    step = np.float32(Q) / np.float32(127)
+    c = np.float32(np.float32(step * np.float32(1.44269502162933349609375)) * np.float32(2.0 ** -10))
+    acc = np.float32(-64 * 127 * 128)
+    s = np.float32(2.0 ** 31 / (64 * 127 * 128 * float(c)))
+    near = (s.view(np.int32) + np.arange(-8, 9)).astype(np.int32).view(np.float32)
+    x = (acc * near).astype(np.float32) * c
+    s = near[x == np.float32(-2.0 ** 31)][0]
+    T = 64 * waves * 2
+    scales = np.full(T, s, np.float32)
+    best = 64 * waves + 7                    # wave 0's second tile
+    scales[best] = 3.0 / X_PER_S
+    v = np.random.default_rng(0).standard_normal((T, 64)).astype(np.float16)
+    out = decode(scales, v.view(np.uint16), waves, negative=np.ones(T, bool))
+    assert np.abs(out - v[best].astype(np.float32)).max() <= 1e-6
