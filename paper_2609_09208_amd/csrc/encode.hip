@@ -634,8 +634,8 @@ hipError_t launch_store_values(const uint16_t* src, int64_t n_seq, int64_t n_tok
 // transposed in registers, one exchange per bit of the token index
 // (v_permlane32_swap, v_permlane16_swap, DPP): lane l gets dim 8 (l % 8) + l / 8
 // of all eight tokens, one 8-byte store. One wave per token with byte stores
-// of stride 8 was bound by those stores: 131072 tokens 23.6 us, now 7.9; 2 M
-// tokens 352 us, now 78 (5.2 TB/s). A group per wave: waves that loop over two
+// of stride 8 was bound by those stores: 131072 tokens 21.8 us, now 5.6; 2 M
+// tokens 359 us, now 77 (5.3 TB/s; graph replays). A group per wave: waves that loop over two
 // to sixteen groups took 78 to 98 us. (The same transpose for fp16 values, with
 // its 16-byte stores 128 bytes apart, was slower than the gathers above: 95
 // to 117 us for 2 M tokens against 88.)
@@ -666,18 +666,11 @@ __device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
   b = r[1];
 }
 
-// Grid: x over the groups of a sequence (one per wave), y over sequences.
-template <typename F>
-__device__ __forceinline__ void for_each_group(const ValueRange& r, F&& body) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t stride = (int64_t)gridDim.x * (kBlock / 64);
-  for (int64_t s = blockIdx.y; s < r.n_seq; s += gridDim.y)
-    for (int64_t i = (int64_t)blockIdx.x * (kBlock / 64) + wave; i < r.n_groups; i += stride)
-      body(s, r.g_first + i);
-}
-
 // INT8 values with a power-of-two scale per token (Sec. II-E), as
 // store_value_token_i8_wave defines them.
+// Group i of the range, i counting over sequences and their groups: one per wave
+// (with a workgroup's waves on one sequence, three of four had no group where a
+// sequence has one).
 __global__ __launch_bounds__(kBlock) void store_values_i8_kernel(const uint16_t* __restrict__ src,
                                                                  ValueRange r,
                                                                  uint8_t* __restrict__ v_u8,
@@ -685,7 +678,13 @@ __global__ __launch_bounds__(kBlock) void store_values_i8_kernel(const uint16_t*
   const int lane = lane_id();
   const uint32_t sel16 = (lane >> 4) & 1 ? 0x07060302u : 0x05040100u;
   const uint32_t sel8 = (lane >> 3) & 1 ? 0x03070105u : 0x06020400u;
-  for_each_group(r, [&](int64_t s, int64_t g8) {
+  const uint32_t n = (uint32_t)(r.n_seq * r.n_groups), per_seq = (uint32_t)r.n_groups;
+  const uint32_t stride = gridDim.x * (kBlock / 64);
+  for (uint32_t i = blockIdx.x * (kBlock / 64) +
+                    __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+       i < n; i += stride) {
+    const uint32_t seq = i / per_seq;
+    const int64_t s = seq, g8 = r.g_first + (i - seq * per_seq);
     const uint4 v = load_group(src, r, s, g8, lane);
     const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
     float x[8];
@@ -725,16 +724,30 @@ __global__ __launch_bounds__(kBlock) void store_values_i8_kernel(const uint16_t*
       const int64_t t = g8 * 8 + (lane >> 3);
       if ((lane & 7) == 0 && t >= r.t0 && t < r.t0 + r.n_tok) v_exp[row + (lane >> 3)] = (int8_t)g;
     }
-  });
+  }
 }
 
 static ValueRange value_range(int64_t n_seq, int64_t n_tok, int64_t t_cap, int64_t t0) {
   return {n_seq, n_tok, t_cap, t0, t0 / 8, (t0 + n_tok - 1) / 8 - t0 / 8 + 1};
 }
-static dim3 store_grid(const ValueRange& r) {
-  const int64_t blocks = (r.n_groups + kBlock / 64 - 1) / (kBlock / 64);
-  return dim3((uint32_t)std::min<int64_t>(blocks, 1 << 15),
-              (uint32_t)std::min<int64_t>(r.n_seq, 1 << 15));
+// The same, one wave per token: for calls of one token per sequence, whose groups
+// would have one lane in eight at work (65536 sequences 13.0 us against 18.3, 4096 2.8
+// against 3.3; two tokens 21.4 against 18.3), and for small calls (up to kTokenWaves
+// tokens: 256 sequences of 2 to 8 tokens 2.2 against 2.45; 16 tokens 2.6 and 2.5).
+constexpr int64_t kTokenWaves = 2048;
+__global__ __launch_bounds__(kBlock) void store_tokens_i8_kernel(const uint16_t* __restrict__ src,
+                                                                 ValueRange r,
+                                                                 uint8_t* __restrict__ v_u8,
+                                                                 int8_t* __restrict__ v_exp) {
+  const uint32_t n = (uint32_t)(r.n_seq * r.n_tok), n_tok = (uint32_t)r.n_tok;
+  const uint32_t stride = gridDim.x * (kBlock / 64);
+  for (uint32_t i = blockIdx.x * (kBlock / 64) +
+                    __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+       i < n; i += stride) {
+    const uint32_t s = i / n_tok;
+    store_value_token_i8_wave(src + (int64_t)i * kDim, v_u8 + s * r.t_cap * kDim,
+                              v_exp + s * r.t_cap, r.t0 + (i - s * n_tok));
+  }
 }
 
 hipError_t launch_store_values_i8(const uint16_t* src, int64_t n_seq, int64_t n_tok,
@@ -742,8 +755,13 @@ hipError_t launch_store_values_i8(const uint16_t* src, int64_t n_seq, int64_t n_
                                   hipStream_t stream) {
   if (n_seq == 0 || n_tok == 0) return hipSuccess;
   const ValueRange r = value_range(n_seq, n_tok, t_cap, t0);
-  hipLaunchKernelGGL(store_values_i8_kernel, store_grid(r), dim3(kBlock), 0, stream, src, r, v_u8,
-                     v_exp);
+  const bool tokens = n_tok == 1 || n_seq * n_tok <= kTokenWaves;
+  const int64_t waves = tokens ? n_seq * n_tok : n_seq * r.n_groups;
+  const dim3 grid(bounded_grid((waves + kBlock / 64 - 1) / (kBlock / 64)));
+  if (tokens)
+    hipLaunchKernelGGL(store_tokens_i8_kernel, grid, dim3(kBlock), 0, stream, src, r, v_u8, v_exp);
+  else
+    hipLaunchKernelGGL(store_values_i8_kernel, grid, dim3(kBlock), 0, stream, src, r, v_u8, v_exp);
   return hipGetLastError();
 }
 

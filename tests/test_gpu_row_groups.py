@@ -19,7 +19,11 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n_seq,n_tok,t0,t_cap", [(1, 1, 0, 8), (3, 1, 7, 16), (2, 9, 6, 24),
                                                   (5, 16, 8, 32), (2, 23, 5, 40), (4, 777, 3, 784),
-                                                  (33000, 1, 2, 8)])
+                                                  (33000, 1, 2, 8),
+                                                  # over 2048 tokens: eight tokens per wave
+                                                  (256, 8, 8, 16), (257, 8, 8, 16), (300, 9, 6, 24),
+                                                  (130, 16, 8, 32), (129, 23, 5, 40), (700, 3, 7, 16),
+                                                  (1025, 2, 6, 8), (33000, 2, 3, 8), (1, 4099, 5, 4104)])
 def test_store_int8_ranges(n_seq, n_tok, t0, t_cap):
     rng = np.random.default_rng(n_seq + 10 * n_tok + t0)
     v = (rng.standard_normal((n_seq, n_tok, 64)) * 2.0 ** rng.integers(-12, 9, (n_seq, n_tok, 1)))
@@ -41,7 +45,8 @@ def test_store_int8_ranges(n_seq, n_tok, t0, t_cap):
 
 def test_store_int8_tokens_alone_and_in_a_group():
     # NaN, infinities and mixed signs: what a token becomes depends on nothing but itself
-    # (one-token calls take the partial-group stores, the whole range the group stores)
+    # (one-token calls take a wave per token, the whole range of 129 sequences the group
+    # stores, a range that starts and ends inside groups the partial ones)
     v = np.zeros((1, 16, 64), np.float16)
     v[0, 1] = np.nan
     v[0, 2, ::3] = np.nan
@@ -49,14 +54,21 @@ def test_store_int8_tokens_alone_and_in_a_group():
     v[0, 3, 5] = 65504.0
     v[0, 4] = -(2.0 ** -24)
     v[0, 5:] = np.random.default_rng(3).standard_normal((11, 64)).astype(np.float16)
-    u1, e1 = pa.alloc_value_cache_int8(1, 1, 16, DEV)
+    n = 300
+    v = np.repeat(v, n, axis=0)
+    u1, e1 = pa.alloc_value_cache_int8(n, 1, 16, DEV)
     u2, e2 = pa.alloc_value_cache_int8(1, 1, 16, DEV)
+    u3, e3 = pa.alloc_value_cache_int8(n, 1, 16, DEV)
     src = to_dev(v)
-    pa.pot_store_values_int8(src, 1, 16, 16, 0, u1, e1)
+    pa.pot_store_values_int8(src, n, 16, 16, 0, u1, e1)
     for t in range(16):
-        pa.pot_store_values_int8(src[:, t].contiguous(), 1, 1, 16, t, u2, e2)
+        pa.pot_store_values_int8(src[0, t].contiguous(), 1, 1, 16, t, u2, e2)
+    pa.pot_store_values_int8(src[:, 3:13].contiguous(), n, 10, 16, 3, u3, e3)
     torch.cuda.synchronize()
-    assert torch.equal(u1, u2) and torch.equal(e1, e2)
+    assert torch.equal(u1, u2.expand_as(u1)) and torch.equal(e1, e2.expand_as(e1))
+    byte = lambda u: u.view(-1, 2, 64, 8).transpose(2, 3).reshape(-1, 16, 64)  # [seq][token][dim]
+    assert torch.equal(byte(u3)[:, 3:13], byte(u1)[:, 3:13]) and torch.equal(e3[:, 0, 3:13], e1[:, 0, 3:13])
+    assert not byte(u3)[:, :3].any() and not byte(u3)[:, 13:].any() and not e3[:, 0, 13:].any()
 
 
 @pytest.mark.parametrize("had", [False, True])
