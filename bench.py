@@ -527,7 +527,7 @@ def bulk_encode(pa, lay, dev):
     gbs = n * per_row / (us * 1e-6) / 1e9
     return {"rows": n, "us_per_call": us, "alg_bytes_per_row": per_row, "achieved_gbs": gbs,
             "frac": gbs / HBM_PEAK_GBS, "same_codes_as_cache": same,
-            "kernel": f"potattn::encode_pot_kernel<{k}>",
+            "kernel": f"potattn::encode_pot_kernel<{k}, false>",
             "timing": f"mean of 10 passes over {len(cl)} layers, HIP events around the passes"}
 
 

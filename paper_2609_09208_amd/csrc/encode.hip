@@ -6,16 +6,17 @@
 // so a row is one 16-byte load per lane over 8 lanes and its code word g (the
 // 8 nibbles of those elements) is one 4-byte store; the row scale is a max over
 // 8 values and three DPP lane exchanges. With the optional Walsh-Hadamard
-// rotation it works on 16 rows and rotates them on the matrix cores, exactly
-// (rows with elements above 4096 by fp64 butterflies, eight at a time). Each ratio |x| / s is correctly rounded from
-// one reciprocal per row (a Newton-corrected hardware reciprocal, then
-// Markstein's correction of the quotient). PoT-4 then takes its code from
-// the ratio's bits with integer operations (an add that carries into the
-// exponent exactly above the cut point, a shift and a clamp) and its sign
-// bits from the inputs' sign bits eight at a time by byte permutes; PoT-Mk
-// (K > 0) squares the mantissa against the product of its two grid points. (The INT8
-// comparator's encoder takes the same shape; the fused per-token append in the
-// decode kernel encodes one row per wavefront, one element per lane.)
+// rotation it rotates them by fp64 butterflies or, over many rows, 16 at a time
+// on the matrix cores, exactly (rows with elements above 4096 by the
+// butterflies). Each ratio |x| / s is correctly rounded from one reciprocal per
+// row (a Newton-corrected hardware reciprocal, then Markstein's correction of the
+// quotient). PoT-4 then takes its code from the ratio's bits with integer
+// operations (an add that carries into the exponent exactly above the cut point,
+// a shift and a clamp) and its sign bits from the inputs' sign bits eight at a
+// time by byte permutes; PoT-Mk (K > 0) squares the mantissa against the product
+// of its two grid points. (The INT8 comparator's encoder takes the same shape; the
+// fused per-token append in the decode kernel encodes one row per wavefront, one
+// element per lane.)
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
@@ -374,7 +375,7 @@ __device__ __forceinline__ void encode_rows8(const EncodeArgs& a, int64_t row0,
   }
 }
 
-template <int K>
+template <int K, bool HAD>
 __global__ __launch_bounds__(kBlock) void encode_pot_kernel(const EncodeArgs a,
                                                             const EncodeTables tab) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -384,7 +385,7 @@ __global__ __launch_bounds__(kBlock) void encode_pot_kernel(const EncodeArgs a,
   for (uint32_t grp = blockIdx.x * (kBlock / 64) + wave; grp < groups; grp += stride)
     // the group index as an opaque uniform value: addresses are rebuilt from
     // it each trip as scalar bases plus the fixed lane offsets
-    encode_rows8<K, false>(a, (int64_t)__builtin_amdgcn_readfirstlane(grp) * 8, cut);
+    encode_rows8<K, HAD>(a, (int64_t)__builtin_amdgcn_readfirstlane(grp) * 8, cut);
 }
 
 // Rotated keys: the 64 x 64 Hadamard matrix on the matrix cores, 16 rows per
@@ -400,12 +401,16 @@ __global__ __launch_bounds__(kBlock) void encode_pot_kernel(const EncodeArgs a,
 // code words. Butterflies cost about 250 VALU operations per 8 rows, this 45 per
 // 16 and 16 matrix instructions. Butterflies -> here: 131072 rows k = 0 10.5 -> 9.6,
 // k = 4 14.2 -> 13.5 (now 12.4); 2 M rows k = 0 102 -> 85, k = 4 150 -> 130 us
-// (now 116); up to 16384 rows, one group per wave either way, no difference.
+// (now 116). Up to kButterflyRows rows, where a wave has one group either way, the
+// butterflies are the shorter chain (graph replays, k = 0 and 4: 1 row 2.2 and 2.5 us
+// against 2.8 and 3.1 here, 4096 rows 2.5 and 2.8 against 3.0 and 3.4, 24576 rows 4.0
+// and 4.6 against 4.2 and 5.0; 32768 rows 4.4 and 5.2 against 4.4 and 5.1).
 typedef _Float16 half8e __attribute__((ext_vector_type(8)));
 typedef _Float16 half2e __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x2e __attribute__((ext_vector_type(2)));
 typedef float f32x4e __attribute__((ext_vector_type(4)));
 constexpr uint32_t kExactHalf = 0x6C00;  // 4096 in fp16
+constexpr int64_t kButterflyRows = 24576;
 
 // amdgpu_waves_per_eu(4): 98..104 VGPRs; at five waves the matrix spills.
 template <int K>
@@ -783,11 +788,14 @@ hipError_t launch_encode_pot(const uint16_t* k, int64_t n_rows, int64_t out_stri
                      codes_se, codes_m};
   auto go = [&](auto k_tag) {
     constexpr int KK = decltype(k_tag)::value;
-    if (hadamard)
+    if (hadamard && n_rows > kButterflyRows)
       hipLaunchKernelGGL((encode_pot_had_kernel<KK>), dim3(encode_grid((n_rows + 1) / 2, false)),
                          dim3(kBlock), 0, stream, a, tab);
+    else if (hadamard)
+      hipLaunchKernelGGL((encode_pot_kernel<KK, true>), dim3(encode_grid(n_rows, false)),
+                         dim3(kBlock), 0, stream, a, tab);
     else
-      hipLaunchKernelGGL((encode_pot_kernel<KK>), dim3(encode_grid(n_rows, KK == 0)),
+      hipLaunchKernelGGL((encode_pot_kernel<KK, false>), dim3(encode_grid(n_rows, KK == 0)),
                          dim3(kBlock), 0, stream, a, tab);
   };
   switch (tab.mant_bits) {

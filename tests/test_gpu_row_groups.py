@@ -2,7 +2,8 @@
 the INT8 value store over ranges that start and end inside a group, over more
 sequences than one grid dimension holds and over NaN, infinite and zero tokens;
 the INT8 key encoder over row counts beside a multiple of eight, with a row
-stride; the PoT key encoder likewise, plain and rotated (16 rows per wave), over
+stride; the PoT key encoder likewise, plain and rotated (by butterflies and, 16
+rows per wave, on the matrix cores), over
 values that fall on both of the rotation's paths and at the mantissa cut points.
 Bytes and scales are exact against the oracle; nothing else is written.
 """
@@ -115,6 +116,18 @@ def pot_rows(n, had):
 @pytest.mark.parametrize("n,stride", [(1, 1), (7, 3), (15, 1), (16, 2), (17, 1), (33, 5),
                                       (4099, 1)])
 def test_pot_encode_row_counts(n, stride, mant_bits, had):
+    check_pot_encode(n, stride, mant_bits, had)
+
+
+# rotated on the matrix cores, 16 rows per wave (butterflies up to 24576 rows)
+@pytest.mark.parametrize("mant_bits", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("n,stride", [(24576, 1), (24577, 1), (24583, 3), (24591, 1), (24592, 2),
+                                      (24593, 1), (24609, 1)])
+def test_pot_encode_rotated_on_the_matrix_cores(n, stride, mant_bits):
+    check_pot_encode(n, stride, mant_bits, True)
+
+
+def check_pot_encode(n, stride, mant_bits, had):
     k = pot_rows(n, had)
     se = torch.full((n * stride, 32), 99, dtype=torch.uint8, device=DEV)
     cm = torch.full((n * stride, 8 * max(mant_bits, 1)), 98, dtype=torch.uint8, device=DEV)
