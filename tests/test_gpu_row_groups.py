@@ -4,16 +4,19 @@ sequences than one grid dimension holds and over NaN, infinite and zero tokens;
 the INT8 key encoder over row counts beside a multiple of eight, with a row
 stride; the PoT key encoder likewise, plain and rotated (by butterflies and, 16
 rows per wave, on the matrix cores), over
-values that fall on both of the rotation's paths and at the mantissa cut points.
+values that fall on both of the rotation's paths, and with caller scales that put
+the ratios one ulp below, at and above every cut point.
 Bytes and scales are exact against the oracle; nothing else is written.
 """
+import math
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
 import paper_2609_09208_amd as pa
-from parity_util import DEV, to_dev
+from parity_util import DEV, gpu_encode, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -144,3 +147,58 @@ def check_pot_encode(n, stride, mant_bits, had):
     want_s = np.full(n * stride, -5.0, np.float32)
     want_s[::stride][:n] = osc
     assert np.array_equal(sc.cpu().numpy().view(np.uint32), want_s.view(np.uint32))
+
+
+def cut_points(k):
+    """The fp32 cut points between neighbouring grid values, and the zero cut: the largest fp32
+    below sqrt((n + i)(n + i + 1)) / n * 2^-e (n = 2^k) and below sqrt(2) 2^-7."""
+    n = 1 << k
+    # below sqrt(num / den^2) in [1, 2), rounded down to 24 bits; never a whole root
+    root = lambda num, den: math.ldexp(math.isqrt((num << 46) // den ** 2), -23)
+    cuts = [root((n + i) * (n + i + 1), n) for i in range(n)]
+    return ([np.float32(c * 2.0 ** -e) for c in cuts for e in range(0, 8)]
+            + [np.float32(root(2, 1) * 2.0 ** -7)])
+
+
+def ulps(x, d):
+    return (np.float32(x).view(np.int32) + np.int32(d)).view(np.float32)
+
+
+@pytest.mark.parametrize("path", ["plain", "butterflies", "matrix cores"])
+@pytest.mark.parametrize("k", [0, 1, 2, 3, 4])
+def test_ratios_beside_every_cut_point(k, path):
+    # a row with one element x (rotated: x / 8 times a row of the Hadamard matrix) and a scale s
+    # such that RN(x / s) is the cut, its neighbours and theirs
+    rng = np.random.default_rng(40 + k)
+    rows, scales = [], []
+    for cut in cut_points(k):
+        seen = set()
+        for mant in (1.0, 1.3125, 1.9990234375, 1.5 + 2.0 ** -10):
+            x = np.float32(mant * 2.0 ** rng.integers(-3, 4))
+            for d in range(-6, 7):
+                s = ulps(np.float32(x / cut), d)
+                u = np.float32(x / s)
+                off = int(u.view(np.int32)) - int(cut.view(np.int32))
+                if abs(off) <= 2:
+                    seen.add(off)
+                    m, sign = rng.integers(64), rng.choice([-1.0, 1.0])
+                    if path == "plain":
+                        row = np.zeros(64, np.float16)
+                        row[m] = sign * x
+                    else:                # H row m times x / 8: (H r / 8)_m = 64 x / 64
+                        row = np.array([sign * x / 8 * (-1) ** bin(m & j).count("1")
+                                        for j in range(64)], np.float16)
+                    rows.append(row)
+                    scales.append(s)
+        assert {-1, 0, 1} <= seen, (k, float(cut), seen)
+    rows, scales = np.stack(rows), np.array(scales, np.float32)
+    n = 24700 if path == "matrix cores" else len(rows)
+    reps = -(-n // len(rows))
+    rows, scales = np.tile(rows, (reps, 1)), np.tile(scales, reps)
+    assert (len(rows) > 24576) == (path == "matrix cores")
+    had = path != "plain"
+    se, cm, _ = gpu_encode(rows.view(np.uint16), k, had, scales)
+    ose, ocm, _ = oracle.encode_keys(rows.view(np.uint16), k, hadamard=had, key_scale=scales)
+    assert np.array_equal(se, ose)
+    if k:
+        assert np.array_equal(cm, ocm)
