@@ -109,7 +109,8 @@ typedef struct pot_format {
  *  decode_begin, decode_end (in) NULL, or hipEvent_t handles the caller
  *               created: the call records decode_begin on its stream right
  *               before the decode kernel and decode_end right after it (before
- *               the split combine), so that kernel can be timed alone. They
+ *               the combine kernel, where there is one), so that kernel can be
+ *               timed alone. They
  *               do not select the instrumented build. A failed record returns
  *               POT_ERR_HIP.
  *  force_wg_waves (in) 0: the planner picks the decode workgroup size; 4:
@@ -203,7 +204,8 @@ pot_status pot_store_values_int8(const uint16_t* v_fp16, int64_t n_seq, int64_t 
 
 /* Workspace bytes pot_decode_attention needs for this problem shape: the
  * key-split partials (M_s, l_s, o_s) for the largest split count the planner
- * can choose, and room for query operands of each (batch, kv head, split).
+ * can choose, and room of each (batch, kv head, split) at its head, of which
+ * the merge takes one ticket word per (batch, kv head).
  * Host-only. Returns 0 for invalid shapes. The same figure serves
  * pot_int8_decode_attention and pot_fp16_decode_attention. */
 size_t pot_decode_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv,
@@ -243,10 +245,12 @@ pot_status pot_workspace_init(void* workspace, size_t ws_bytes, void* stream);
  * order; the running maximum is the integer M = ceil(max x)
  * (eq. logsm) so rescales are exact powers of two; weights 2^(x-M) multiply
  * the fp16 values with fp32 accumulation (matrix cores, weights split into
- * fp16 high and low parts); key splits (chosen to give every CU at most one
- * workgroup) are merged with exact 2^(M_s - M) factors.
- * Launches: the split decode kernel (which prepares the queries and merges up
- * to 32 splits) and, with more splits, a combine kernel, both on `stream`.
+ * fp16 high and low parts, summed alike for the denominator); key splits
+ * (chosen to give every CU at most one workgroup, or a few four-wave ones) are
+ * merged with exact 2^(M_s - M) factors.
+ * Launches: the split decode kernel (which prepares the queries and, on
+ * CU-wide workgroups, merges up to 32 splits) and, with more splits or splits of
+ * four-wave workgroups, a combine kernel, both on `stream`.
  */
 pot_status pot_decode_attention(const pot_format* fmt, const float* q,
                                 const uint8_t* codes_se,
@@ -263,8 +267,9 @@ pot_status pot_decode_attention(const pot_format* fmt, const float* q,
  * pot_encode_keys(fmt, k_new, B*Hkv, t_cap, 0, ...) on the rows at T - 1,
  * pot_store_values(v_new, B*Hkv, 1, t_cap, T - 1, v_cache) and
  * pot_decode_attention(...) over T keys, with bit-identical cache contents and
- * output, but without the two extra launches: the query-preparation kernel
- * writes the new rows before the decode kernel starts.
+ * output (where waves claim tiles, see force_wg_waves, O to fp32 rounding), but
+ * without the two extra launches: the decode workgroup whose keys end at T - 1
+ * writes the new row in its prologue, before any of its waves reads that row.
  *  k_new, v_new [B][Hkv][d] fp16, dense, device, 16-byte aligned: the new
  *               token's key (encoded with the row absmax scale, rotated first
  *               when fmt->hadamard) and values.
@@ -356,12 +361,12 @@ pot_status pot_append_decode_attention_v8(const pot_format* fmt, int32_t engine,
  * dbg->force_splits) exceeds POT_NOALLOC_SCRATCH_BYTES -> POT_ERR_WORKSPACE,
  * checked on the host before any HIP call. The bound covers the largest split
  * count the planner may choose: 264 bytes per query head and key split (the
- * split partials) plus one prepared-query slot per kv head and key split
- * (1280 bytes at G = 8). At the TinyLlama shape (Hq = 32, Hkv = 4) it is
+ * split partials) plus room of 1280 bytes (at G = 8) per kv head and key split,
+ * the merge tickets among it. At the TinyLlama shape (Hq = 32, Hkv = 4) it is
  * about 7 MB for B >= 8 and 1.7 MB at B = 1.
  * Every call on one GPU shares that GPU's scratch, which keeps the previous
- * call's contents (the kernels write every word they read, so nothing needs
- * clearing): calls that overlap in time on one GPU race and must not be made. */
+ * call's contents (partials are written before they are read, and a merge
+ * ticket counts only under its own call's tag, so nothing needs clearing): calls that overlap in time on one GPU race and must not be made. */
 pot_status pot_decode_attention_noalloc(const pot_format* fmt, const float* q,
                                         const uint8_t* codes_se, const uint8_t* codes_m,
                                         const float* key_scale, const uint16_t* v_cache,

@@ -354,6 +354,7 @@ def alloc_value_cache_int8(B: int, Hkv: int, t_cap: int, device):
 
 
 def alloc_workspace(nbytes: int, device):
-    """Workspace buffer for the decode calls (zero-filled; the kernels write
-    every word they read, so any contents would do)."""
+    """Workspace buffer for the decode calls (zero-filled, though any contents
+    would do: the kernels write partials before they read them, and a merge
+    ticket counts only under its own call's tag)."""
     return torch.zeros(max(int(nbytes), 256), dtype=torch.uint8, device=device)

@@ -78,8 +78,9 @@ __device__ __forceinline__ float max_f32(float a, float b) {
   return __builtin_amdgcn_fmed3f(a, b, __builtin_inff());
 }
 
-// Waits until this wave's vector stores are acknowledged by the L2, where
-// every later load of the workgroup finds them.
+// Waits until this wave's vector stores are acknowledged: by the L2, where every
+// later load of the workgroup finds them, or, for agent-scope stores, from beyond
+// it. For other XCDs (merge_splits) only the latter counts.
 __device__ __forceinline__ void wait_stores_in_l2() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ---- streaming loads -----------------------------------------------------------
@@ -461,7 +462,11 @@ __device__ __forceinline__ void prepare_queries(const DecodeArgs& a, int kvh, in
 // own L2), and a wave waits until its stores have arrived before the barrier in
 // front of the count. No fence: an agent-scope release or acquire fence writes
 // back or invalidates the whole L2 of the XCD, per workgroup (that took B = 64
-// from 258 to 541 us). Nothing ever waits for another workgroup.
+// from 258 to 541 us). This rests on the hardware and not on the memory model,
+// which orders relaxed accesses to different words by fences only: an agent-scope
+// store that s_waitcnt vmcnt(0) has seen acknowledged is at the point that
+// agent-scope accesses of every XCD go to. Nothing ever waits for another
+// workgroup.
 //
 // The workspace may hold anything before a call. The ticket word is the
 // call's tag (52 bits, never 0) and the count (12 bits); every workgroup first

@@ -2,14 +2,15 @@
 // library owns, for callers that cannot allocate device memory (code under
 // HIP graph capture, tight serving loops).
 //
-// The workspace (prepared query operands and key-split partials) lives in a
+// The workspace (merge tickets and key-split partials) lives in a
 // static device array of POT_NOALLOC_SCRATCH_BYTES, one copy per GPU, held
 // from the library's load until the process ends. Host code never uses the
 // array's name as an address (in host code it names a host-side stand-in):
 // the device address of the current GPU's copy is looked up once per device
 // with hipGetSymbolAddress and cached, and only that address is handed to the
 // kernels, exactly as a caller's workspace would be. The decode kernels write
-// every workspace word they read, so nothing needs clearing between calls.
+// the partials before they read them, and a ticket word counts only under the
+// call's own tag, so nothing needs clearing between calls.
 // Every call on one GPU shares that GPU's copy: calls that overlap in time on
 // one GPU (two streams, or two host threads) race on it.
 #include <hip/hip_runtime.h>

@@ -15,9 +15,8 @@ namespace potattn {
 constexpr int kDim = 64;        // head dimension d
 constexpr int kExpMax = 6;      // E for a 3-bit exponent field (Sec. II-A)
 constexpr int kZeroField = 7;   // e = E + 1 is the exact zero (Sec. II-A)
-constexpr int kQMax = 127;      // symmetric INT8 query
 constexpr int kBlock = 256;     // threads per workgroup (4 waves)
-constexpr int kTile = 256;      // keys per tile, one key per thread in scoring
+constexpr int kTile = 256;      // key splits are whole multiples of this many keys
 
 // fp32 log2(e) rounded to nearest, bit pattern 0x3FB8AA3B.
 __device__ __forceinline__ float log2e_f32() { return __uint_as_float(0x3FB8AA3Bu); }

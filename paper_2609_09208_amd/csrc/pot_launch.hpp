@@ -89,8 +89,10 @@ struct DecodeArgs {
   int32_t* dbg_m_split;
   // fused append (PoT only; app_k NULL: none): the new token of every
   // (batch, kv head) sequence is encoded into cache row T - 1 and its values
-  // stored there by the decode workgroup whose key range holds that row,
-  // before it loads any key
+  // stored there by the decode workgroup whose key range holds that row, in its
+  // prologue. Waves whose first tile does not hold the row request that tile's
+  // keys before; the wave whose first tile holds it, and every later load, comes
+  // after the prologue's barrier
   const uint16_t* app_k;     // fp16 [B*Hkv][64]
   const uint16_t* app_v;     // fp16 [B*Hkv][64]
   uint8_t* app_codes_se;     // the cache arrays, written at row T - 1 only

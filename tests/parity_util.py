@@ -51,8 +51,8 @@ def gpu_pot_decode(d, codes_se, codes_m, key_scale, mant_bits=0, frac_bits=7,
                    hadamard=False, taps=True, force_splits=0, engine="sac", wg_waves=0):
     """d: workloads.make_decode_inputs dict; cache arrays are host numpy in the
     row layout. engine "sac" runs pot_decode_attention (shift-accumulate),
-    "ds4a" pot_ds4a_decode_attention (byte decode + v_dot4), "dot"
-    pot_dot_decode_attention (codes decoded to dot-unit weights, any k).
+    "ds4a" pot_ds4a_decode_attention (PoT-4 codes decoded to fp16 weights), "dot"
+    pot_dot_decode_attention (the same for any k).
     Returns dict of numpy results (taps when requested)."""
     B, Hq, Hkv, T, t_cap = d["B"], d["Hq"], d["Hkv"], d["T"], d["t_cap"]
     fmt = pa.make_format(mant_bits, frac_bits, hadamard)

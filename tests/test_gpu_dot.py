@@ -1,8 +1,7 @@
 """GPU parity of the decoded-weight score path (pot_dot_decode_attention).
 
-PoT-Mk codes are decoded to 16-bit integer weights sigma (2^k + j) 2^(7-e)
-and scored with v_dot2 (PoT-4 goes through the byte path of
-pot_ds4a_decode_attention). The int32 scores are exactly those of eq. (sac)
+Codes are decoded to fp16 weights sigma (1 + j / 2^k) 2^(-8-e) and scored by
+fp16 matrix instructions, exactly. The int32 scores are exactly those of eq. (sac)
 with eq. (mant), so the bar is pot_decode_attention's: codes, q^, Delta,
 scores and integer maxima bit-exact against the oracle, O within 2e-3, over
 every mantissa width and head-group size, ragged tails, head-room, Hadamard,

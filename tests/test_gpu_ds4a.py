@@ -1,7 +1,7 @@
 """GPU parity of the byte-decode score path (pot_ds4a_decode_attention).
 
-The path decodes PoT-4 code nibbles to int8 sigma 2^(6-e) bytes and scores
-them with v_dot4 (a software form of the packed shift-dot of Sec. III,
+The path decodes PoT-4 code nibbles to fp16 weights sigma 2^(-8-e) and scores
+them by fp16 matrix instructions (a software form of the packed shift-dot of Sec. III,
 eq. ds4a). Its int32 scores must be exactly those of the shift-accumulate
 definition, so the bar is the same as for pot_decode_attention: codes,
 q^, Delta, scores and integer maxima bit-exact against the oracle, O within
