@@ -130,7 +130,7 @@ int device_cus() {
 //    with 4.
 //  - That rule rounds down: from half the CUs on it leaves one workgroup per unit
 //    and the other CUs without work. For long ranges (from 12288 keys; at 8192 one
-//    workgroup is as fast, 132 units 35.2 against 34.9) the fp16 comparator and the
+//    workgroup is as fast, 132 units 36.7 and 36.5) the fp16 comparator and the
 //    engines that are bound by their issue take three splits of four-wave
 //    workgroups up to two thirds of the CUs (T = 16384, 160 units: PoT-M1 80.4 ->
 //    76.5, PoT-M4 108 -> 93, fp16 119.9 -> 108.4), PoT-4 and INT8 keys over fp16 values,
