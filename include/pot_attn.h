@@ -366,7 +366,8 @@ pot_status pot_append_decode_attention_v8(const pot_format* fmt, int32_t engine,
  * about 7 MB for B >= 8 and 1.7 MB at B = 1.
  * Every call on one GPU shares that GPU's scratch, which keeps the previous
  * call's contents (partials are written before they are read, and a merge
- * ticket counts only under its own call's tag, so nothing needs clearing): calls that overlap in time on one GPU race and must not be made. */
+ * ticket counts only under its own call's tag, so nothing needs clearing): calls
+ * that overlap in time on one GPU race and must not be made. */
 pot_status pot_decode_attention_noalloc(const pot_format* fmt, const float* q,
                                         const uint8_t* codes_se, const uint8_t* codes_m,
                                         const float* key_scale, const uint16_t* v_cache,

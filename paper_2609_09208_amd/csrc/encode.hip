@@ -736,7 +736,7 @@ static ValueRange value_range(int64_t n_seq, int64_t n_tok, int64_t t_cap, int64
   return {n_seq, n_tok, t_cap, t0, t0 / 8, (t0 + n_tok - 1) / 8 - t0 / 8 + 1};
 }
 // The same, one wave per token: for calls of one token per sequence, whose groups
-// would have one lane in eight at work (65536 sequences 13.0 us against 18.3, 4096 2.8
+// would have one lane in eight at work (65536 sequences 11.4 us against 18.3, 4096 2.6
 // against 3.3; two tokens 21.4 against 18.3), and for small calls (up to kTokenWaves
 // tokens: 256 sequences of 2 to 8 tokens 2.2 against 2.45; 16 tokens 2.6 and 2.5).
 constexpr int64_t kTokenWaves = 2048;
